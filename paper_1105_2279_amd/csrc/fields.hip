@@ -47,79 +47,154 @@ int launch_order(const Geo &g, const LaunchCfg &cfg, int groups_per_block) {
 }
 
 // ------------------------------------------------------------ pack / unpack
-// AoS double[V][4][3][3][2] -> the SoA link layout (LinkLayout).
-// One thread per (stored element, site); the element is blockIdx.y so the
-// SoA writes of a wave are contiguous (every other slot for paired FP32).
+// AoS double[V][4][3][3][2] <-> the SoA link layout (LinkLayout), and the same
+// for Dirac fields.  Both directions are bound by HBM: a site's components
+// are adjacent on the AoS side and a whole array apart on the SoA side, so a
+// block takes a run of consecutive sites, whose AoS image is one contiguous
+// stretch of memory, through LDS and touches global memory only in whole
+// 1 KB wave accesses on both sides.  At 32^3x64 FP32-12 the four conversions
+// (links and a Dirac field, there and back) take 778 us, 5.7 TB/s of the 6.2
+// a streaming kernel reaches; with a thread per component and site, whose
+// AoS accesses were 16 bytes every 576 or 192, they took 3135 us.
+constexpr int kLinkTileSites = 64;   // one site per lane, one direction per wave
+constexpr int kFermTileSites = 128;  // twelve (component pair, half) items for four waves
+// Entries of a site in the LDS tile: one more than it has, so that 16-byte
+// accesses of eight neighbouring sites (one LDS cycle) fall on different banks.
+constexpr int kLinkTilePitch = 36 + 1, kFermTilePitch = 12 + 1;
+
+// ENTRIES entries of each of the block's SITES sites (n of them inside the
+// lattice), contiguous in `mem`, to or from the tile.
+template <int ENTRIES, int SITES, int PITCH>
+__device__ __forceinline__ void aos_to_tile(const double2 *__restrict__ mem, int n, double2 *tile) {
+    constexpr int kPer = ENTRIES * SITES / 256;
+    static_assert(kPer * 256 == ENTRIES * SITES, "whole trips");
+    nv2_t<double> v[kPer];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {  // every load in flight before the first LDS write
+        const int e = i * 256 + (int)threadIdx.x;
+        if (n == SITES || e < n * ENTRIES) v[i] = gptr<nv2_t<double>>(mem)[e];
+    }
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        const int e = i * 256 + (int)threadIdx.x, site = e / ENTRIES;
+        if (n == SITES || e < n * ENTRIES) tile[site * PITCH + (e - site * ENTRIES)] = double2{v[i].x, v[i].y};
+    }
+}
+template <int ENTRIES, int SITES, int PITCH>
+__device__ __forceinline__ void tile_to_aos(const double2 *tile, int n, double2 *__restrict__ mem) {
+    constexpr int kPer = ENTRIES * SITES / 256;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        const int e = i * 256 + (int)threadIdx.x, site = e / ENTRIES;
+        if (n == SITES || e < n * ENTRIES) {
+            const double2 t = tile[site * PITCH + (e - site * ENTRIES)];
+            store_stream<double>(mem + e, t.x, t.y);
+        }
+    }
+}
+
+// One block per 64 sites, wave mu storing the links of direction mu.
 template <typename R, int NR>
 __global__ void __launch_bounds__(256) k_pack_links(Geo g, const double2 *__restrict__ aos,
                                                     vec2_t<R> *__restrict__ soa) {
-    const int s = blockIdx.x * 256 + threadIdx.x;
-    const int comp = blockIdx.y;  // enumerates (mu, a, b) as (mu*NR + a)*3 + b
-    if (s >= g.V) return;
-    const int b = comp % 3, a = (comp / 3) % NR, mu = comp / (3 * NR);
-    const double2 v = aos[((int64_t)s * 4 + mu) * 9 + a * 3 + b];
-    vec2_t<R> o;
-    o.x = (R)v.x;  // FP64 -> FP32 conversion rounds to nearest even
-    o.y = (R)v.y;
-    soa[LinkLayout<R, NR>::slot(mu, a * 3 + b, g.S, s)] = o;
+    __shared__ double2 tile[kLinkTileSites * kLinkTilePitch];
+    const int s0 = blockIdx.x * kLinkTileSites;
+    aos_to_tile<36, kLinkTileSites, kLinkTilePitch>(aos + (int64_t)s0 * 36, min(kLinkTileSites, g.V - s0), tile);
+    __syncthreads();
+    const int lane = threadIdx.x & 63, mu = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (s0 + lane >= g.V) return;
+    Cx<R> e[3][3];
+#pragma unroll
+    for (int c = 0; c < 3 * NR; ++c) {
+        const double2 v = tile[lane * kLinkTilePitch + mu * 9 + c];
+        e[c / 3][c % 3] = Cx<R>{(R)v.x, (R)v.y};  // FP64 -> FP32 conversion rounds to nearest even
+    }
+    const LinksWO<R, NR> out{soa, g.S};
+    out.store(mu, s0 + lane, e);
 }
 
-// SoA -> AoS; one thread per (mu, site), row 2 rebuilt in FP64 for NR == 2.
+// SoA -> AoS, row 2 rebuilt in FP64 for NR == 2.
 template <typename R, int NR>
 __global__ void __launch_bounds__(256) k_unpack_links(Geo g, const vec2_t<R> *__restrict__ soa,
                                                       double2 *__restrict__ aos) {
-    const int s = blockIdx.x * 256 + threadIdx.x;
-    const int mu = blockIdx.y;
-    if (s >= g.V) return;
-    M3<double> m;
+    __shared__ double2 tile[kLinkTileSites * kLinkTilePitch];
+    const int s0 = blockIdx.x * kLinkTileSites;
+    const int lane = threadIdx.x & 63, mu = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (s0 + lane < g.V) {
+        const LinksRO<R, NR> U{soa, g.S};
+        Cx<R> e[3][3];
+        U.template load_rows<false, NR>(mu, s0 + lane, e);
+        M3<double> m;
 #pragma unroll
-    for (int a = 0; a < NR; ++a)
+        for (int c = 0; c < 3 * NR; ++c)
+            m.e[c / 3][c % 3] = Cx<double>{(double)e[c / 3][c % 3].re, (double)e[c / 3][c % 3].im};
+        if constexpr (NR == 2) rebuild_row2(m);
 #pragma unroll
-        for (int b = 0; b < 3; ++b) {
-            const vec2_t<R> v = soa[LinkLayout<R, NR>::slot(mu, a * 3 + b, g.S, s)];
-            m.e[a][b] = Cx<double>{(double)v.x, (double)v.y};
-        }
-    if constexpr (NR == 2) rebuild_row2(m);
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-        for (int b = 0; b < 3; ++b) aos[((int64_t)s * 4 + mu) * 9 + a * 3 + b] = double2{m.e[a][b].re, m.e[a][b].im};
+        for (int c = 0; c < 9; ++c)
+            tile[lane * kLinkTilePitch + mu * 9 + c] = double2{m.e[c / 3][c % 3].re, m.e[c / 3][c % 3].im};
+    }
+    __syncthreads();
+    tile_to_aos<36, kLinkTileSites, kLinkTilePitch>(tile, min(kLinkTileSites, g.V - s0), aos + (int64_t)s0 * 36);
 }
 
-// Index, in complex elements, of component comp of site s in the library's
-// Dirac-field layout (FermLayout: FP32 components paired in 16-byte entries).
-template <typename R> __device__ __forceinline__ int64_t fermion_index(int comp, int s, int64_t S) {
-    if constexpr (FermLayout<R>::kPaired) return ((int64_t)(comp >> 1) * S + s) * 2 + (comp & 1);
-    else return (int64_t)comp * S + s;
-}
-
+// Dirac fields: one block per 128 sites; item i of the SoA side is array
+// i / 2 (FP64: one component; FP32: a pair) of the sites' half i % 2.
 template <typename R>
 __global__ void __launch_bounds__(256) k_pack_fermion(Geo g, const double2 *__restrict__ aos,
                                                       vec2_t<R> *__restrict__ soa) {
-    const int s = blockIdx.x * 256 + threadIdx.x;
-    const int comp = blockIdx.y;  // spin*3 + colour
-    if (s >= g.V) return;
-    const double2 v = aos[(int64_t)s * 12 + comp];
-    vec2_t<R> o;
-    o.x = (R)v.x;
-    o.y = (R)v.y;
-    soa[fermion_index<R>(comp, s, g.S)] = o;
+    __shared__ double2 tile[kFermTileSites * kFermTilePitch];
+    const int s0 = blockIdx.x * kFermTileSites;
+    aos_to_tile<12, kFermTileSites, kFermTilePitch>(aos + (int64_t)s0 * 12, min(kFermTileSites, g.V - s0), tile);
+    __syncthreads();
+    constexpr int kPair = FermLayout<R>::kPaired ? 2 : 1;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+#pragma unroll
+    for (int j = 0; j < 6 / kPair; ++j) {
+        const int i = j * 4 + w, k = i >> 1, site = (i & 1) * 64 + lane;
+        if (s0 + site >= g.V) continue;
+        const double2 *t = tile + site * kFermTilePitch + k * kPair;
+        if constexpr (kPair == 2) {
+            nv4_t<R> v;
+            v.x = (R)t[0].x;
+            v.y = (R)t[0].y;
+            v.z = (R)t[1].x;
+            v.w = (R)t[1].y;
+            __builtin_nontemporal_store(v, gptr_w<nv4_t<R>>((nv4_t<R> *)soa + (int64_t)k * g.S + s0 + site));
+        } else {
+            store_stream<R>(soa + (int64_t)k * g.S + s0 + site, t[0].x, t[0].y);
+        }
+    }
 }
 
 template <typename R>
 __global__ void __launch_bounds__(256) k_unpack_fermion(Geo g, const vec2_t<R> *__restrict__ soa,
                                                         double2 *__restrict__ aos) {
-    const int s = blockIdx.x * 256 + threadIdx.x;
-    const int comp = blockIdx.y;
-    if (s >= g.V) return;
-    const vec2_t<R> v = soa[fermion_index<R>(comp, s, g.S)];
-    aos[(int64_t)s * 12 + comp] = double2{(double)v.x, (double)v.y};
+    __shared__ double2 tile[kFermTileSites * kFermTilePitch];
+    const int s0 = blockIdx.x * kFermTileSites;
+    constexpr int kPair = FermLayout<R>::kPaired ? 2 : 1;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+#pragma unroll
+    for (int j = 0; j < 6 / kPair; ++j) {
+        const int i = j * 4 + w, k = i >> 1, site = (i & 1) * 64 + lane;
+        if (s0 + site >= g.V) continue;
+        double2 *t = tile + site * kFermTilePitch + k * kPair;
+        if constexpr (kPair == 2) {
+            const nv4_t<R> v = gptr<nv4_t<R>>(soa)[(int64_t)k * g.S + s0 + site];
+            t[0] = double2{(double)v.x, (double)v.y};
+            t[1] = double2{(double)v.z, (double)v.w};
+        } else {
+            const nv2_t<R> v = gptr<nv2_t<R>>(soa)[(int64_t)k * g.S + s0 + site];
+            t[0] = double2{(double)v.x, (double)v.y};
+        }
+    }
+    __syncthreads();
+    tile_to_aos<12, kFermTileSites, kFermTilePitch>(tile, min(kFermTileSites, g.V - s0), aos + (int64_t)s0 * 12);
 }
 
-static dim3 site_grid(const Geo &g, int comps) { return dim3((g.V + 255) / 256, comps, 1); }
+static dim3 tile_grid(const Geo &g, int sites) { return dim3((g.V + sites - 1) / sites); }
 
 hipError_t launch_pack_links(const Geo &g, int prec, int nrows, const double *aos, void *soa, hipStream_t st) {
-    const dim3 grid = site_grid(g, 4 * nrows * 3);
+    const dim3 grid = tile_grid(g, kLinkTileSites);
     const double2 *in = reinterpret_cast<const double2 *>(aos);
     if (prec == 0) {
         k_pack_links<double, 3><<<grid, 256, 0, st>>>(g, in, (double2 *)soa);
@@ -132,7 +207,7 @@ hipError_t launch_pack_links(const Geo &g, int prec, int nrows, const double *ao
 }
 
 hipError_t launch_unpack_links(const Geo &g, int prec, int nrows, const void *soa, double *aos, hipStream_t st) {
-    const dim3 grid = site_grid(g, 4);
+    const dim3 grid = tile_grid(g, kLinkTileSites);
     double2 *out = reinterpret_cast<double2 *>(aos);
     if (prec == 0) {
         k_unpack_links<double, 3><<<grid, 256, 0, st>>>(g, (const double2 *)soa, out);
@@ -145,7 +220,7 @@ hipError_t launch_unpack_links(const Geo &g, int prec, int nrows, const void *so
 }
 
 hipError_t launch_pack_fermion(const Geo &g, int prec, const double *aos, void *soa, hipStream_t st) {
-    const dim3 grid = site_grid(g, 12);
+    const dim3 grid = tile_grid(g, kFermTileSites);
     const double2 *in = reinterpret_cast<const double2 *>(aos);
     if (prec == 0) k_pack_fermion<double><<<grid, 256, 0, st>>>(g, in, (double2 *)soa);
     else k_pack_fermion<float><<<grid, 256, 0, st>>>(g, in, (float2 *)soa);
@@ -153,7 +228,7 @@ hipError_t launch_pack_fermion(const Geo &g, int prec, const double *aos, void *
 }
 
 hipError_t launch_unpack_fermion(const Geo &g, int prec, const void *soa, double *aos, hipStream_t st) {
-    const dim3 grid = site_grid(g, 12);
+    const dim3 grid = tile_grid(g, kFermTileSites);
     double2 *out = reinterpret_cast<double2 *>(aos);
     if (prec == 0) k_unpack_fermion<double><<<grid, 256, 0, st>>>(g, (const double2 *)soa, out);
     else k_unpack_fermion<float><<<grid, 256, 0, st>>>(g, (const float2 *)soa, out);
@@ -477,6 +552,8 @@ __global__ void __launch_bounds__(256) k_copy_fermion(Geo g, const V *__restrict
     const int64_t o = (int64_t)blockIdx.y * g.S + s;
     dst[o] = src[o];
 }
+
+static dim3 site_grid(const Geo &g, int comps) { return dim3((g.V + 255) / 256, comps, 1); }
 
 // One 16-byte entry per (array, site): 12 arrays of double2 (FP64) or the
 // six paired arrays of FP32 fields.
