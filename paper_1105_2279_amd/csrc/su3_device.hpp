@@ -511,9 +511,18 @@ __device__ __forceinline__ void reunitarise(const Cx<double> w[2][3], Cx<double>
 // (V exp(-i arg(det V) / 3)).  For a 3x3 matrix with rows x0, x1, x2 the
 // cofactor matrix has rows x1 x x2, x2 x x0, x0 x x1 (plain cross products)
 // and det X = x0 . (x1 x x2), so X^(-dag) = conj(cofactors) / conj(det).
-// kPolarIters iterations reach FP64 rounding for the condition numbers that
-// APE combinations have (below about 1e3).  A singular W gives NaN.
+// A singular W gives NaN.
+//
+// The projection is bound by FP64 VALU issue.  After any step every singular
+// value of X is at least 1, so ||X||_F^2 - 3 bounds their distance from 1;
+// a lane whose bound is below kPolarLast squares it with one more step and
+// stops (five or six steps for the condition numbers that APE combinations
+// have; kPolarIters, for those beyond 1e3, ends the loop in any case).  Any
+// positive z has the same limit, so z comes from the hardware estimates and
+// is 1, exactly, once the bound is below kPolarUnscaled, where it no longer
+// helps and its error would be one of X.
 constexpr int kPolarIters = 9;
+constexpr double kPolarUnscaled = 0.03125, kPolarLast = 0x1p-26;
 
 __device__ __forceinline__ Cx<double> cmul(const Cx<double> &a, const Cx<double> &b) {
     return Cx<double>{fma(a.re, b.re, -a.im * b.im), fma(a.re, b.im, a.im * b.re)};
@@ -523,25 +532,46 @@ __device__ __forceinline__ void cross3(const Cx<double> a[3], const Cx<double> b
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         const int i = (k + 1) % 3, j = (k + 2) % 3;
-        const Cx<double> t1 = cmul(a[i], b[j]), t2 = cmul(a[j], b[i]);
-        c[k] = Cx<double>{t1.re - t2.re, t1.im - t2.im};
+        const Cx<double> t = conj_cross(a[i], b[j], a[j], b[i]);
+        c[k] = Cx<double>{t.re, -t.im};
     }
+}
+// 1/d: the hardware reciprocal refined by two Newton steps (as rsqrt_nr)
+__device__ __forceinline__ double rcp_nr(double d) {
+    double y = __builtin_amdgcn_rcp(d);
+#pragma unroll
+    for (int it = 0; it < 2; ++it) y = fma(y, fma(-d, y, 1.0), y);
+    return y;
+}
+__device__ __forceinline__ Cx<double> row_dot(const Cx<double> a[3], const Cx<double> b[3]) {
+    Cx<double> d = cmul(a[0], b[0]);
+    cmac(d, a[1], b[1]);
+    cmac(d, a[2], b[2]);
+    return d;
+}
+
+// exp(-i arg(d) / 3), principal branch, for |d| = 1 to rounding: an FP32
+// estimate w (the signs of d are those of its FP32 parts, so the branch is
+// too), then w t^(-1/3), t = w^3 d, by its series about t = 1 to second order:
+// |t - 1| is below 1e-5, the third order below 1e-16.
+__device__ __forceinline__ Cx<double> det_phase(const Cx<double> &d) {
+    const float th = atan2f((float)d.im, (float)d.re) * (-1.0f / 3.0f);
+    const Cx<double> w{(double)cosf(th), (double)sinf(th)};
+    const Cx<double> t = cmul(cmul(cmul(w, w), w), d);
+    const Cx<double> u{t.re - 1.0, t.im};
+    const Cx<double> u2 = cmul(u, u);
+    constexpr double k1 = -1.0 / 3.0, k2 = 2.0 / 9.0;
+    return cmul(w, Cx<double>{fma(k2, u2.re, fma(k1, u.re, 1.0)), fma(k2, u2.im, k1 * u.im)});
 }
 
 __device__ __forceinline__ void polar_project(Cx<double> x[3][3], Cx<double> v[3][3]) {
 #pragma unroll 1
-    for (int it = 0; it < kPolarIters; ++it) {
+    for (int it = 0; it < kPolarIters; ++it) {  // a lane leaves when it is done, whatever the others do
         Cx<double> c[3][3];
         cross3(x[1], x[2], c[0]);
         cross3(x[2], x[0], c[1]);
         cross3(x[0], x[1], c[2]);
-        Cx<double> d{0.0, 0.0};
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const Cx<double> t = cmul(x[0][k], c[0][k]);
-            d.re += t.re;
-            d.im += t.im;
-        }
+        const Cx<double> d = row_dot(x[0], c[0]);
         double nx = 0.0, nc = 0.0;
 #pragma unroll
         for (int i = 0; i < 3; ++i)
@@ -550,33 +580,26 @@ __device__ __forceinline__ void polar_project(Cx<double> x[3][3], Cx<double> v[3
                 nx = fma(x[i][j].re, x[i][j].re, fma(x[i][j].im, x[i][j].im, nx));
                 nc = fma(c[i][j].re, c[i][j].re, fma(c[i][j].im, c[i][j].im, nc));
             }
-        const double dd = fma(d.re, d.re, d.im * d.im);  // |det|^2
-        // z^4 = ||X^-1||_F^2 / ||X||_F^2 = (nc / dd) / nx
-        const double z = sqrt(sqrt(nc / (dd * nx)));
-        const double hz = 0.5 * z, hiz = 0.5 / z;
-        const double rdd = 1.0 / dd;
+        const double bound = it > 0 ? nx - 3.0 : 1.0;  // W itself may have singular values below 1
+        const double rdd = rcp_nr(fma(d.re, d.re, d.im * d.im));  // 1 / |det|^2
+        // z^4 = ||X^-1||_F^2 / ||X||_F^2 = (nc / |det|^2) / nx
+        const double zs = __builtin_amdgcn_rsq(__builtin_amdgcn_rsq((nc * rdd) * __builtin_amdgcn_rcp(nx)));
+        const double z = bound < kPolarUnscaled ? 1.0 : zs;
+        const double hz = 0.5 * z, k = 0.5 * rcp_nr(z) * rdd;
+        // X^(-dag) / (2 z) = conj(c) g, g = det / (2 z |det|^2)
+        const Cx<double> g{k * d.re, k * d.im};
 #pragma unroll
         for (int i = 0; i < 3; ++i)
 #pragma unroll
             for (int j = 0; j < 3; ++j) {
-                // conj(c_ij) / conj(d) = conj(c_ij conj(d)) / |d|^2
-                const Cx<double> cd{fma(c[i][j].re, d.re, c[i][j].im * d.im), fma(c[i][j].im, d.re, -c[i][j].re * d.im)};
-                const Cx<double> y{cd.re * rdd, -cd.im * rdd};
-                x[i][j] = Cx<double>{fma(hz, x[i][j].re, hiz * y.re), fma(hz, x[i][j].im, hiz * y.im)};
+                x[i][j].re = fma(c[i][j].re, g.re, fma(c[i][j].im, g.im, hz * x[i][j].re));
+                x[i][j].im = fma(c[i][j].re, g.im, fma(-c[i][j].im, g.re, hz * x[i][j].im));
             }
+        if (bound < kPolarLast) break;
     }
     Cx<double> c0[3];
     cross3(x[1], x[2], c0);
-    Cx<double> d{0.0, 0.0};
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const Cx<double> t = cmul(x[0][k], c0[k]);
-        d.re += t.re;
-        d.im += t.im;
-    }
-    double sn, cs;
-    sincos(-atan2(d.im, d.re) / 3.0, &sn, &cs);
-    const Cx<double> ph{cs, sn};
+    const Cx<double> ph = det_phase(row_dot(x[0], c0));
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
