@@ -406,9 +406,9 @@ int qdpx_jit_eval(qdpx_ctx *ctx, int32_t kernel, const qdpx_geom *geom, const vo
  * QDPX_OP_SHIFT, QDPX_OP_CHAIN or QDPX_OP_JACOBI) on `geom` and remember the
  * fastest in the context: threads per block, consecutive 64-site groups per
  * wave, the block order over the 8 XCDs (xcd_map 0: dispatch order; 1: each
- * XCD a contiguous range of groups; 2: each XCD a slab of z planes walked t
- * plane by t plane, used where the groups of a t plane split evenly over the
- * XCDs, else order 0), the number of t planes walked together, and the LDS
+ * XCD a contiguous range of groups; 2: each XCD tiles of the (y, z) cross
+ * section that its L2 holds, each walked t plane by t plane, used where the
+ * groups of a t plane are a whole number, else order 0), the number of t planes walked together, and the LDS
  * tile of the FP32 APE step with the Gram-Schmidt projection (lds_tile 0:
  * every link loaded through the caches; 1: each 64-site group's own links,
  * rows 0 and 1, staged in LDS once for the four direction waves; 2: also
@@ -430,8 +430,7 @@ int qdpx_jit_eval(qdpx_ctx *ctx, int32_t kernel, const qdpx_geom *geom, const vo
  * for the default geometry, 1 for one read from the launch table, 2 for one
  * qdpx_tune found, 3 for one qdpx_tune_set gave; a launch table written
  * without lds_tile gives the default, 4 for the FP32 APE step, else 0);
- * t_window must divide Lt and only matters when Lx is a multiple of 8 and Ly
- * of 8 (or Lx of 16 and Ly of 4).  For QDPX_OP_BATCHED (tuned by
+ * t_window must divide Lt and only matters when Lx Ly Lz is a multiple of 64.  For QDPX_OP_BATCHED (tuned by
  * qdpx_tune_batched, which qdpx_tune refuses with QDPX_EUNSUPPORTED) block is
  * 256 or 512 and sites_per_thread is the number of 64-site groups per work
  * ticket, keyed by the first lattice's extents. */

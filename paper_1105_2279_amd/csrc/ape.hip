@@ -48,8 +48,9 @@ __global__ void __launch_bounds__(512) k_ape_step(Geo g, LinksRO<R, NR> U, Links
 #pragma unroll 1
         for (int j = 0; j < NS; ++j) {  // no early exit: every wave meets every barrier
             const int i = (tile * NS + j) * gpb + (w >> 2);
-            const bool valid = i < ngroups;
-            const int grp = !valid ? 0 : xcd == 2 ? slabwalk(g, i, gpb * NS) : traverse(g, i, tw);
+            const int gi = xcd == 2 ? slabwalk(g, i, gpb * NS) : i < ngroups ? traverse(g, i, tw) : -1;
+            const bool valid = gi >= 0;
+            const int grp = valid ? gi : 0;
             if (j > 0) __syncthreads();  // the previous group's copies have been read
             if (valid) {
                 stage_own_link(g, U, grp, mu, lane, mine);
@@ -73,8 +74,8 @@ __global__ void __launch_bounds__(512) k_ape_step(Geo g, LinksRO<R, NR> U, Links
 #pragma unroll 1
     for (int j = 0; j < NS; ++j) {
         const int i = (tile * NS + j) * gpb + (w >> 2);
-        if (i >= ngroups) return;
-        const int grp = xcd == 2 ? slabwalk(g, i, gpb * NS) : traverse(g, i, tw);
+        const int grp = xcd == 2 ? slabwalk(g, i, gpb * NS) : i < ngroups ? traverse(g, i, tw) : -1;
+        if (grp < 0) continue;
         ape_group<R, NR, MODE, PROJ>(g, U, out, c1, c2, mask, partials, grp, mu, lane, nullptr,
                                      sizeof(R) == 8 ? lds_dyn + w * kF64BackPerWave : nullptr);
     }
@@ -89,11 +90,8 @@ hipError_t launch_ape_step(const Geo &g, int prec, int nrows, const void *Uin, v
     if (mode == kApePlaq && mask != 0xFu) return hipErrorInvalidValue;  // owned planes need every staple
     if (proj && mode != kApe) return hipErrorInvalidValue;             // polar: plaquettes in their own pass
     if (prec != 0 && mode != kApe) return hipErrorInvalidValue;        // FP32: plaquettes from k_plaquette
-    const int groups = (g.V + 63) / 64;
     const int gpb = cfg.block / 256;
-    const int per_block = gpb * cfg.nsite;
-    const dim3 grid((groups + per_block - 1) / per_block);
-    const int xcd = launch_order(g, cfg, per_block);
+    const int grid = cfg.grid, xcd = cfg.xcd;
     const int lds_level = (prec != 0 && !proj) ? cfg.lds : 0;
     const size_t lds64 = (prec == 0 && !proj) ? sizeof(double2) * kF64BackPerWave * (cfg.block / 64)
                                               : (size_t)16 * ape_lds_f4_per_group(lds_level) * gpb;

@@ -349,6 +349,23 @@ static bool stream_capturing(hipStream_t st) {
     return s == hipStreamCaptureStatusActive;
 }
 
+// Bytes of each site that operation op reads again from neighbouring sites:
+// links as the kernel reads them, the Dirac field it shifts, or (JACOBI, whose
+// links one neighbour reads again, not all) the field and half the links.
+static int reread_bytes(qdpx_op op, qdpx_prec prec, qdpx_linkfmt fmt) {
+    const int links = 4 * (prec == QDPX_F64 ? 96 : fmt == QDPX_LINK12 ? 48 : 72), field = prec == QDPX_F64 ? 192 : 96;
+    return op == QDPX_OP_APE ? links : op == QDPX_OP_JACOBI ? links / 2 + field : field;
+}
+
+static bool fwd_only(qdpx_op op) { return op == QDPX_OP_SHIFT || op == QDPX_OP_CHAIN; }
+static int groups_per_block(qdpx_op op, const LaunchCfg &c) { return op == QDPX_OP_APE ? c.block / 256 * c.nsite : c.nsite; }
+
+// Default block order: where what an XCD's eighth of the lattice reads again
+// fits its L2, contiguous ranges of groups (every neighbour is read from
+// beyond the L2 once, and a lattice of few groups has no tiles); above, the
+// slab walk.
+constexpr int64_t kXcdL2 = 4 << 20;
+
 static LaunchCfg cfg_for(qdpx_ctx *ctx, qdpx_op op, const qdpx_geom *geom, qdpx_prec prec, qdpx_linkfmt fmt) {
     LaunchCfg c;
     if (op == QDPX_OP_BATCHED) c.nsite = 1;  // groups per ticket
@@ -356,8 +373,28 @@ static LaunchCfg cfg_for(qdpx_ctx *ctx, qdpx_op op, const qdpx_geom *geom, qdpx_
     if (ctx) {
         TuneKey k{(int)op, (int)prec, (int)fmt, {geom->L[0], geom->L[1], geom->L[2], geom->L[3]}};
         auto it = ctx->tuned.find(k);
-        if (it != ctx->tuned.end()) c = it->second.cfg;
+        if (it != ctx->tuned.end()) return it->second.cfg;
     }
+    if (op == QDPX_OP_APE || op == QDPX_OP_SHIFT || op == QDPX_OP_CHAIN || op == QDPX_OP_JACOBI) {
+        Geo g = make_geo(geom->L);
+        const int bytes = reread_bytes(op, prec, fmt);
+        if ((int64_t)g.V / kXcds * bytes > kXcdL2 && tile_plan(g, bytes, fwd_only(op), groups_per_block(op, c))) c.xcd = 2;
+    }
+    return c;
+}
+
+// The launch of op in the directions of mask on g: its geometry and, in g,
+// the tiles of its block order.  Without the t direction the slab walk has
+// nothing to keep for the next t plane and its tiles' halos are read for
+// nothing: contiguous ranges, unless the lattice is so large (kFarRanges an
+// XCD) that eight ranges that far apart cost more than the halos (FP64 Jacobi
+// hop in x, y, z: 51.8 against 55.1 us at 20^3x40, 15 MB; 127.9 against 117.6
+// us at 24^3x48, 32 MB).
+constexpr int64_t kFarRanges = 28 << 20;
+
+static LaunchCfg plan_launch(Geo &g, LaunchCfg c, qdpx_op op, qdpx_prec prec, qdpx_linkfmt fmt, uint32_t mask = 0xF) {
+    if (c.xcd == 2 && !(mask & 8) && (int64_t)g.V / kXcds * reread_bytes(op, prec, fmt) <= kFarRanges) c.xcd = 1;
+    order_blocks(g, c, groups_per_block(op, c), reread_bytes(op, prec, fmt), fwd_only(op));
     return c;
 }
 
@@ -453,8 +490,8 @@ extern "C" int qdpx_eval_shift_mul_axpy(qdpx_ctx *ctx, const qdpx_geom *geom, qd
     if (norm2 && (overlap(work, need, chi, fb) || overlap(work, need, psi, fb) || overlap(work, need, phi, fb) ||
                   overlap(work, need, U, lb)))
         return fail(QDPX_EALIAS, "%s: workspace overlaps a field", fn);
-    const Geo g = make_geo(geom->L);
-    const LaunchCfg cfg = cfg_for(ctx, QDPX_OP_SHIFT, geom, prec, fmt);
+    Geo g = make_geo(geom->L);
+    const LaunchCfg cfg = plan_launch(g, cfg_for(ctx, QDPX_OP_SHIFT, geom, prec, fmt), QDPX_OP_SHIFT, prec, fmt, dir_mask);
     hipStream_t st = (hipStream_t)stream;
     double *part = norm2 ? (double *)work : nullptr;
     QDPX_TRY_HIP(launch_shift(g, prec, nrows_of(fmt), U, psi, phi, a, 0, 0.0, chi, part, cfg, st, dir_mask,
@@ -475,7 +512,7 @@ extern "C" int qdpx_eval_shift_mul_axpy_noalloc(qdpx_ctx *ctx, const qdpx_geom *
     QDPX_CHECK_CTX(fn);
     if (!geom_ok(geom, fn)) return QDPX_EINVAL;
     if (int r = check_format(prec, fmt, fn)) return r;
-    const Geo g = make_geo(geom->L);
+    Geo g = make_geo(geom->L);
     if (g.V > kNoAllocMaxSites)
         return fail(QDPX_EINVAL, "%s: %d sites exceed the %d sites its fixed scratch memory holds", fn, g.V,
                     kNoAllocMaxSites);
@@ -491,7 +528,7 @@ extern "C" int qdpx_eval_shift_mul_axpy_noalloc(qdpx_ctx *ctx, const qdpx_geom *
     const int np = shift_num_partials(g);
     if ((size_t)np + (size_t)finalize_stage_a_blocks(np) > (size_t)kNoAllocDoubles)
         return fail(QDPX_EINVAL, "%s: scratch memory too small for %d partials", fn, np);
-    const LaunchCfg cfg = cfg_for(ctx, QDPX_OP_SHIFT, geom, prec, fmt);
+    const LaunchCfg cfg = plan_launch(g, cfg_for(ctx, QDPX_OP_SHIFT, geom, prec, fmt), QDPX_OP_SHIFT, prec, fmt, dir_mask);
     hipStream_t st = (hipStream_t)stream;
     double *part = norm2 ? ctx->scratch : nullptr;
     QDPX_TRY_HIP(launch_shift(g, prec, nrows_of(fmt), U, psi, phi, a, 0, 0.0, chi, part, cfg, st, dir_mask,
@@ -520,8 +557,8 @@ extern "C" int qdpx_shift_chain(qdpx_ctx *ctx, const qdpx_geom *geom, qdpx_prec 
     if (overlap(psi, fb, phi, fb) || overlap(psi, fb, U, lb)) return fail(QDPX_EALIAS, "%s: psi overlaps an input", fn);
     if (overlap(work, need, psi, fb) || overlap(work, need, phi, fb) || overlap(work, need, U, lb))
         return fail(QDPX_EALIAS, "%s: workspace overlaps a field", fn);
-    const Geo g = make_geo(geom->L);
-    const LaunchCfg cfg = cfg_for(ctx, QDPX_OP_CHAIN, geom, prec, fmt);
+    Geo g = make_geo(geom->L);
+    const LaunchCfg cfg = plan_launch(g, cfg_for(ctx, QDPX_OP_CHAIN, geom, prec, fmt), QDPX_OP_CHAIN, prec, fmt);
     hipStream_t st = (hipStream_t)stream;
     void *tmp = work;
     double *part = (double *)((char *)work + round256(fb));
@@ -550,8 +587,8 @@ extern "C" int qdpx_eval_hop(qdpx_ctx *ctx, const qdpx_geom *geom, qdpx_prec pre
     if (dir_mask & ~0xFu) return fail(QDPX_EINVAL, "%s: dir_mask 0x%x has bits beyond the 4 directions", fn, dir_mask);
     const size_t fb = qdpx_fermion_bytes(geom, prec), lb = qdpx_links_bytes(geom, prec, fmt);
     if (overlap(out, fb, psi, fb) || overlap(out, fb, U, lb)) return fail(QDPX_EALIAS, "%s: out overlaps an input", fn);
-    const Geo g = make_geo(geom->L);
-    const LaunchCfg cfg = cfg_for(ctx, QDPX_OP_JACOBI, geom, prec, fmt);
+    Geo g = make_geo(geom->L);
+    const LaunchCfg cfg = plan_launch(g, cfg_for(ctx, QDPX_OP_JACOBI, geom, prec, fmt), QDPX_OP_JACOBI, prec, fmt, dir_mask);
     QDPX_TRY_HIP(launch_hop(g, prec, nrows_of(fmt), U, psi, nullptr, 1.0, 1.0, false, dir_mask, out, cfg,
                             (hipStream_t)stream),
                  fn);
@@ -578,8 +615,8 @@ extern "C" int qdpx_jacobi_smear(qdpx_ctx *ctx, const qdpx_geom *geom, qdpx_prec
     if (overlap(chi, fb, U, lb)) return fail(QDPX_EALIAS, "%s: chi overlaps U", fn);
     if (overlap(work, need, chi, fb) || overlap(work, need, U, lb))
         return fail(QDPX_EALIAS, "%s: workspace overlaps a field", fn);
-    const Geo g = make_geo(geom->L);
-    const LaunchCfg cfg = cfg_for(ctx, QDPX_OP_JACOBI, geom, prec, fmt);
+    Geo g = make_geo(geom->L);
+    const LaunchCfg cfg = plan_launch(g, cfg_for(ctx, QDPX_OP_JACOBI, geom, prec, fmt), QDPX_OP_JACOBI, prec, fmt, dir_mask);
     hipStream_t st = (hipStream_t)stream;
     void *s0 = work;
     void *tmp = (char *)work + round256(fb);
@@ -645,8 +682,8 @@ extern "C" int qdpx_ape_smear(qdpx_ctx *ctx, const qdpx_geom *geom, qdpx_prec pr
     if (overlap(U_in, lb, U_out, lb)) return fail(QDPX_EALIAS, "%s: U_out overlaps U_in", fn);
     if (need_work && (overlap(work, need, U_in, lb) || overlap(work, need, U_out, lb)))
         return fail(QDPX_EALIAS, "%s: workspace overlaps the links", fn);
-    const Geo g = make_geo(geom->L);
-    const LaunchCfg cfg = cfg_for(ctx, QDPX_OP_APE, geom, prec, fmt);
+    Geo g = make_geo(geom->L);
+    const LaunchCfg cfg = plan_launch(g, cfg_for(ctx, QDPX_OP_APE, geom, prec, fmt), QDPX_OP_APE, prec, fmt, smear_mask);
     hipStream_t st = (hipStream_t)stream;
     void *tmp = (n_steps >= 2) ? work : nullptr;
     double *part = (double *)((char *)work + (n_steps >= 2 ? round256(lb) : 0));
@@ -792,8 +829,8 @@ extern "C" int qdpx_ape_smear_batched(qdpx_ctx *ctx, int n_lat, const qdpx_geom 
         base += batched_lattice_bytes(&geoms[i], prec, fmt);
         L.ngroups = (L.g.V + 63) / 64;
         const int per_t = L.g.L[0] * L.g.L[1] * L.g.L[2];
-        if (L.g.bwl || per_t % 64 == 0) {
-            L.ncol = per_t / 64;  // bricks (or runs of 64 sites) of one t plane
+        if (per_t % 64 == 0) {
+            L.ncol = per_t / 64;  // runs of 64 sites of one t plane
             L.nrow = L.g.L[3];
         } else {
             L.ncol = L.ngroups;
@@ -930,7 +967,7 @@ extern "C" int qdpx_tune(qdpx_ctx *ctx, qdpx_op op, const qdpx_geom *geom, qdpx_
                     (int)op);
     hipStream_t st = (hipStream_t)stream;
     if (stream_capturing(st)) return fail(QDPX_ECAPTURE, "%s: stream is capturing", fn);
-    const Geo g = make_geo(geom->L);
+    const Geo geo = make_geo(geom->L);
     const size_t lb = qdpx_links_bytes(geom, prec, fmt), fb = qdpx_fermion_bytes(geom, prec);
     std::vector<void *> bufs;
     auto alloc = [&](size_t n) -> void * {
@@ -953,7 +990,7 @@ extern "C" int qdpx_tune(qdpx_ctx *ctx, qdpx_op op, const qdpx_geom *geom, qdpx_
         A = alloc(fb);
         B = alloc(fb);
         C = alloc(fb);
-        part = alloc(reduce_bytes(shift_num_partials(g), 1));
+        part = alloc(reduce_bytes(shift_num_partials(geo), 1));
     }
     if (!U || !A || (op != QDPX_OP_APE && (!B || !C || !part))) {
         release();
@@ -966,7 +1003,7 @@ extern "C" int qdpx_tune(qdpx_ctx *ctx, qdpx_op op, const qdpx_geom *geom, qdpx_
     const int tws[] = {1, 2, 4, 8, 16};
     for (int x = 0; x < 3; ++x)
         for (int tw : tws) {
-            if (geom->L[3] % tw || (tw > 1 && (g.bwl == 0 || x == 2))) continue;
+            if (geom->L[3] % tw || (tw > 1 && (geo.ncol == 0 || x == 2))) continue;
             if (op == QDPX_OP_APE) {
                 for (int b : blocks_ape)
                     for (int n : ns_ape)
@@ -982,7 +1019,9 @@ extern "C" int qdpx_tune(qdpx_ctx *ctx, qdpx_op op, const qdpx_geom *geom, qdpx_
         return fail(QDPX_EHIP, "%s: could not create timing events", fn);
     }
     const int nrows = nrows_of(fmt);
-    auto run = [&](const LaunchCfg &c) -> hipError_t {
+    auto run = [&](const LaunchCfg &cand) -> hipError_t {
+        Geo g = geo;
+        const LaunchCfg c = plan_launch(g, cand, op, prec, fmt);
         if (op == QDPX_OP_APE) return launch_ape_step(g, prec, nrows, U, A, 0.5, 0.5 / 6.0, 0xFu, nullptr, 0, c, st);
         if (op == QDPX_OP_JACOBI) return launch_hop(g, prec, nrows, U, A, B, 0.1, 1.0, false, 0xFu, C, c, st);
         return launch_shift(g, prec, nrows, U, A, B, 0.3, op == QDPX_OP_CHAIN ? 1 : 0, 0.1, C, (double *)part, c, st);

@@ -16,24 +16,22 @@ Geo make_geo(const int32_t L[4]) {
     g.st[3] = L[0] * L[1] * L[2];
     g.V = g.st[3] * L[3];
     g.S = ((int64_t)g.V + 255) / 256 * 256;
-    g.bwl = g.P = g.pbx = g.ncol = 0;
-    if (L[0] % 16 == 0 && L[1] % 4 == 0) {
-        g.bwl = 4;
-        g.pbx = L[0] / 16;
-        g.P = g.pbx * (L[1] / 4);
-    } else if (L[0] % 8 == 0 && L[1] % 8 == 0) {
-        g.bwl = 3;
-        g.pbx = L[0] / 8;
-        g.P = g.pbx * (L[1] / 8);
-    }
-    if (g.bwl || g.st[3] % 64 == 0) g.ncol = g.st[3] / 64;
+    g.P = g.st[2] % 64 == 0 ? g.st[2] / 64 : 0;
+    g.ncol = g.st[3] % 64 == 0 ? g.st[3] / 64 : 0;
     g.dL0 = FastDiv::make(L[0]);
     g.dL1 = FastDiv::make(L[1]);
     g.dL2 = FastDiv::make(L[2]);
     g.dP = FastDiv::make(g.P ? g.P : 1);
-    g.dpbx = FastDiv::make(g.pbx ? g.pbx : 1);
-    g.dplane = FastDiv::make(g.P ? g.P * L[2] : 1);
-    g.dslab = FastDiv::make(g.ncol >= 8 ? g.ncol >> 3 : 1);
+    g.dncol = FastDiv::make(g.ncol ? g.ncol : 1);
+    // the slab walk's tiles: eight of ncol / 8 consecutive columns (tile_plan
+    // chooses others)
+    g.pz = g.ncol;
+    g.nz = g.wz = 1;
+    g.wseg = 0;
+    g.wp = g.ncol >= 8 ? g.ncol >> 3 : 1;
+    g.dwp = g.dwc = FastDiv::make(g.wp);
+    g.dunit = FastDiv::make(g.wp * L[3]);
+    g.dnyt = g.dtiles = FastDiv::make(8);
     return g;
 }
 
@@ -44,6 +42,83 @@ int launch_order(const Geo &g, const LaunchCfg &cfg, int groups_per_block) {
     const int groups = (g.V + 63) / 64;
     if (g.ncol && g.ncol % 8 == 0 && groups % (8 * groups_per_block) == 0) return 2;
     return 0;
+}
+
+// The tiles of the slab walk for a kernel that reads `bytes` of each site
+// again from its neighbours, to both sides or (fwd_only) one.  What a tile
+// reads beyond itself is its halo in y and z, so a wide tile is better, as
+// long as the t planes between the first and the last read of a site (about
+// three, with the groups in flight) stay in the 4 MB L2: kTilePlane bytes a
+// plane with its halo, beyond which the t neighbours are fetched again.  At
+// 32^3x64 the FP64 smearing step's eight slabs of four z planes (2.4 MB a
+// plane) read 2.97 times their links from beyond L2, 8 x 8 tiles of (y, z)
+// (1.2 MB) a modelled 1.5.  A t range cut in two or more, where tiles alone
+// do not fill eight XCDs, reads its end planes again.  False where the
+// groups do not form (column, t) pairs or every plan leaves more than a
+// sixteenth of the blocks without a group.
+constexpr double kTilePlane = 1.25e6;
+// Added to the cost where the XCDs do not all work on tiles to the end.
+constexpr double kTilesUneven = 0.25;
+
+bool tile_plan(Geo &g, int bytes, bool fwd_only, int groups_per_block) {
+    if (!g.ncol) return false;
+    const int Lt = g.L[3];
+    const int nz = g.P ? g.L[2] : 1, pz = g.ncol / nz;  // Lz layers, or one of whole z planes
+    const double sides = fwd_only ? 1.0 : 2.0;
+    const double yhalo = g.P ? g.L[0] : g.st[2];  // sites a layer and side
+    // Tile sides tried: the whole extent and the numbers below it of at most
+    // two set bits.
+    auto next = [](int n, int all) {
+        do ++n;
+        while (n < all && (n & (n - 1) & ((n & (n - 1)) - 1)));
+        return n;
+    };
+    double best = 1e300;
+    int by = 0, bz = 0, bseg = 0;
+    for (int ty = 1; ty <= pz; ty = next(ty, pz))
+        for (int tz = 1; tz <= nz; tz = next(tz, nz)) {
+            const int nyt = (pz + ty - 1) / ty, nzt = (nz + tz - 1) / tz;
+            const double area = 64.0 * ty * tz;
+            const double all = area + (nyt > 1 ? sides * yhalo * tz : 0.0) + (nzt > 1 ? sides * 64.0 * ty : 0.0);
+            const double over = all * bytes / kTilePlane - 1.0;
+            const double planes = all / area * (over > 0.0 ? 1.0 + 0.9 * (over < 1.0 ? over : 1.0) : 1.0);
+            if (planes >= best) continue;
+            for (int seg = 0; seg <= 4 && Lt % (1 << seg) == 0 && (Lt >> seg) >= (seg ? 4 : 1); ++seg) {
+                const int64_t unit = (int64_t)ty * tz * (Lt >> seg), upx = (((int64_t)nyt * nzt << seg) + 7) / 8;
+                const int64_t blocks = 8 * ((upx * unit + groups_per_block - 1) / groups_per_block);
+                const double waste = (double)(blocks * groups_per_block) / ((double)g.ncol * Lt) - 1.0;
+                const double cost = planes * (seg ? 1.0 + 2.0 * sides / (Lt >> seg) : 1.0) + waste +
+                                    ((nyt * nzt << seg) % 8 ? kTilesUneven : 0.0);
+                if (waste > 1.0 / 16 || cost >= best) continue;
+                best = cost;
+                by = ty;
+                bz = tz;
+                bseg = seg;
+            }
+        }
+    if (!by) return false;
+    const int nyt = (pz + by - 1) / by, nzt = (nz + bz - 1) / bz;
+    g.pz = pz;
+    g.nz = nz;
+    g.wp = by;
+    g.wz = bz;
+    g.wseg = bseg;
+    g.dwp = FastDiv::make(g.wp);
+    g.dwc = FastDiv::make(g.wp * bz);
+    g.dunit = FastDiv::make(g.wp * bz * (Lt >> bseg));
+    g.dnyt = FastDiv::make(nyt);
+    g.dtiles = FastDiv::make(nyt * nzt);
+    return true;
+}
+
+void order_blocks(Geo &g, LaunchCfg &cfg, int groups_per_block, int bytes, bool fwd_only) {
+    const int groups = (g.V + 63) / 64;
+    cfg.grid = (groups + groups_per_block - 1) / groups_per_block;
+    if (cfg.xcd != 2) return;
+    if (tile_plan(g, bytes, fwd_only, groups_per_block))
+        cfg.grid = 8 * (((((int)g.dtiles.d << g.wseg) + 7) / 8 * (int)g.dunit.d + groups_per_block - 1) / groups_per_block);
+    else
+        cfg.xcd = launch_order(g, cfg, groups_per_block);
 }
 
 // ------------------------------------------------------------ pack / unpack
@@ -249,7 +324,7 @@ hipError_t launch_unpack_fermion(const Geo &g, int prec, const void *soa, double
 // norms are added in wave
 // order and reduced by a wave butterfly into one partial per group, so
 // every sum has a fixed order and nothing depends on the launch geometry.
-template <typename R, int NR, int MODE, int NS>
+template <typename R, int NR, int MODE, int NS, bool SLAB>
 __global__ void __launch_bounds__(256) k_shift(Geo g, LinksRO<R, NR> U, FermRO<R> psi, FermRO<R> phi, R a, R c,
                                                 unsigned mask, int bwd, FermWO<R> out, double *__restrict__ partials,
                                                 int xcd, int tw) {
@@ -262,8 +337,9 @@ __global__ void __launch_bounds__(256) k_shift(Geo g, LinksRO<R, NR> U, FermRO<R
 #pragma unroll 1
     for (int j = 0; j < NS; ++j) {
         const int i = tile * NS + j;  // the same for the four waves
-        if (i >= ngroups) return;
-        const int grp = xcd == 2 ? slabwalk(g, i, NS) : traverse(g, i, tw);
+        if (!SLAB && i >= ngroups) return;
+        const int grp = SLAB ? slabwalk(g, i, NS) : traverse(g, i, tw);
+        if (SLAB && grp < 0) continue;
         Site x;
         const bool live = group_site(g, grp, lane, x);
         const int s = x.s;
@@ -371,16 +447,19 @@ static void shift_dispatch_ns(const Geo &g, const void *U, const void *psi, cons
     LinksRO<R, NR> u{(const V *)U, g.S};
     FermRO<R> p{(const V *)psi, g.S}, f{(const V *)phi, g.S};
     FermWO<R> o{(V *)out, g.S};
-    const int groups = (g.V + 63) / 64;
-    const int per_block = cfg.nsite;  // one 64-site group per iteration, four waves
-    const dim3 grid((groups + per_block - 1) / per_block);
-    const int xcd = launch_order(g, cfg, per_block);
+    const int grid = cfg.grid, xcd = cfg.xcd;
+#define QDPX_SHIFT_LAUNCH(NS)                                                                                       \
+    if (xcd == 2)                                                                                                   \
+        k_shift<R, NR, MODE, NS, true><<<grid, 256, 0, st>>>(g, u, p, f, (R)a, (R)c, mask, bwd, o, partials, 2, 1); \
+    else                                                                                                            \
+        k_shift<R, NR, MODE, NS, false><<<grid, 256, 0, st>>>(g, u, p, f, (R)a, (R)c, mask, bwd, o, partials, xcd, cfg.tw)
     switch (cfg.nsite) {
-    case 2: k_shift<R, NR, MODE, 2><<<grid, 256, 0, st>>>(g, u, p, f, (R)a, (R)c, mask, bwd, o, partials, xcd, cfg.tw); break;
-    case 4: k_shift<R, NR, MODE, 4><<<grid, 256, 0, st>>>(g, u, p, f, (R)a, (R)c, mask, bwd, o, partials, xcd, cfg.tw); break;
-    case 8: k_shift<R, NR, MODE, 8><<<grid, 256, 0, st>>>(g, u, p, f, (R)a, (R)c, mask, bwd, o, partials, xcd, cfg.tw); break;
-    default: k_shift<R, NR, MODE, 1><<<grid, 256, 0, st>>>(g, u, p, f, (R)a, (R)c, mask, bwd, o, partials, xcd, cfg.tw); break;
+    case 2: QDPX_SHIFT_LAUNCH(2); break;
+    case 4: QDPX_SHIFT_LAUNCH(4); break;
+    case 8: QDPX_SHIFT_LAUNCH(8); break;
+    default: QDPX_SHIFT_LAUNCH(1); break;
     }
+#undef QDPX_SHIFT_LAUNCH
 }
 
 template <int MODE>
@@ -415,7 +494,9 @@ hipError_t launch_shift(const Geo &g, int prec, int nrows, const void *U, const 
 // order, applies s0, kappa and norm, and stores them.  The order of every
 // sum is fixed,
 // so each site's result does not depend on the launch geometry.
-template <typename R, int NR, int NS, bool DIV>
+// SLAB: the slab walk, compiled apart: its decoding in the same kernel took
+// 1.5 % off the other orders on small lattices (20^3x40 in x, y, z: 52 us).
+template <typename R, int NR, int NS, bool DIV, bool SLAB>
 __global__ void __launch_bounds__(256) k_hop(Geo g, LinksRO<R, NR> U, FermRO<R> psi, FermRO<R> s0, R kappa, R norm,
                                               unsigned mask, FermWO<R> out, int xcd, int tw) {
     __shared__ vec2_t<R> part[4][12][64];  // [direction][component][lane]
@@ -426,8 +507,9 @@ __global__ void __launch_bounds__(256) k_hop(Geo g, LinksRO<R, NR> U, FermRO<R> 
 #pragma unroll 1
     for (int j = 0; j < NS; ++j) {
         const int i = tile * NS + j;  // the same for the four waves
-        if (i >= ngroups) return;
-        const int grp = xcd == 2 ? slabwalk(g, i, NS) : traverse(g, i, tw);
+        if (!SLAB && i >= ngroups) return;
+        const int grp = SLAB ? slabwalk(g, i, NS) : traverse(g, i, tw);
+        if (SLAB && grp < 0) continue;
         Site x;
         const bool live = group_site(g, grp, lane, x);
         const int s = x.s;
@@ -518,16 +600,19 @@ static void hop_dispatch_ns(const Geo &g, const void *U, const void *psi, const 
     LinksRO<R, NR> u{(const V *)U, g.S};
     FermRO<R> p{(const V *)psi, g.S}, z{(const V *)s0, g.S};
     FermWO<R> o{(V *)out, g.S};
-    const int groups = (g.V + 63) / 64;
-    const int per_block = cfg.nsite;  // one 64-site group per iteration, four waves
-    const dim3 grid((groups + per_block - 1) / per_block);
-    const int xcd = launch_order(g, cfg, per_block);
+    const int grid = cfg.grid, xcd = cfg.xcd;
+#define QDPX_HOP_LAUNCH(NS)                                                                                  \
+    if (xcd == 2)                                                                                            \
+        k_hop<R, NR, NS, DIV, true><<<grid, 256, 0, st>>>(g, u, p, z, (R)kappa, (R)norm, mask, o, 2, 1);     \
+    else                                                                                                     \
+        k_hop<R, NR, NS, DIV, false><<<grid, 256, 0, st>>>(g, u, p, z, (R)kappa, (R)norm, mask, o, xcd, cfg.tw)
     switch (cfg.nsite) {
-    case 2: k_hop<R, NR, 2, DIV><<<grid, 256, 0, st>>>(g, u, p, z, (R)kappa, (R)norm, mask, o, xcd, cfg.tw); break;
-    case 4: k_hop<R, NR, 4, DIV><<<grid, 256, 0, st>>>(g, u, p, z, (R)kappa, (R)norm, mask, o, xcd, cfg.tw); break;
-    case 8: k_hop<R, NR, 8, DIV><<<grid, 256, 0, st>>>(g, u, p, z, (R)kappa, (R)norm, mask, o, xcd, cfg.tw); break;
-    default: k_hop<R, NR, 1, DIV><<<grid, 256, 0, st>>>(g, u, p, z, (R)kappa, (R)norm, mask, o, xcd, cfg.tw); break;
+    case 2: QDPX_HOP_LAUNCH(2); break;
+    case 4: QDPX_HOP_LAUNCH(4); break;
+    case 8: QDPX_HOP_LAUNCH(8); break;
+    default: QDPX_HOP_LAUNCH(1); break;
     }
+#undef QDPX_HOP_LAUNCH
 }
 
 template <bool DIV>

@@ -17,9 +17,10 @@ struct LaunchCfg {
     int block = 256;  // threads per block, multiple of 64
     int nsite = 1;    // consecutive 64-site groups handled per wave
     int xcd = 1;      // 0: identity, 1: XCD-contiguous tile ranges, 2: XCD slab walk
-    int tw = 1;       // t planes walked together (brick mapping only; must divide Lt)
+    int tw = 1;       // t planes walked together (where the groups form columns; must divide Lt)
     int lds = 0;      // LDS tile of the FP32 APE step: 0 none, 1 own links, 2 also backward links,
                       // 3 also the plane products, 4 own links and plane products
+    int grid = 0;     // blocks of the launch (order_blocks)
 };
 
 // Threads per block of the fixed-shape reduction kernels (plaquette,
@@ -42,6 +43,11 @@ int tune_table_write(const char *path, const char *arch, const std::vector<TuneE
 
 Geo make_geo(const int32_t L[4]);
 int launch_order(const Geo &g, const LaunchCfg &cfg, int groups_per_block);
+bool tile_plan(Geo &g, int bytes, bool fwd_only, int groups_per_block);
+// Settles the order of a launch of groups_per_block 64-site groups a block:
+// the tiles of the slab walk in g, and in cfg the order and the grid.  Every
+// launch of a kernel that takes a LaunchCfg takes both from here.
+void order_blocks(Geo &g, LaunchCfg &cfg, int groups_per_block, int bytes, bool fwd_only);
 
 // ---- fields.hip
 hipError_t launch_pack_links(const Geo &g, int prec, int nrows, const double *aos, void *soa, hipStream_t st);
@@ -88,7 +94,7 @@ constexpr int kXcds = 8;
 
 // One lattice of a batch (device table entry).  Its 64-site groups form a
 // (column, t-row) grid, group = col + ncol * row, where a column is one
-// brick (or run of groups) of one z plane and rows step in t.  The columns
+// run of 64 sites of a t plane and rows step in t.  The columns
 // are split into 8 contiguous ranges [xcol0[x], xcol1[x]), one per XCD
 // queue; queue x walks its range t-row by t-row (group j of the queue is
 // row j / cols, column xcol0 + j % cols), in tickets of group_chunk groups.

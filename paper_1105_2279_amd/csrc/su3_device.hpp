@@ -35,29 +35,33 @@ struct FastDiv {
 };
 
 // ---------------------------------------------------------------- geometry
-// Extents, per-direction site strides, the padded SoA stride and the
-// mapping of 64-site groups (one group per wave) to sites.
+// Extents, per-direction site strides, the padded SoA stride and the order
+// of 64-site groups (one group per wave).
 //
-// Brick mapping (bwl = 4 or 3): when Lx is a multiple of bw = 2^bwl and Ly a
-// multiple of 64/bw, group g is a bw x (64/bw) brick of one (z, t) plane:
-// g = p + P*(z + Lz*t) with p the brick within the xy plane (P bricks per
-// plane, pbx along x); lane l sits at x = xb*bw + l % bw, y = yb*(64/bw) + l / bw.
-// A wave then touches 64/bw rows of bw consecutive sites (whole cache lines),
-// and the groups of one xy plane are numbered consecutively, so a window of
-// t planes can be walked together (see traverse()).  Otherwise (bwl = 0)
-// group g is the 64 consecutive sites [64 g, 64 g + 64).  The mapping depends
-// only on the extents, so per-group partial sums never depend on the launch.
+// Group g is the 64 consecutive sites [64 g, 64 g + 64), so that a wave reads
+// or writes a component in one stretch of whole cache lines, 1 KB for 16-byte
+// entries.  (Bricks of 16 x 4 or 8 x 8 sites of an xy plane, whose rows are
+// 256 or 128 bytes, were slower wherever a row of the lattice is longer than
+// theirs: the FP64 chain step of 32^3x64 440 against 402 us, the FP32-12 Jacobi
+// hop there 230 against 217 us, the FP64 smearing step of 24^3x48 296 against
+// 282 us.)  Where the groups of a t plane, or of an xy plane, are a whole
+// number they are numbered as columns: group = column + ncol t, column =
+// p + P z.  The mapping depends only on the extents, so per-group partial
+// sums never depend on the launch.
 struct Geo {
     int L[4];
     int st[4];  // 1, Lx, Lx*Ly, Lx*Ly*Lz
     int V;
-    int bwl;    // log2 of the brick width, 0 for the linear mapping
-    int P;      // bricks per xy plane
-    int pbx;    // bricks along x
+    int P;      // groups per xy plane when every group lies in one xy plane, else 0
     int ncol;   // groups per t plane when every group lies in one t plane, else 0
     int64_t S;  // padded site count: V rounded up to 256
-    // divisors of the site decoding: Lx, Ly, Lz, P, pbx, P*Lz, ncol/8
-    FastDiv dL0, dL1, dL2, dP, dpbx, dplane, dslab;
+    // divisors of the site decoding: Lx, Ly, Lz, P, ncol
+    FastDiv dL0, dL1, dL2, dP, dncol;
+    // The XCD slab walk (slabwalk): the ncol columns as nz layers of pz, cut
+    // into tiles of wp columns by wz layers, nyt tiles a layer; a unit is one
+    // tile in one of 2^wseg equal t ranges.
+    int pz, nz, wp, wz, wseg;
+    FastDiv dunit, dwc, dwp, dnyt, dtiles;  // by a unit's groups, wp * wz, wp, nyt, all tiles
 };
 
 // Neighbour addressing for one site: coordinates are decoded once, every hop
@@ -81,16 +85,14 @@ __device__ __forceinline__ int num_groups(const Geo &g) { return (g.V + 63) >> 6
 // run on the scalar unit).  Returns false for the padding lanes of the last
 // linear group.
 __device__ __forceinline__ bool group_site(const Geo &g, int grp, int lane, Site &x) {
-    if (g.bwl) {
-        const int r = g.dP.div(grp), p = grp - r * g.P;
-        const int t = g.dL2.div(r), z = r - t * g.L[2];
-        const int yb = g.dpbx.div(p), xb = p - yb * g.pbx;
-        const int bw = 1 << g.bwl;
-        x.c[0] = xb * bw + (lane & (bw - 1));
-        x.c[1] = yb * (64 >> g.bwl) + (lane >> g.bwl);
-        x.c[2] = z;
+    if (g.P) {  // z and t of the whole group, one division per lane
+        const int r = g.dP.div(grp), p = grp - r * g.P, t = g.dL2.div(r);
+        const int q = p * 64 + lane;
+        x.c[1] = g.dL0.div(q);
+        x.c[0] = q - x.c[1] * g.L[0];
+        x.c[2] = r - t * g.L[2];
         x.c[3] = t;
-        x.s = x.c[0] + g.L[0] * (x.c[1] + g.L[1] * (z + g.L[2] * t));
+        x.s = grp * 64 + lane;
         return true;
     }
     const int s = grp * 64 + lane;
@@ -99,37 +101,42 @@ __device__ __forceinline__ bool group_site(const Geo &g, int grp, int lane, Site
     return true;
 }
 
-// Launch order -> group.  With the brick mapping and a window of tw t planes
-// (tw divides Lt), consecutive logical indices walk the tw planes of one
-// (brick, z) column before moving on, so the blocks in flight on one XCD hold
-// each other's t neighbours in L2.  tw = 1 (or the linear mapping) is the
-// identity.  A bijection on [0, num_groups).
+// Launch order -> group.  Where the groups form columns and with a window of
+// tw t planes (tw divides Lt), consecutive logical indices walk the tw planes
+// of one column before moving on, so the blocks in flight on one XCD hold
+// each other's t neighbours in L2.  tw = 1 (or no columns) is the identity.
+// A bijection on [0, num_groups).
 // tw is a power of two (checked on the host).
 __device__ __forceinline__ int traverse(const Geo &g, int i, int tw) {
-    if (!g.bwl || tw <= 1) return i;
+    if (!g.ncol || tw <= 1) return i;
     const int tin = i & (tw - 1), rest = i >> __builtin_ctz(tw);
-    const int plane = g.P * g.L[2];
-    const int tc = g.dplane.div(rest), pz = rest - tc * plane;
-    return pz + plane * (tc * tw + tin);
+    const int tc = g.dncol.div(rest), c = rest - tc * g.ncol;
+    return c + g.ncol * (tc * tw + tin);
 }
 
 // Launch order -> group, XCD slab walk.  Blocks are dispatched to the 8
-// XCDs round-robin (block b runs on XCD b % 8).  The ncol groups of a t plane
-// (column index c = brick + P z) are split into 8 contiguous ranges of
-// ncol / 8 columns, a slab of z planes, and XCD x takes range x in every t
-// plane, walking its slab t plane by t plane.  A group's x, y and z
-// neighbours then lie in the same slab a few groups away, and its t
-// neighbours ncol / 8 groups away, all handled on the same XCD close together
-// in time, so they are served from that XCD's L2.  Requires ncol % 8 == 0 and
-// num_groups % (8 m) == 0 for m groups per block (checked on the host).
-// A bijection.
+// XCDs round-robin (block b runs on XCD b % 8).  The columns of the lattice
+// (ncol groups a t plane) are cut into tiles,
+// each a stretch of some z planes; XCD x takes every unit (a tile, or
+// a range of t planes of one) of its eighth of them, one after another, and
+// walks a unit t plane by t plane.  A group's x, y and z neighbours then lie
+// in the same tile a few groups away and its t neighbours one tile further,
+// all on the same XCD close together in time, so they are served from that
+// XCD's L2 where three or four t planes of the tile fit it (tile_plan on
+// the host chooses the tile).  Returns -1 where the last tile of a row, the
+// last unit of an XCD or its last block is not full; apart from those a
+// bijection.
 // m is a power of two (groups per block times groups per wave).
 __device__ __forceinline__ int slabwalk(const Geo &g, int i, int m) {
     const int blk = i >> __builtin_ctz(m), within = i & (m - 1);
     const int x = blk & 7, jj = (blk >> 3) * m + within;
-    const int cx = g.ncol >> 3;
-    const int t = g.dslab.div(jj), k = jj - t * cx;
-    return (x * cx + k) + g.ncol * t;
+    const int u = g.dunit.div(jj), r = jj - u * (int)g.dunit.d;
+    const int tl = g.dwc.div(r), k = r - tl * (int)g.dwc.d;
+    const int q = 8 * u + x, seg = g.dtiles.div(q), tile = q - seg * (int)g.dtiles.d;
+    const int zt = g.dnyt.div(tile), yt = tile - zt * (int)g.dnyt.d;
+    const int kz = g.dwp.div(k), cp = k - kz * g.wp + g.wp * yt, z = zt * g.wz + kz;
+    if (seg >> g.wseg || cp >= g.pz || z >= g.nz) return -1;
+    return cp + g.pz * z + g.ncol * (seg * (g.L[3] >> g.wseg) + tl);
 }
 
 // x.c[mu] for a wave-uniform but run-time mu, by selects: indexing the
