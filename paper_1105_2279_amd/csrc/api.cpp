@@ -360,12 +360,6 @@ static int reread_bytes(qdpx_op op, qdpx_prec prec, qdpx_linkfmt fmt) {
 static bool fwd_only(qdpx_op op) { return op == QDPX_OP_SHIFT || op == QDPX_OP_CHAIN; }
 static int groups_per_block(qdpx_op op, const LaunchCfg &c) { return op == QDPX_OP_APE ? c.block / 256 * c.nsite : c.nsite; }
 
-// Default block order: where what an XCD's eighth of the lattice reads again
-// fits its L2, contiguous ranges of groups (every neighbour is read from
-// beyond the L2 once, and a lattice of few groups has no tiles); above, the
-// slab walk.
-constexpr int64_t kXcdL2 = 4 << 20;
-
 static LaunchCfg cfg_for(qdpx_ctx *ctx, qdpx_op op, const qdpx_geom *geom, qdpx_prec prec, qdpx_linkfmt fmt) {
     LaunchCfg c;
     if (op == QDPX_OP_BATCHED) c.nsite = 1;  // groups per ticket

@@ -10,11 +10,12 @@
 //   (sum MASK E)        sum over the directions in MASK (hex) of E, the
 //                       direction variable m standing for each in turn
 //
-// The generator writes one HIP kernel per expression (one site per lane,
-// blocks of 256 sites, in FP32 taken so that each XCD walks one contiguous
-// range; each node becomes straight-line code on a 12-component spinor, a shift
-// moves the site index and coordinates, a sum becomes a loop over its
-// directions that is not unrolled), compiles it with
+// The generator writes one HIP kernel per expression (one site per lane, the
+// 64-site groups taken in the block order of the hand-written kernels; each
+// node becomes straight-line code on a 12-component spinor, a shift moves the
+// site index and coordinates; the directions of an expression's sum go to the
+// four waves of a group where that can be, else a sum becomes a loop over
+// them), compiles it with
 // hipRTC for the device's architecture with packed FP32 disabled, and keeps
 // the code object in an on-disk cache keyed by a hash of the source and
 // options, so a later process loads it without compiling (the paper's
@@ -176,6 +177,70 @@ struct Gen {
 
     std::string fresh(const char *p) { return std::string(p) + std::to_string(next_id++); }
 
+    // Moves site `s`, coordinates c, by the shift n: the new site's variable;
+    // cc its coordinates.
+    std::string move(const Node &n, const std::string &s, const std::string c[4], std::string cc[4]) {
+        const bool var = (n.dir < 0);
+        const std::string D = var ? std::string("m") : std::to_string(n.dir);
+        const std::string t = fresh("s"), moved = fresh("c");
+        const std::string L = var ? "lsel(m, L0, L1, L2, L3)" : "L" + D;
+        const std::string st = var ? "lsel(m, st0, st1, st2, st3)" : "st" + D;
+        const std::string cur = var ? "lsel(m, " + c[0] + ", " + c[1] + ", " + c[2] + ", " + c[3] + ")" : c[n.dir];
+        body << "    int " << t << " = " << s << ", " << moved << " = " << cur << ";\n";
+        if (n.sign > 0)
+            body << "    if (" << moved << " == " << L << " - 1) { " << moved << " = 0; " << t << " -= (" << L
+                 << " - 1) * " << st << "; } else { ++" << moved << "; " << t << " += " << st << "; }\n";
+        else
+            body << "    if (" << moved << " == 0) { " << moved << " = " << L << " - 1; " << t << " += (" << L
+                 << " - 1) * " << st << "; } else { --" << moved << "; " << t << " -= " << st << "; }\n";
+        for (int d = 0; d < 4; ++d) {
+            if (!var) {
+                cc[d] = (d == n.dir) ? moved : c[d];
+            } else {
+                cc[d] = fresh("c");
+                body << "    const int " << cc[d] << " = (m == " << d << ") ? " << moved << " : " << c[d] << ";\n";
+            }
+        }
+        return t;
+    }
+
+    // The part of a split expression outside its sum, in each wave for the
+    // components it owns: first the loads of its (shifted) fields, then, once
+    // the partial sums have met in LDS, the arithmetic.
+    std::map<const Node *, std::string> owned;
+    void emit_loads(const Node &n, const std::string &s, const std::string c[4]) {
+        if (n.kind == Node::Sum) return;
+        if (n.kind == Node::Field || n.kind == Node::Shift) {
+            const Node *p = &n;
+            std::string t = s, cc[4] = {c[0], c[1], c[2], c[3]};
+            while (p->kind == Node::Shift) {
+                std::string moved[4];
+                t = move(*p, t, cc, moved);
+                for (int d = 0; d < 4; ++d) cc[d] = moved[d];
+                p = p->kids[0].get();
+            }
+            owned[&n] = fresh("v");
+            body << "    own " << owned[&n] << "; ldown(f" << p->idx << ", S, " << t << ", w, " << owned[&n] << ");\n";
+            return;
+        }
+        for (const auto &k : n.kids) emit_loads(*k, s, c);
+    }
+    std::string emit_owned(const Node &n) {
+        if (owned.count(&n)) return owned[&n];
+        const std::string v = fresh("v");
+        if (n.kind == Node::Sum) {
+            body << "    own " << v << "; gather(part, " << n.mask << "u, w, lane, " << v << ");\n";
+        } else if (n.kind == Node::Scale) {
+            const std::string a = emit_owned(*n.kids[0]);
+            body << "    own " << v << "; oscale(scal" << n.idx << ", " << a << ", " << v << ");\n";
+        } else {
+            const std::string a = emit_owned(*n.kids[0]), b = emit_owned(*n.kids[1]);
+            body << "    own " << v << "; " << (n.kind == Node::Add ? "oadd(" : "osub(") << a << ", " << b << ", " << v
+                 << ");\n";
+        }
+        return v;
+    }
+
     // Emits code for n evaluated at site `s` with coordinates c[0..3].  A
     // direction of -1 is the sum's loop variable m (a run-time value: sums
     // become loops that are not unrolled, so one direction's operands are
@@ -190,26 +255,8 @@ struct Gen {
             return v;
         }
         case Node::Shift: {
-            const std::string t = fresh("s"), moved = fresh("c");
-            const std::string L = var ? "lsel(m, L0, L1, L2, L3)" : "L" + D;
-            const std::string st = var ? "lsel(m, st0, st1, st2, st3)" : "st" + D;
-            const std::string cur = var ? "lsel(m, " + c[0] + ", " + c[1] + ", " + c[2] + ", " + c[3] + ")" : c[n.dir];
-            body << "    int " << t << " = " << s << ", " << moved << " = " << cur << ";\n";
-            if (n.sign > 0)
-                body << "    if (" << moved << " == " << L << " - 1) { " << moved << " = 0; " << t << " -= (" << L
-                     << " - 1) * " << st << "; } else { ++" << moved << "; " << t << " += " << st << "; }\n";
-            else
-                body << "    if (" << moved << " == 0) { " << moved << " = " << L << " - 1; " << t << " += (" << L
-                     << " - 1) * " << st << "; } else { --" << moved << "; " << t << " -= " << st << "; }\n";
             std::string cc[4];
-            for (int d = 0; d < 4; ++d) {
-                if (!var) {
-                    cc[d] = (d == n.dir) ? moved : c[d];
-                } else {
-                    cc[d] = fresh("c");
-                    body << "    const int " << cc[d] << " = (m == " << d << ") ? " << moved << " : " << c[d] << ";\n";
-                }
-            }
+            const std::string t = move(n, s, c, cc);
             return emit(*n.kids[0], t, cc);
         }
         case Node::Umul:
@@ -258,6 +305,36 @@ typedef real real2 __attribute__((ext_vector_type(2)));
 struct cx { real re, im; };
 struct spinor { cx c[4][3]; };
 struct link { cx e[3][3]; };
+// The launch's block order and site decoding (JitGeo on the host); a division
+// by d is (mulhi(m, n) + n) >> l for 0 <= n < 2^31.
+struct divisor { unsigned d, m, l; };
+struct jitgeo {
+    long long S;
+    int ngroups, order, ncol, pz, nz, wp, wz, wseg, tlen;
+    divisor L0, L1, L2, unit, wc, wpd, nyt, tiles;
+};
+__device__ __forceinline__ int quot(const divisor &f, int n) {
+    return (int)(((unsigned)(((unsigned long long)f.m * (unsigned)n) >> 32) + (unsigned)n) >> f.l);
+}
+// 64-site group number i of the launch, groups per block; -1: none.  Blocks
+// reach the 8 XCDs round-robin.  Order 1: each XCD one contiguous range of
+// blocks; order 2: each XCD tiles of the lattice's cross section, t plane by
+// t plane.
+__device__ __forceinline__ int group_of(const jitgeo &g, int blk, int nblk, int within, int groups) {
+    const int x = blk & 7;
+    if (g.order == 2) {
+        const int jj = (blk >> 3) * groups + within, u = quot(g.unit, jj), r = jj - u * (int)g.unit.d;
+        const int tl = quot(g.wc, r), k = r - tl * (int)g.wc.d;
+        const int q = 8 * u + x, seg = quot(g.tiles, q), tile = q - seg * (int)g.tiles.d;
+        const int zt = quot(g.nyt, tile), yt = tile - zt * (int)g.nyt.d;
+        const int kz = quot(g.wpd, k), cp = k - kz * g.wp + g.wp * yt, z = zt * g.wz + kz;
+        if (seg >> g.wseg || cp >= g.pz || z >= g.nz) return -1;
+        return cp + g.pz * z + g.ncol * (seg * g.tlen + tl);
+    }
+    const int xq = nblk >> 3, xr = nblk & 7;
+    const int i = (x * xq + min(x, xr) + (blk >> 3)) * groups + within;
+    return i < g.ngroups ? i : -1;
+}
 // the value for direction m of four per-direction values (m run-time, wave-uniform)
 __device__ __forceinline__ int lsel(int m, int a, int b, int c, int d) { return m == 0 ? a : m == 1 ? b : m == 2 ? c : d; }
 typedef real real4 __attribute__((ext_vector_type(4)));
@@ -389,67 +466,195 @@ __device__ __forceinline__ void sscale(real k, const spinor &a, spinor &r) {
 #pragma unroll
         for (int i = 0; i < 3; ++i) r.c[sp][i] = cx{k * a.c[sp][i].re, k * a.c[sp][i].im};
 }
+#if SPLIT
+// The components a wave of a split kernel finishes and stores: double, spin
+// w; float, the whole pairs k = w and, for w < 2, k = w + 4 (slot t is
+// component 2k + (t & 1) of pair k = w + 4 (t >> 1)).
+#if PAIRED
+#define NOWN 4
+#else
+#define NOWN 3
+#endif
+struct own { cx c[NOWN]; };
+__device__ __forceinline__ int component(int w, int t) {
+#if PAIRED
+    const int k = w + 4 * (t >> 1);
+    return k < 6 ? 2 * k + (t & 1) : -1;
+#else
+    return 3 * w + t;
+#endif
+}
+__device__ __forceinline__ void ldown(const real2 *__restrict__ f, long long S, int s, int w, own &r) {
+#if PAIRED
+    const real4 *P = (const real4 *)f;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int k = w + 4 * h;
+        real4 v = {0, 0, 0, 0};
+        if (k < 6) v = P[(long long)k * S + s];
+        r.c[2 * h] = cx{v.x, v.y};
+        r.c[2 * h + 1] = cx{v.z, v.w};
+    }
+#else
+#pragma unroll
+    for (int t = 0; t < 3; ++t) r.c[t] = ldc(f, S, 3 * w + t, s);
+#endif
+}
+__device__ __forceinline__ void stown(real2 *__restrict__ f, long long S, int s, int w, const own &r) {
+#if PAIRED
+    real4 *P = (real4 *)f;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int k = w + 4 * h;
+        const cx a = r.c[2 * h], b = r.c[2 * h + 1];
+        const real4 v = {a.re, a.im, b.re, b.im};
+        if (k < 6) __builtin_nontemporal_store(v, P + ((long long)k * S + s));
+    }
+#else
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+        const real2 v = {r.c[t].re, r.c[t].im};
+        __builtin_nontemporal_store(v, f + ((long long)(3 * w + t) * S + s));
+    }
+#endif
+}
+// the directions' partial sums, in order
+__device__ __forceinline__ void gather(const real2 (&part)[4][12][64], unsigned mask, int w, int lane, own &r) {
+#pragma unroll
+    for (int t = 0; t < NOWN; ++t) {
+        cx z{(real)0, (real)0};
+        const int q = component(w, t);
+        if (q >= 0)
+#pragma unroll
+            for (int d = 0; d < 4; ++d)
+                if ((mask >> d) & 1u) {
+                    const real2 e = part[d][q][lane];
+                    z.re += e.x;
+                    z.im += e.y;
+                }
+        r.c[t] = z;
+    }
+}
+__device__ __forceinline__ void oadd(const own &a, const own &b, own &r) {
+#pragma unroll
+    for (int t = 0; t < NOWN; ++t) r.c[t] = cx{a.c[t].re + b.c[t].re, a.c[t].im + b.c[t].im};
+}
+__device__ __forceinline__ void osub(const own &a, const own &b, own &r) {
+#pragma unroll
+    for (int t = 0; t < NOWN; ++t) r.c[t] = cx{a.c[t].re - b.c[t].re, a.c[t].im - b.c[t].im};
+}
+__device__ __forceinline__ void oscale(real k, const own &a, own &r) {
+#pragma unroll
+    for (int t = 0; t < NOWN; ++t) r.c[t] = cx{k * a.c[t].re, k * a.c[t].im};
+}
+#endif
 )HIP";
 
+// The sum whose directions go to the four waves of a 64-site group: the
+// expression's only one, of two directions or more, with nothing but sums,
+// differences, scalings and (shifted) fields around it (all componentwise, so
+// that each wave can finish its share of the components).  Null: none.
+const Node *split_sum(const Node &n) {
+    switch (n.kind) {
+    case Node::Sum: return (n.mask & (n.mask - 1)) ? &n : nullptr;
+    case Node::Scale: return split_sum(*n.kids[0]);
+    case Node::Add:
+    case Node::Sub: {
+        auto plain = [](const Node *p) {  // no sum and no link inside
+            std::vector<const Node *> todo{p};
+            while (!todo.empty()) {
+                const Node *q = todo.back();
+                todo.pop_back();
+                if (q->kind == Node::Sum || q->kind == Node::Umul || q->kind == Node::Uadj) return false;
+                if (q->kind == Node::Shift && q->kids[0]->kind != Node::Shift && q->kids[0]->kind != Node::Field)
+                    return false;
+                for (const auto &k : q->kids) todo.push_back(k.get());
+            }
+            return true;
+        };
+        if (plain(n.kids[1].get())) return split_sum(*n.kids[0]);
+        if (plain(n.kids[0].get())) return split_sum(*n.kids[1]);
+        return nullptr;
+    }
+    default: return nullptr;
+    }
+}
+
+// 64-site groups a block of 256 threads takes.
+int groups_per_block(const Node &root) { return split_sum(root) ? 1 : 4; }
+
+// A kernel with a split sum has the hand-written hop's shape: wave w computes
+// direction w, so that four directions' loads are in flight at once and not
+// one or two after another, the partial sums meet in LDS, and each wave
+// finishes the components it owns.  The smearing update with its norm, one
+// site per lane and the directions in a loop of two at a time, against split:
+// 205 / 158 us at 24^3x48 in FP64, 520 / 466 us at 32^3x64, 277 / 241 us there
+// in FP32-12, 58 / 43 us at 14x18x22x30 in FP64.
 std::string generate(const Node &root, int prec, int nrows, int n_fields, int n_scalars) {
     std::ostringstream src;
-    std::string pre = kPrelude;
+    const Node *sum = split_sum(root);
     const std::string real = prec == QDPX_F64 ? "double" : "float";
     src << "#define REAL " << real << "\n#define NROWS " << nrows << "\n#define PAIRED " << (prec == QDPX_F32 ? 1 : 0)
-        << "\n" << pre;
+        << "\n#define SPLIT " << (sum ? 1 : 0) << "\n" << kPrelude;
     src << "extern \"C\" __global__ void __launch_bounds__(256) qdpx_jit_kernel(int L0, int L1, int L2, int L3, "
-           "long long S, const real2 *__restrict__ U";
+           "jitgeo geo, const real2 *__restrict__ U";
     for (int i = 0; i < n_fields; ++i) src << ", const real2 *__restrict__ f" << i;
     src << ", real2 *__restrict__ out";
     // scalar K is the parameter scalK: generated locals are named by fresh()
     // as one of v, u, s, c followed by a number, so sK would clash with a site
     for (int i = 0; i < n_scalars; ++i) src << ", real scal" << i;
     src << ", double *__restrict__ partials) {\n";
-    src << "    const int V = L0 * L1 * L2 * L3;\n"
-           "    const int st0 = 1, st1 = L0, st2 = L0 * L1, st3 = L0 * L1 * L2;\n"
-           "    (void)st0;\n";
-    if (prec == QDPX_F32) {
-        // Blocks reach the 8 XCDs round-robin: block b takes tile
-        // (b mod 8) q + min(b mod 8, r) + b div 8 (nb = 8q + r blocks), a
-        // bijection that gives each XCD one contiguous range of sites, so the
-        // z and t neighbours a block reads were mostly fetched into its own
-        // XCD's L2 by the blocks before it (the FP32 hop 3 % faster at
-        // 32^3x64; the FP64 one, with twice the bytes per site, 12 % slower,
-        // so FP64 kernels keep the plain order).
-        src << "    const int nblk = (int)gridDim.x, blk = (int)blockIdx.x;\n"
-               "    const int xcq = nblk >> 3, xcr = nblk & 7, xcb = blk & 7;\n"
-               "    const int site = (xcb * xcq + min(xcb, xcr) + (blk >> 3)) * 256 + (int)threadIdx.x;\n";
-    } else {
-        src << "    const int site = blockIdx.x * 256 + threadIdx.x;\n";
-    }
-    src << "    double n2 = 0.0;\n"
-           "    if (site < V) {\n"
-           "    int r = site;\n"
-           "    int x0 = r % L0; r /= L0;\n"
-           "    int x1 = r % L1; r /= L1;\n"
-           "    int x2 = r % L2;\n"
-           "    int x3 = r / L2;\n";
+    src << "    const int st0 = 1, st1 = L0, st2 = L0 * L1, st3 = L0 * L1 * L2;\n"
+           "    (void)st0; (void)st1; (void)st2; (void)st3; (void)L3;\n"
+           "    const long long S = geo.S;\n"
+           "    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));\n";
+    src << (sum ? "    __shared__ real2 part[4][12][64];\n    __shared__ double nrm[4][64];\n"
+                  "    const int grp = group_of(geo, (int)blockIdx.x, (int)gridDim.x, 0, 1);\n"
+                : "    const int grp = group_of(geo, (int)blockIdx.x, (int)gridDim.x, w, 4);\n");
+    src << "    if (grp < 0) return;\n"
+           "    const int last = L0 * L1 * L2 * L3 - 1;\n"
+           "    const int at = grp * 64 + lane, site = min(at, last);\n"  // padding lanes load from the last site
+           "    const int q0 = quot(geo.L0, site), q1 = quot(geo.L1, q0), x3 = quot(geo.L2, q1);\n"
+           "    const int x0 = site - q0 * L0, x1 = q0 - q1 * L1, x2 = q1 - x3 * L2;\n"
+           "    double n2 = 0.0;\n";
     Gen g;
     const std::string c[4] = {"x0", "x1", "x2", "x3"};
-    const std::string res = g.emit(root, "site", c);
-    src << g.body.str();
-    src << "    stspinor(out, S, site, " << res << ");\n"
-        << "#pragma unroll\n    for (int sp = 0; sp < 4; ++sp)\n#pragma unroll\n"
-           "        for (int a = 0; a < 3; ++a) {\n"
-           "            const cx z = "
-        << res
-        << ".c[sp][a];\n"
-           "            n2 = fma((double)z.re, (double)z.re, fma((double)z.im, (double)z.im, n2));\n"
-           "        }\n"
-           "    }\n"
-           // a wave whose first site is past the end has no partial (there
-           // are ceil(V / 64))
-           "    if (partials) {  // |out|^2 of each 64-site group, fixed butterfly\n"
-           "#pragma unroll\n"
+    if (sum) {
+        g.emit_loads(root, "site", c);
+        g.body << "    spinor acc; szero(acc);\n    if ((" << sum->mask << "u >> w) & 1u) {\n    const int m = w;\n";
+        const std::string a = g.emit(*sum->kids[0], "site", c);
+        g.body << "    acc = " << a
+               << ";\n    }\n"
+                  "#pragma unroll\n    for (int q = 0; q < 12; ++q) "
+                  "part[w][q][lane] = real2{acc.c[q / 3][q % 3].re, acc.c[q / 3][q % 3].im};\n"
+                  "    __syncthreads();\n";
+        const std::string res = g.emit_owned(root);
+        src << g.body.str() << "    if (at <= last) {\n    stown(out, S, site, w, " << res
+            << ");\n#pragma unroll\n    for (int t = 0; t < NOWN; ++t) {\n        if (component(w, t) < 0) continue;\n"
+               "        const cx z = "
+            << res
+            << ".c[t];\n"
+               "        n2 = fma((double)z.re, (double)z.re, fma((double)z.im, (double)z.im, n2));\n    }\n    }\n"
+               "    if (partials) {  // |out|^2 of the group: the waves' shares in order, a fixed butterfly\n"
+               "        nrm[w][lane] = n2;\n"
+               "        __syncthreads();\n"
+               "        n2 = ((nrm[0][lane] + nrm[1][lane]) + nrm[2][lane]) + nrm[3][lane];\n";
+    } else {
+        const std::string res = g.emit(root, "site", c);
+        src << g.body.str() << "    if (at <= last) {\n    stspinor(out, S, site, " << res
+            << ");\n#pragma unroll\n    for (int sp = 0; sp < 4; ++sp)\n#pragma unroll\n"
+               "        for (int a = 0; a < 3; ++a) {\n"
+               "            const cx z = "
+            << res
+            << ".c[sp][a];\n"
+               "            n2 = fma((double)z.re, (double)z.re, fma((double)z.im, (double)z.im, n2));\n"
+               "        }\n    }\n"
+               "    if (partials) {  // |out|^2 of each group, a fixed butterfly\n";
+    }
+    src << "#pragma unroll\n"
            "        for (int off = 32; off >= 1; off >>= 1) n2 += __shfl_xor(n2, off, 64);\n"
-           "        if ((threadIdx.x & 63) == 0 && site < V) partials[site >> 6] = n2;\n"
-           "    }\n"
-           "}\n";
+        << (sum ? "        if (threadIdx.x == 0) partials[grp] = n2;\n" : "        if (lane == 0) partials[grp] = n2;\n")
+        << "    }\n}\n";
     return src.str();
 }
 
@@ -549,11 +754,23 @@ void write_entry_atomic(const std::string &p, const std::string &key, const std:
     else std::remove(tmp.c_str());
 }
 
+// The kernels' `jitgeo` argument.
+struct JitGeo {
+    long long S;
+    int ngroups, order, ncol, pz, nz, wp, wz, wseg, tlen;
+    FastDiv L0, L1, L2, unit, wc, wpd, nyt, tiles;
+};
+JitGeo jit_geo(const Geo &g, int order) {
+    return JitGeo{(long long)g.S, (g.V + 63) / 64, order, g.ncol,  g.pz,  g.nz,  g.wp,   g.wz,    g.wseg,
+                  g.L[3] >> g.wseg, g.dL0, g.dL1,  g.dL2, g.dunit, g.dwc, g.dwp, g.dnyt, g.dtiles};
+}
+
 struct JitKernel {
     std::string source;
     hipModule_t module = nullptr;
     hipFunction_t fn = nullptr;
     int prec = 0, nrows = 3, n_fields = 0, n_scalars = 0;
+    int groups = 4;  // 64-site groups per block
     bool from_cache = false;
 };
 
@@ -564,7 +781,7 @@ const char *kOptions[] = {"-O3", "-std=c++17", "-Xclang", "-target-feature", "-X
 constexpr int kNumOptions = sizeof(kOptions) / sizeof(kOptions[0]);
 
 int parse_and_generate(const char *expr, qdpx_prec prec, qdpx_linkfmt fmt, int n_fields, int n_scalars,
-                       std::string &source, const char *fn) {
+                       std::string &source, int &groups, const char *fn) {
     char msg[512];
     if (!expr) return set_error(QDPX_EINVAL, (std::string(fn) + ": expression is NULL").c_str());
     if ((prec != QDPX_F64 && prec != QDPX_F32) || (fmt != QDPX_LINK18 && fmt != QDPX_LINK12) ||
@@ -584,6 +801,7 @@ int parse_and_generate(const char *expr, qdpx_prec prec, qdpx_linkfmt fmt, int n
         return set_error(QDPX_EINVAL, msg);
     }
     source = generate(*root, prec, fmt == QDPX_LINK12 ? 2 : 3, n_fields, n_scalars);
+    groups = groups_per_block(*root);
     return QDPX_OK;
 }
 
@@ -603,7 +821,8 @@ void jit_release(const qdpx_ctx *ctx) {
 extern "C" int qdpx_jit_generate(const char *expr, qdpx_prec prec, qdpx_linkfmt fmt, int32_t n_fields,
                                  int32_t n_scalars, char *buf, size_t buf_bytes, size_t *needed) {
     std::string src;
-    if (int r = parse_and_generate(expr, prec, fmt, n_fields, n_scalars, src, "qdpx_jit_generate")) return r;
+    int groups = 0;
+    if (int r = parse_and_generate(expr, prec, fmt, n_fields, n_scalars, src, groups, "qdpx_jit_generate")) return r;
     if (needed) *needed = src.size() + 1;
     if (buf && buf_bytes) {
         const size_t n = std::min(buf_bytes - 1, src.size());
@@ -620,7 +839,7 @@ extern "C" int qdpx_jit_compile(qdpx_ctx *ctx, const char *expr, qdpx_prec prec,
     if (!ctx || !kernel) return set_error(QDPX_EINVAL, "qdpx_jit_compile: ctx or kernel is NULL");
     if (int r = device_ok(ctx, fn)) return r;
     JitKernel k;
-    if (int r = parse_and_generate(expr, prec, fmt, n_fields, n_scalars, k.source, fn)) return r;
+    if (int r = parse_and_generate(expr, prec, fmt, n_fields, n_scalars, k.source, k.groups, fn)) return r;
     k.prec = prec;
     k.nrows = (fmt == QDPX_LINK12) ? 2 : 3;
     k.n_fields = n_fields;
@@ -727,6 +946,7 @@ extern "C" int qdpx_jit_eval(qdpx_ctx *ctx, int32_t kernel, const qdpx_geom *geo
         k.nrows = src.nrows;
         k.n_fields = src.n_fields;
         k.n_scalars = src.n_scalars;
+        k.groups = src.groups;
     }
     if (!U || !out || !fields) return set_error(QDPX_EINVAL, "qdpx_jit_eval: NULL pointer");
     if ((uintptr_t)U & 15u) return set_error(QDPX_EINVAL, "qdpx_jit_eval: link field not 16-byte aligned");
@@ -749,8 +969,14 @@ extern "C" int qdpx_jit_eval(qdpx_ctx *ctx, int32_t kernel, const qdpx_geom *geo
     if (k.n_scalars && !scalars) return set_error(QDPX_EINVAL, "qdpx_jit_eval: scalars is NULL");
     const size_t need = (size_t)workspace_reduce_bytes(geom);
     if (norm2 && (!work || work_bytes < need)) return set_error(QDPX_ENOMEM, "qdpx_jit_eval: workspace too small");
-    const Geo g = make_geo(geom->L);
-    long long S = (long long)g.S;
+    Geo g = make_geo(geom->L);
+    // The block order of the hand-written hop: tiles where an XCD's share of
+    // the fields and half the links is beyond its L2.
+    LaunchCfg cfg;
+    const int bytes = k.prec == QDPX_F64 ? 192 + 192 : 96 + (k.nrows == 2 ? 96 : 144);
+    if ((int64_t)g.V / kXcds * bytes > kXcdL2 && tile_plan(g, bytes, false, k.groups)) cfg.xcd = 2;
+    order_blocks(g, cfg, k.groups, bytes, false);
+    JitGeo geo = jit_geo(g, cfg.xcd);
     int L0 = geom->L[0], L1 = geom->L[1], L2 = geom->L[2], L3 = geom->L[3];
     double *partials = norm2 ? (double *)work : nullptr;
     // kernel arguments in declaration order
@@ -762,7 +988,7 @@ extern "C" int qdpx_jit_eval(qdpx_ctx *ctx, int32_t kernel, const qdpx_geom *geo
     args.push_back(&L1);
     args.push_back(&L2);
     args.push_back(&L3);
-    args.push_back(&S);
+    args.push_back(&geo);
     args.push_back(&U);
     for (int i = 0; i < k.n_fields; ++i) {
         fptr[i] = fields[i];
@@ -775,8 +1001,7 @@ extern "C" int qdpx_jit_eval(qdpx_ctx *ctx, int32_t kernel, const qdpx_geom *geo
         args.push_back(k.prec == QDPX_F64 ? (void *)&sd[i] : (void *)&sf[i]);
     }
     args.push_back(&partials);
-    const unsigned grid = (unsigned)((g.V + 255) / 256);
-    hipError_t e = hipModuleLaunchKernel(k.fn, grid, 1, 1, 256, 1, 1, 0, (hipStream_t)stream, args.data(), nullptr);
+    hipError_t e = hipModuleLaunchKernel(k.fn, (unsigned)cfg.grid, 1, 1, 256, 1, 1, 0, (hipStream_t)stream, args.data(), nullptr);
     if (e != hipSuccess) return set_error(QDPX_EHIP, "qdpx_jit_eval: launch failed");
     if (norm2) {
         e = launch_finalize(partials, shift_num_partials(g), 0, (double)g.V, norm2, (hipStream_t)stream);

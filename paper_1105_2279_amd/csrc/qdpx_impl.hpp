@@ -41,9 +41,17 @@ int tune_table_read(const char *path, const char *arch, std::vector<TuneEntry> &
 // Writes the table atomically (temporary file + rename); 0 or -1 (err set).
 int tune_table_write(const char *path, const char *arch, const std::vector<TuneEntry> &in, std::string &err);
 
+// Number of XCDs of the MI355X: each has its own L2 and its own work queue.
+constexpr int kXcds = 8;
+
 Geo make_geo(const int32_t L[4]);
 int launch_order(const Geo &g, const LaunchCfg &cfg, int groups_per_block);
 bool tile_plan(Geo &g, int bytes, bool fwd_only, int groups_per_block);
+// Default block order: where what an XCD's eighth of the lattice reads again
+// fits its L2, contiguous ranges of groups (every neighbour is read from
+// beyond the L2 once, and a lattice of few groups has no tiles); above, the
+// slab walk.
+constexpr int64_t kXcdL2 = 4 << 20;
 // Settles the order of a launch of groups_per_block 64-site groups a block:
 // the tiles of the slab walk in g, and in cfg the order and the grid.  Every
 // launch of a kernel that takes a LaunchCfg takes both from here.
@@ -89,8 +97,6 @@ int plaquette_num_partials(const Geo &g);  // per component (2 components)
 hipError_t launch_plaquette(const Geo &g, int prec, int nrows, const void *U, double *partials, hipStream_t st);
 
 // ---- batched.hip
-// Number of XCDs of the MI355X: each has its own L2 and its own work queue.
-constexpr int kXcds = 8;
 
 // One lattice of a batch (device table entry).  Its 64-site groups form a
 // (column, t-row) grid, group = col + ncol * row, where a column is one
