@@ -140,21 +140,35 @@ hipError_t launch_ape_step(const Geo &g, int prec, int nrows, const void *Uin, v
 // (without the bound the compiler takes 130 for three).
 template <typename R, int NR>
 __global__ void __launch_bounds__(64 * kPlaqWavesPerGroup) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 4 ? 4 : 1)))
-k_plaquette(Geo g, LinksRO<R, NR> U, double *__restrict__ partials) {
+k_plaquette(Geo g, LinksRO<R, NR> U, double *__restrict__ partials, int xcd) {
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    plaquette_wave(g, U, (int)blockIdx.x, w, (int)(threadIdx.x & 63), partials);
+    const int grp = xcd == 2 ? slabwalk(g, (int)blockIdx.x, 1) : xcd_tile(blockIdx.x, gridDim.x);
+    if (grp < 0) return;
+    plaquette_wave(g, U, grp, w, (int)(threadIdx.x & 63), partials);
 }
 
 int plaquette_num_partials(const Geo &g) { return kPlaqWavesPerGroup * ((g.V + 63) / 64); }
 
-hipError_t launch_plaquette(const Geo &g, int prec, int nrows, const void *U, double *partials, hipStream_t st) {
-    const dim3 grid((g.V + 63) / 64), block(64 * kPlaqWavesPerGroup);
+// Block order: contiguous ranges; the slab walk where what an XCD's share
+// reads again is far beyond its L2 (FP64, 16^3x32, 6 MB: 27.1 against 28.0 us;
+// 20^3x40, 15 MB: 45.9 against 45.7; 32^3x64: 323 against 291 us).  In dispatch
+// order, every neighbour on another XCD: 38.1, 62.1 and 292 us.
+constexpr int64_t kPlaqTiles = 16 << 20;
+
+hipError_t launch_plaquette(const Geo &geo, int prec, int nrows, const void *U, double *partials, hipStream_t st) {
+    Geo g = geo;
+    LaunchCfg cfg;
+    const int bytes = 4 * (prec == 0 ? 96 : 24 * nrows);  // of a site's links as read
+    if ((int64_t)g.V / kXcds * bytes > kPlaqTiles && tile_plan(g, bytes, true, 1)) cfg.xcd = 2;
+    order_blocks(g, cfg, 1, bytes, true);
+    const int xcd = cfg.xcd;
+    const dim3 grid(cfg.grid), block(64 * kPlaqWavesPerGroup);
     if (prec == 0)
-        k_plaquette<double, 3><<<grid, block, 0, st>>>(g, LinksRO<double, 3>{(const double2 *)U, g.S}, partials);
+        k_plaquette<double, 3><<<grid, block, 0, st>>>(g, LinksRO<double, 3>{(const double2 *)U, g.S}, partials, xcd);
     else if (nrows == 3)
-        k_plaquette<float, 3><<<grid, block, 0, st>>>(g, LinksRO<float, 3>{(const float2 *)U, g.S}, partials);
+        k_plaquette<float, 3><<<grid, block, 0, st>>>(g, LinksRO<float, 3>{(const float2 *)U, g.S}, partials, xcd);
     else
-        k_plaquette<float, 2><<<grid, block, 0, st>>>(g, LinksRO<float, 2>{(const float2 *)U, g.S}, partials);
+        k_plaquette<float, 2><<<grid, block, 0, st>>>(g, LinksRO<float, 2>{(const float2 *)U, g.S}, partials, xcd);
     return hipGetLastError();
 }
 
