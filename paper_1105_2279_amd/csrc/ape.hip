@@ -14,9 +14,9 @@ namespace qdpx {
 // loads in L1/L2; for FP64 links wave w % 4 of group w / 4 takes the four
 // directions of 16 of its sites (ape_group_f64).
 template <typename R, int NR, int NS, int MODE, int PROJ = 0, int LDS = 0>
-__global__ void __launch_bounds__(512) k_ape_step(Geo g, LinksRO<R, NR> U, LinksWO<R, NR> out, double c1,
-                                                  double c2, unsigned mask, double *__restrict__ partials, int xcd,
-                                                  int tw) {
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 && PROJ == 0 ? 3 : 1)))
+k_ape_step(Geo g, LinksRO<R, NR> U, LinksWO<R, NR> out, double c1, double c2, unsigned mask,
+           double *__restrict__ partials, int xcd, int tw) {
     const int tile = xcd == 1 ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
     const int mu = w & 3;
@@ -35,7 +35,7 @@ __global__ void __launch_bounds__(512) k_ape_step(Geo g, LinksRO<R, NR> U, Links
     // the same bits.
     static_assert(MODE == kApe || sizeof(R) == 8, "FP32 steps take their plaquettes from k_plaquette");
     static_assert(LDS == 0 || (sizeof(R) == 4 && PROJ == 0), "LDS tiles belong to the FP32 row projection");
-    // Dynamic LDS, sized at launch: kF64BackPerWave double2 per wave (FP64), or
+    // Dynamic LDS, sized at launch: f64_lds_per_wave double2 per wave (FP64), or
     // per group ape_lds_f4_per_group(LDS) FP32 pairs: the own links, then
     // (LDS 2 and 3) the backward links, then (LDS 3 and 4) the four product
     // slots.
@@ -68,8 +68,8 @@ __global__ void __launch_bounds__(512) k_ape_step(Geo g, LinksRO<R, NR> U, Links
         }
         return;
     }
-    // FP64 steps exchange each lane's backward link through LDS (one
-    // kF64BackPerWave region per wave); FP32 steps without an LDS tile load
+    // FP64 steps exchange each lane's own and backward links through LDS (one
+    // f64_lds_per_wave region per wave); FP32 steps without an LDS tile load
     // every link
 #pragma unroll 1
     for (int j = 0; j < NS; ++j) {
@@ -77,7 +77,7 @@ __global__ void __launch_bounds__(512) k_ape_step(Geo g, LinksRO<R, NR> U, Links
         const int grp = xcd == 2 ? slabwalk(g, i, gpb * NS) : i < ngroups ? traverse(g, i, tw) : -1;
         if (grp < 0) continue;
         ape_group<R, NR, MODE, PROJ>(g, U, out, c1, c2, mask, partials, grp, mu, lane, nullptr,
-                                     sizeof(R) == 8 ? lds_dyn + w * kF64BackPerWave : nullptr);
+                                     sizeof(R) == 8 ? lds_dyn + w * f64_lds_per_wave(MODE) : nullptr);
     }
 }
 
@@ -93,7 +93,7 @@ hipError_t launch_ape_step(const Geo &g, int prec, int nrows, const void *Uin, v
     const int gpb = cfg.block / 256;
     const int grid = cfg.grid, xcd = cfg.xcd;
     const int lds_level = (prec != 0 && !proj) ? cfg.lds : 0;
-    const size_t lds64 = (prec == 0 && !proj) ? sizeof(double2) * kF64BackPerWave * (cfg.block / 64)
+    const size_t lds64 = (prec == 0 && !proj) ? sizeof(double2) * f64_lds_per_wave(mode) * (cfg.block / 64)
                                               : (size_t)16 * ape_lds_f4_per_group(lds_level) * gpb;
 #define QDPX_APE_LAUNCH(R, NR, NS, M, P, T)                                                                      \
     k_ape_step<R, NR, NS, M, P, T><<<grid, cfg.block, lds64, st>>>(g, LinksRO<R, NR>{(const vec2_t<R> *)Uin, g.S}, \

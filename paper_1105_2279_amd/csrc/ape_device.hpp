@@ -206,21 +206,22 @@ __device__ __forceinline__ void plaquette_wave(const Geo &g, const LinksRO<R, NR
 // products (link precision) and one 2x2 determinant (FP64) instead of the
 // third row of X.  Exact for SU(3) arguments; stored links and their
 // products are SU(3) to the rounding of the link precision.
-template <typename R> __device__ __forceinline__ double retrace_rows01(const M23<R> &u, const M23<R> &X) {
-    Cx<R> p[2][2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            p[a][b] = Cx<R>{(R)0, (R)0};
-#pragma unroll
-            for (int j = 0; j < 3; ++j) cmac_ca(p[a][b], X.e[a][j], u.e[b][j]);
-        }
-    const double p00r = p[0][0].re, p00i = p[0][0].im, p11r = p[1][1].re, p11i = p[1][1].im;
-    const double p01r = p[0][1].re, p01i = p[0][1].im, p10r = p[1][0].re, p10i = p[1][0].im;
-    const double d = fma(p00r, p11r, -(p00i * p11i)) - fma(p01r, p10r, -(p01i * p10i));
-    return (p00r + p11r) + d;
-}
+template <typename R> struct RowTrace {
+    Cx<R> p[2][2] = {{{(R)0, (R)0}, {(R)0, (R)0}}, {{(R)0, (R)0}, {(R)0, (R)0}}};
+    // column j of rows 0 and 1 of U and X
+    __device__ __forceinline__ void add(const Cx<R> &u0, const Cx<R> &u1, const Cx<R> &x0, const Cx<R> &x1) {
+        cmac_ca(p[0][0], x0, u0);
+        cmac_ca(p[0][1], x0, u1);
+        cmac_ca(p[1][0], x1, u0);
+        cmac_ca(p[1][1], x1, u1);
+    }
+    __device__ __forceinline__ double value() const {
+        const double p00r = p[0][0].re, p00i = p[0][0].im, p11r = p[1][1].re, p11i = p[1][1].im;
+        const double p01r = p[0][1].re, p01i = p[0][1].im, p10r = p[1][0].re, p10i = p[1][0].im;
+        const double d = fma(p00r, p11r, -(p00i * p11i)) - fma(p01r, p10r, -(p01i * p10i));
+        return (p00r + p11r) + d;
+    }
+};
 
 // Coordinate mu of x for a run-time, wave-uniform mu.  The FP32 steps read it
 // through selects: with their LDS staging, indexing the array made the
@@ -570,29 +571,54 @@ enum ApeMode { kApe = 0, kApePlaq = 1 };
 // L ^ 16 (p + 1) (same site, direction nu) forms those of plane mu.  The two
 // upper staples U_nu(x) U_mu(x+nu) U_nu(x+mu)^dag and U_mu(x) U_nu(x+mu)
 // U_mu(x+nu)^dag are made of the same four links, so each lane loads one
-// neighbour link, U_mu(x+nu), and takes U_nu(x+mu) and rows 0 and 1 of
-// U_nu(x) from its partner by cross-lane exchange; the lower staple's
-// U_nu(x-nu) is the partner's backward link, which every lane loads once
-// and shares through LDS.  Every link is read as its rows 0 and 1, row 2
-// rebuilt in FP64.  A link update then issues 84 vector loads of 16 bytes
-// instead of 151: the memory pipeline, not the arithmetic, bounds the FP64
-// step.  The fused plaquette takes each plane once, in the
-// lane of its lower direction.  Direction-dependent addresses differ
-// between lanes here, so they are formed in 64 bits per lane.
+// neighbour link, U_mu(x+nu), and takes U_nu(x+mu) from its partner by
+// cross-lane exchange.  The partner's own link U_nu(x) and its backward link
+// U_nu(x-nu) (the lower staple's) every lane loads once and shares through
+// LDS.  Every link is read as its rows 0 and 1, row 2 rebuilt in FP64: 66
+// vector loads of 16 bytes per link update.  The fused plaquette takes each
+// plane once, in the lane of its lower direction.
+//
+// What bounds the step is the latency of those loads at the three waves per
+// SIMD that its registers allow, so the loads of a half phase are issued
+// while the half phase before is computed: U_mu(x-nu) before the upper
+// staple, U_nu(x-nu+mu) before the lower one's first product and the next
+// phase's U_mu(x+nu) before its second.  Against 84 loads, each half phase's
+// issued and waited for in it: 882 to 837 us at 32^3x64, 272 to 258 us at
+// 24^3x48 (327 to 301 us with the plaquette), 5360 to 4706 us at 48^3x96, 76 to
+// 68 us at 14x18x22x30.  Direction-dependent addresses differ between lanes
+// here, so they are formed in 64 bits per lane.
 
-constexpr int kF64BackPerWave = 6 * 64;  // double2 per wave: columns 0 and 1 of one backward link per lane
+// double2 per wave: columns 0 and 1 of one backward link per lane, then rows
+// 0 and 1 of its own link, then (kApePlaq) the lane's two traces, kept here
+// for want of registers: 12 or 13 KB, of which a CU's LDS holds the twelve
+// that three waves per SIMD need.
+constexpr int kF64LinkLds = 6 * 64;
+__host__ __device__ constexpr int f64_lds_per_wave(int mode) { return 2 * kF64LinkLds + (mode ? 64 : 0); }
 
+// v[i] for a per-lane i in 0..3, by the two bits of i
 __device__ __forceinline__ int sel4(int i, int a, int b, int c, int d) {
-    return i == 0 ? a : i == 1 ? b : i == 2 ? c : d;
+    const int lo = (i & 1) ? b : a, hi = (i & 1) ? d : c;
+    return (i & 2) ? hi : lo;
 }
-// x +- mu for a per-lane mu (selects instead of indexing the geometry)
-__device__ __forceinline__ int hop_fwd_v(const Geo &g, int s, int cmu, int mu) {
-    const int L = sel4(mu, g.L[0], g.L[1], g.L[2], g.L[3]), st = sel4(mu, g.st[0], g.st[1], g.st[2], g.st[3]);
-    return (cmu == L - 1) ? s - (L - 1) * st : s + st;
+// Where a site lies on the lattice's edges: bit d set at the upper end of
+// direction d, bit 4 + d at the lower end (one register in place of four
+// coordinates).
+__device__ __forceinline__ int edge_bits(const Geo &g, const Site &x) {
+    int e = 0;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        e |= x.c[d] == g.L[d] - 1 ? 1 << d : 0;
+        e |= x.c[d] == 0 ? 16 << d : 0;
+    }
+    return e;
 }
-__device__ __forceinline__ int hop_bwd_v(const Geo &g, int s, int cmu, int mu) {
-    const int L = sel4(mu, g.L[0], g.L[1], g.L[2], g.L[3]), st = sel4(mu, g.st[0], g.st[1], g.st[2], g.st[3]);
-    return (cmu == 0) ? s + (L - 1) * st : s - st;
+// Steps from a site to x + mu and x - mu for a per-lane mu
+__device__ __forceinline__ void hops_v(const Geo &g, int edges, int mu, int &fwd, int &bwd) {
+    const int st = sel4(mu, g.st[0], g.st[1], g.st[2], g.st[3]);
+    const int wrap = sel4(mu, (g.L[0] - 1) * g.st[0], (g.L[1] - 1) * g.st[1], (g.L[2] - 1) * g.st[2],
+                          (g.L[3] - 1) * g.st[3]);
+    fwd = (edges >> mu) & 1 ? -wrap : st;
+    bwd = (edges >> (mu + 4)) & 1 ? wrap : -st;
 }
 
 // Element c of the FP64 link at site s of a direction whose array starts at
@@ -608,44 +634,62 @@ __device__ __forceinline__ void st_lane(double2 *dir, int64_t S, int c, int s, c
 __device__ __forceinline__ Cx<double> xchg(const Cx<double> &z, int m) {
     return Cx<double>{__shfl_xor(z.re, m, 64), __shfl_xor(z.im, m, 64)};
 }
-// FP64 link at site s: rows 0 and 1 loaded, row 2 rebuilt as conj(row0 x row1)
-// (exact for SU(3) links; a smeared link's stored row 2 is that by
-// construction), so each neighbour link moves 96 bytes instead of 144.
+// Rows 0 and 1 of the FP64 link at site s; row 2 is rebuilt from them
+// (rebuild_row2) where it is used: exact for SU(3) links, and a smeared
+// link's stored row 2 is that by construction.
 __device__ __forceinline__ void ld_lane_rows01(const double2 *dir, int64_t S, int s, M3<double> &m) {
 #pragma unroll
     for (int c = 0; c < 6; ++c) m.e[c / 3][c % 3] = ld_lane(dir, S, c, s);
-    rebuild_row2(m);
 }
+__device__ __forceinline__ Cx<double> ld_lds(const double2 *p) { return Cx<double>{p->x, p->y}; }
 
 // One wave's share of an FP64 step: the four directions of 16 sites of
-// group grp.  back: this wave's kF64BackPerWave LDS entries.  In kApePlaq
-// mode also the plaquette traces of the INPUT links: partials[grp*4 + w]
+// group grp.  lds: this wave's f64_lds_per_wave(MODE) entries.  In kApePlaq mode
+// also the plaquette traces of the INPUT links: partials[grp*4 + w]
 // (spatial planes) and partials[4*ngroups + grp*4 + w] (temporal planes).
 template <int MODE>
 __device__ __forceinline__ void ape_group_f64(const Geo &g, const LinksRO<double, 3> &U, const LinksWO<double, 3> &out,
                                               double c1, double c2, unsigned mask, double *__restrict__ partials,
-                                              int grp, int w, int lane, double2 *back) {
+                                              int grp, int w, int lane, double2 *lds) {
     const int ngroups = num_groups(g);
-    const int mu = lane >> 4;
+    int mu = lane >> 4;
+    // opaque here, so that what depends on it alone is formed for each group
+    // and not kept in registers across a loop over groups
+    asm volatile("" : "+v"(mu));
     Site x;
     const bool live = group_site(g, grp, 16 * w + (lane & 15), x);
     if (!live) x.init(g, 0);  // padding lanes load from site 0 and store nothing
     const int s = x.s;
-    const int cmu = coord(x, mu);
     const bool smear = (mask >> mu) & 1u;
     const int64_t S9 = 9 * U.S;
     const double2 *dmu = U.p + mu * S9;  // this lane's direction
+    double2 *back = lds, *own = lds + kF64LinkLds;
+    double *trace = reinterpret_cast<double *>(lds + 2 * kF64LinkLds) + lane;  // spatial, 64 on temporal
+    const int edges = edge_bits(g, x);
+    // steps to x + mu, and to x + nu and x - nu of the coming phase; the lanes
+    // of a plane that is not smeared load their own link instead (in the L1)
+    int f_mu, f_nu, b_nu;
+    auto active = [&](int nu) { return smear && ((mask >> nu) & 1u); };
+    M3<double> B;          // U_mu(x+nu) of the coming phase
     {
+        int b_mu;
+        hops_v(g, edges, mu, f_mu, b_mu);
+        hops_v(g, edges, mu ^ 1, f_nu, b_nu);
+        M3<double> bl, u;
+        ld_lane_rows01(dmu, U.S, s + b_mu, bl);
+        ld_lane_rows01(dmu, U.S, s, u);
+        ld_lane_rows01(dmu, U.S, active(mu ^ 1) ? s + f_nu : s, B);
+        __builtin_amdgcn_sched_barrier(0);  // every load first
         // columns 0 and 1 of the backward link U_mu(x-mu) (all the lower
-        // staple reads), for the lanes of the other directions: entry
-        // 2k + i holds element (k, i)
-        const int sb = hop_bwd_v(g, s, cmu, mu);
-        M3<double> bl;
-        ld_lane_rows01(dmu, U.S, sb, bl);
+        // staple reads), entry 2k + i holding element (k, i), and rows 0 and
+        // 1 of the own link, for the lanes of the other directions
+        rebuild_row2(bl);
 #pragma unroll
         for (int k = 0; k < 3; ++k)
 #pragma unroll
             for (int i = 0; i < 2; ++i) back[(2 * k + i) * 64 + lane] = double2{bl.e[k][i].re, bl.e[k][i].im};
+#pragma unroll
+        for (int c = 0; c < 6; ++c) own[c * 64 + lane] = double2{u.e[c / 3][c % 3].re, u.e[c / 3][c % 3].im};
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -655,143 +699,126 @@ __device__ __forceinline__ void ape_group_f64(const Geo &g, const LinksRO<double
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 3; ++j) S[i][j] = Cx<double>{0.0, 0.0};
-    double sp = 0.0, tp = 0.0;
+    if constexpr (MODE != kApe) trace[0] = trace[64] = 0.0;
 #pragma unroll 1
     for (int p = 0; p < 3; ++p) {
-        const int xm = 16 * (p + 1);
+        const int xm = 16 * (p + 1), pl = lane ^ xm;  // the partner's lane
         const int nu = mu ^ (p + 1);
         // plane (mu, nu) is smeared for this lane exactly when it is for the
         // partner (both directions in the mask)
-        const bool act = smear && ((mask >> nu) & 1u);
+        const bool act = active(nu);
         const bool own_plane = mu < nu;  // the plaquette of the plane is taken here
-        const int cnu = coord(x, nu);
-        // upper: U_nu(x) U_mu(x+nu) U_nu(x+mu)^dag.  B = U_mu(x+nu) is loaded by
-        // every lane (the partner needs it); rows of U_nu(x) (the partner's
-        // own rows) and of U_nu(x+mu) (the partner's B) are exchanged one at
-        // a time as the products consume them.
-        M3<double> B;
-        const int s_nu = hop_fwd_v(g, s, cnu, nu);
-        ld_lane_rows01(dmu, U.S, s_nu, B);
+        const int sy = s + b_nu;         // y = x - nu, of the same mu-coordinate as x
         const double2 *dnu = U.p + nu * S9;
-        Cx<double> T[2][3];
+        M3<double> LB;  // U_mu(y)
+        ld_lane_rows01(dmu, U.S, act ? sy : s, LB);
+        __builtin_amdgcn_sched_barrier(0);
+        {
+            // upper: U_nu(x) U_mu(x+nu) U_nu(x+mu)^dag, the rows of U_nu(x)
+            // (the partner's own) and of U_nu(x+mu) (the partner's B) taken
+            // one at a time as the products consume them
+            rebuild_row2(B);
+            Cx<double> T[2][3];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            Cx<double> a[3];  // row i of U_nu(x)
+            for (int i = 0; i < 2; ++i) {
+                Cx<double> a[3];  // row i of U_nu(x)
 #pragma unroll
-            for (int k = 0; k < 3; ++k) a[k] = ld_lane(dnu, U.S, 3 * i + k, s);
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                Cx<double> t{0.0, 0.0};
-#pragma unroll
-                for (int k = 0; k < 3; ++k) cmac(t, a[k], B.e[k][j]);
-                T[i][j] = t;
-            }
-        }
-        // X = T U_nu(x+mu)^dag: X_ij = sum_k T_ik conj(C_jk), C row j from the
-        // partner; every upper staple is formed on its own and then added, so
-        // the smeared link does not depend on whether the plaquette is taken.
-        Cx<double> X[2][3];
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j) X[i][j] = Cx<double>{0.0, 0.0};
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            Cx<double> cj[3];
-#pragma unroll
-            for (int k = 0; k < 3; ++k) cj[k] = xchg(B.e[j][k], xm);
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int k = 0; k < 3; ++k) cmac_cb(X[i][j], T[i][k], cj[k]);
-        }
-        if (act) {
-            if constexpr (MODE != kApe) {
-                if (own_plane) {
-                    M23<double> uu, xx;  // rows 0 and 1 of U_mu(x) and of X
-#pragma unroll
-                    for (int i = 0; i < 2; ++i)
-#pragma unroll
-                        for (int j = 0; j < 3; ++j) {
-                            uu.e[i][j] = ld_lane(dmu, U.S, 3 * i + j, s);
-                            xx.e[i][j] = X[i][j];
-                        }
-                    const double pl = retrace_rows01(uu, xx);
-                    if (nu == 3) tp += pl;
-                    else sp += pl;
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
+                for (int k = 0; k < 3; ++k) a[k] = ld_lds(own + (3 * i + k) * 64 + pl);
 #pragma unroll
                 for (int j = 0; j < 3; ++j) {
-                    S[i][j].re += X[i][j].re;
-                    S[i][j].im += X[i][j].im;
+                    Cx<double> t{0.0, 0.0};
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) cmac(t, a[k], B.e[k][j]);
+                    T[i][j] = t;
                 }
+            }
+            // X = T U_nu(x+mu)^dag by columns: X_ij = sum_k T_ik conj(C_jk), C row j
+            // from the partner; every upper staple is formed on its own and then
+            // added, so the smeared link does not depend on whether the plaquette
+            // is taken.
+            RowTrace<double> tr;
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                Cx<double> cj[3], X[2];
+#pragma unroll
+                for (int k = 0; k < 3; ++k) cj[k] = xchg(B.e[j][k], xm);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    X[i] = Cx<double>{0.0, 0.0};
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) cmac_cb(X[i], T[i][k], cj[k]);
+                }
+                if (act) {
+                    if constexpr (MODE != kApe)
+                        if (own_plane)  // with rows 0 and 1 of U_mu(x)
+                            tr.add(ld_lds(own + j * 64 + lane), ld_lds(own + (3 + j) * 64 + lane), X[0], X[1]);
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        S[i][j].re += X[i].re;
+                        S[i][j].im += X[i].im;
+                    }
+                }
+            }
+            if constexpr (MODE != kApe) {
+                if (act && own_plane) {
+                    trace[nu == 3 ? 64 : 0] += tr.value();
+                }
+            }
         }
+        __builtin_amdgcn_sched_barrier(0);
+        M3<double> LC;  // U_nu(y+mu)
+        ld_lane_rows01(act ? dnu : dmu, U.S, act ? sy + f_mu : s, LC);
+        __builtin_amdgcn_sched_barrier(0);
+        Cx<double> T[2][3];
         {
-            // lower: U_nu(y)^dag U_mu(y) U_nu(y+mu), y = x - nu, by rows k:
-            // T2_ij = sum_k conj(LA_ki) LB_kj with LA = U_nu(x-nu), the
+            // lower: U_nu(y)^dag U_mu(y) U_nu(y+mu) by rows k:
+            // T_ij = sum_k conj(LA_ki) LB_kj with LA = U_nu(x-nu), the
             // partner's backward link (columns 0 and 1 from LDS), then
-            // S_ij += sum_k T2_ik LC_kj
-            __builtin_amdgcn_sched_barrier(0);  // the lower staple's loads stay below the upper one
-            if (act) {
-                const int sy = hop_bwd_v(g, s, cnu, nu);
-                const int syf = hop_fwd_v(g, sy, cmu, mu);  // y has the same mu-coordinate as x
-                Cx<double> T2[2][3];
+            // S_ij += sum_k T_ik LC_kj
+            rebuild_row2(LB);
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 3; ++j) T[i][j] = Cx<double>{0.0, 0.0};
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                Cx<double> la[2];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) la[i] = ld_lds(back + (2 * k + i) * 64 + pl);
 #pragma unroll
                 for (int i = 0; i < 2; ++i)
 #pragma unroll
-                    for (int j = 0; j < 3; ++j) T2[i][j] = Cx<double>{0.0, 0.0};
-#pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    Cx<double> la[2], lb[3];
-#pragma unroll
-                    for (int i = 0; i < 2; ++i) {
-                        const double2 v = back[(2 * k + i) * 64 + (lane ^ xm)];
-                        la[i] = Cx<double>{v.x, v.y};
-                    }
-                    if (k < 2) {
-#pragma unroll
-                        for (int j = 0; j < 3; ++j) lb[j] = ld_lane(dmu, U.S, 3 * k + j, sy);
-                    } else {  // row 2 of U_mu(y), rebuilt from its rows 0 and 1
-                        M3<double> m;
-                        ld_lane_rows01(dmu, U.S, sy, m);
-#pragma unroll
-                        for (int j = 0; j < 3; ++j) lb[j] = m.e[2][j];
-                    }
-#pragma unroll
-                    for (int i = 0; i < 2; ++i)
-#pragma unroll
-                        for (int j = 0; j < 3; ++j) cmac_ca(T2[i][j], la[i], lb[j]);
-                }
-                M3<double> LC;
-                ld_lane_rows01(dnu, U.S, syf, LC);
-#pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    Cx<double> lc[3];
-#pragma unroll
-                    for (int j = 0; j < 3; ++j) lc[j] = LC.e[k][j];
-#pragma unroll
-                    for (int i = 0; i < 2; ++i)
-#pragma unroll
-                        for (int j = 0; j < 3; ++j) cmac(S[i][j], T2[i][k], lc[j]);
-                }
+                    for (int j = 0; j < 3; ++j) cmac_ca(T[i][j], la[i], LB.e[k][j]);
             }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (p < 2) {
+            hops_v(g, edges, mu ^ (p + 2), f_nu, b_nu);
+            ld_lane_rows01(dmu, U.S, active(mu ^ (p + 2)) ? s + f_nu : s, B);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (act) {
+            rebuild_row2(LC);
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 3; ++j) cmac(S[i][j], T[i][k], LC.e[k][j]);
         }
     }
     {
-        // the next group's backward links overwrite these: every lane has read
+        Cx<double> u0[2][3];  // rows 0 and 1 of U_mu(x)
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 3; ++b) u0[a][b] = ld_lds(own + (3 * a + b) * 64 + lane);
+        // the next group's links overwrite these: every lane has read
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         if (live) {
             double2 *omu = out.p + mu * S9;
-            Cx<double> u0[2][3];  // rows 0 and 1 of U_mu(x)
-#pragma unroll
-            for (int a = 0; a < 2; ++a)
-#pragma unroll
-                for (int b = 0; b < 3; ++b) u0[a][b] = ld_lane(dmu, U.S, 3 * a + b, s);
             if (!smear) {  // a direction outside the mask is copied
 #pragma unroll
                 for (int a = 0; a < 2; ++a)
@@ -817,9 +844,7 @@ __device__ __forceinline__ void ape_group_f64(const Geo &g, const LinksRO<double
         }
     }
     if constexpr (MODE != kApe) {
-        if (!live) sp = tp = 0.0;
-        sp = wave_sum(sp);
-        tp = wave_sum(tp);
+        const double sp = wave_sum(live ? trace[0] : 0.0), tp = wave_sum(live ? trace[64] : 0.0);
         if (lane == 0) {
             partials[grp * 4 + w] = sp;
             partials[4 * ngroups + grp * 4 + w] = tp;
@@ -835,13 +860,13 @@ __device__ __forceinline__ void ape_group_f64(const Geo &g, const LinksRO<double
 template <typename R, int NR, int MODE, int PROJ = 0>
 __device__ __forceinline__ void ape_group(const Geo &g, const LinksRO<R, NR> &U, const LinksWO<R, NR> &out, double c1,
                                           double c2, unsigned mask, double *__restrict__ partials, int grp, int mu,
-                                          int lane, const nv4_t<R> *own = nullptr, double2 *back64 = nullptr,
+                                          int lane, const nv4_t<R> *own = nullptr, double2 *lds64 = nullptr,
                                           const nv4_t<R> *back = nullptr) {
     static_assert(PROJ == 0 || MODE == kApe, "the polar projection runs without the fused plaquette");
     if constexpr (sizeof(R) == 8 && PROJ == 0) {
         // FP64 with the row projection: four directions per wave (mu is
         // then the wave's index within the group)
-        ape_group_f64<MODE>(g, U, out, c1, c2, mask, partials, grp, mu, lane, back64);
+        ape_group_f64<MODE>(g, U, out, c1, c2, mask, partials, grp, mu, lane, lds64);
         return;
     }
     static_assert(MODE == kApe || (sizeof(R) == 8 && PROJ == 0),

@@ -79,7 +79,7 @@ template <typename F> __device__ __forceinline__ int find_lattice(int n_lat, int
 // at most 128 registers, four waves per SIMD, what the LDS tile (36 KB per
 // group) leaves room for.
 template <typename R, int NR, int GPB>
-__global__ void __launch_bounds__(256 * GPB) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 4 ? 4 : 1)))
+__global__ void __launch_bounds__(256 * GPB) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 4 ? 4 : 3)))
 k_ape_batched(BatchArgs a, const BatchLat *__restrict__ lats) {
     __shared__ unsigned s_ticket;
     __shared__ int s_ok;
@@ -88,7 +88,7 @@ k_ape_batched(BatchArgs a, const BatchLat *__restrict__ lats) {
     __shared__ nv4_t<R> own[GPB][sizeof(R) == 4 ? 4 * 3 * 64 : 1];
     __shared__ nv4_t<R> back[GPB][sizeof(R) == 4 && ape_lds_back(kBatchedLds) ? kApeTileF4 : 1];
     __shared__ nv4_t<R> slots[GPB][sizeof(R) == 4 && ape_lds_slots(kBatchedLds) ? 4 * kApeSlotF4 : 1];
-    __shared__ double2 back64[sizeof(R) == 8 ? 4 * GPB * kF64BackPerWave : 1];  // FP64: backward links
+    __shared__ double2 lds64[sizeof(R) == 8 ? 4 * GPB * f64_lds_per_wave(kApe) : 1];  // FP64: own and backward links
     // mu is wave-uniform; readfirstlane lets the compiler keep it in an SGPR
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
     const int mu = w & 3, half = w >> 2;
@@ -146,7 +146,7 @@ k_ape_batched(BatchArgs a, const BatchLat *__restrict__ lats) {
                     } else {
                         if (valid)
                             ape_group<R, NR, kApe>(L.g, U, O, a.c1, a.c2, 0xFu, nullptr, grp, mu, lane, nullptr,
-                                                   back64 + w * kF64BackPerWave);
+                                                   lds64 + w * f64_lds_per_wave(kApe));
                     }
                 }
             }
