@@ -10,6 +10,7 @@ path, and importing this package fails loudly when the library is missing.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 
 import torch
@@ -61,6 +62,16 @@ def geom(L) -> Geom:
     for d in range(4):
         g.L[d] = int(L[d])
     return g
+
+
+@functools.lru_cache(maxsize=1024)
+def _geom_ref_of(x, y, z, t):
+    return ctypes.byref(geom((x, y, z, t)))
+
+
+def _geom_ref(L):
+    """The extents as the C entry points take them (they only read them)."""
+    return _geom_ref_of(int(L[0]), int(L[1]), int(L[2]), int(L[3]))
 
 
 _P = ctypes.c_void_p
@@ -142,8 +153,8 @@ def _ptr(t):
 
 
 def _stream(stream=None):
-    if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+    if stream is None:  # the current stream's handle, without an object for it
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
@@ -188,22 +199,22 @@ def qdpx_version() -> str:
 
 
 def qdpx_site_stride(L) -> int:
-    return int(lib().qdpx_site_stride(ctypes.byref(geom(L))))
+    return int(lib().qdpx_site_stride(_geom_ref(L)))
 
 
 def qdpx_links_bytes(L, prec, fmt) -> int:
-    return int(lib().qdpx_links_bytes(ctypes.byref(geom(L)), prec, fmt))
+    return int(lib().qdpx_links_bytes(_geom_ref(L), prec, fmt))
 
 
 def qdpx_fermion_bytes(L, prec) -> int:
-    return int(lib().qdpx_fermion_bytes(ctypes.byref(geom(L)), prec))
+    return int(lib().qdpx_fermion_bytes(_geom_ref(L), prec))
 
 
 def qdpx_workspace_bytes(op, L, prec, fmt, n=1) -> int:
     if op == OP_BATCHED:
         arr = (Geom * len(L))(*[geom(x) for x in L])
         return int(lib().qdpx_workspace_bytes(op, arr, prec, fmt, len(L)))
-    return int(lib().qdpx_workspace_bytes(op, ctypes.byref(geom(L)), prec, fmt, int(n)))
+    return int(lib().qdpx_workspace_bytes(op, _geom_ref(L), prec, fmt, int(n)))
 
 
 def empty_bytes(nbytes: int, device="cuda") -> torch.Tensor:
@@ -225,54 +236,54 @@ def alloc_workspace(op, L, prec, fmt, n=1, device="cuda") -> torch.Tensor:
 
 # ----------------------------------------------------------------- entry points
 def qdpx_pack_links(ctx, L, aos, prec, fmt, soa, stream=None):
-    _check(lib().qdpx_pack_links(ctx.handle, ctypes.byref(geom(L)), _ptr(aos), prec, fmt, _ptr(soa),
+    _check(lib().qdpx_pack_links(ctx.handle, _geom_ref(L), _ptr(aos), prec, fmt, _ptr(soa),
                                  _stream(stream)), "qdpx_pack_links")
 
 
 def qdpx_unpack_links(ctx, L, soa, prec, fmt, aos, stream=None):
-    _check(lib().qdpx_unpack_links(ctx.handle, ctypes.byref(geom(L)), _ptr(soa), prec, fmt, _ptr(aos),
+    _check(lib().qdpx_unpack_links(ctx.handle, _geom_ref(L), _ptr(soa), prec, fmt, _ptr(aos),
                                    _stream(stream)), "qdpx_unpack_links")
 
 
 def qdpx_pack_fermion(ctx, L, aos, prec, soa, stream=None):
-    _check(lib().qdpx_pack_fermion(ctx.handle, ctypes.byref(geom(L)), _ptr(aos), prec, _ptr(soa),
+    _check(lib().qdpx_pack_fermion(ctx.handle, _geom_ref(L), _ptr(aos), prec, _ptr(soa),
                                    _stream(stream)), "qdpx_pack_fermion")
 
 
 def qdpx_unpack_fermion(ctx, L, soa, prec, aos, stream=None):
-    _check(lib().qdpx_unpack_fermion(ctx.handle, ctypes.byref(geom(L)), _ptr(soa), prec, _ptr(aos),
+    _check(lib().qdpx_unpack_fermion(ctx.handle, _geom_ref(L), _ptr(soa), prec, _ptr(aos),
                                      _stream(stream)), "qdpx_unpack_fermion")
 
 
 def qdpx_eval_shift_mul_axpy(ctx, L, prec, fmt, U, psi, phi, a, chi, norm2=None, work=None, stream=None,
                              dir_mask=0xF, sign=1):
-    _check(lib().qdpx_eval_shift_mul_axpy(ctx.handle, ctypes.byref(geom(L)), prec, fmt, _ptr(U), _ptr(psi),
+    _check(lib().qdpx_eval_shift_mul_axpy(ctx.handle, _geom_ref(L), prec, fmt, _ptr(U), _ptr(psi),
                                           _ptr(phi), float(a), int(dir_mask), int(sign), _ptr(chi), _ptr(norm2),
                                           _ptr(work), _nbytes(work), _stream(stream)), "qdpx_eval_shift_mul_axpy")
 
 
 def qdpx_eval_shift_mul_axpy_noalloc(ctx, L, prec, fmt, U, psi, phi, a, chi, norm2=None, stream=None, dir_mask=0xF,
                                      sign=1):
-    _check(lib().qdpx_eval_shift_mul_axpy_noalloc(ctx.handle, ctypes.byref(geom(L)), prec, fmt, _ptr(U), _ptr(psi),
+    _check(lib().qdpx_eval_shift_mul_axpy_noalloc(ctx.handle, _geom_ref(L), prec, fmt, _ptr(U), _ptr(psi),
                                                   _ptr(phi), float(a), int(dir_mask), int(sign), _ptr(chi),
                                                   _ptr(norm2), _stream(stream)), "qdpx_eval_shift_mul_axpy_noalloc")
 
 
 def qdpx_shift_chain(ctx, L, prec, fmt, U, psi, phi, a, c, n_iter, norms=None, work=None, stream=None):
-    _check(lib().qdpx_shift_chain(ctx.handle, ctypes.byref(geom(L)), prec, fmt, _ptr(U), _ptr(psi), _ptr(phi),
+    _check(lib().qdpx_shift_chain(ctx.handle, _geom_ref(L), prec, fmt, _ptr(U), _ptr(psi), _ptr(phi),
                                   float(a), float(c), int(n_iter), _ptr(norms), _ptr(work), _nbytes(work),
                                   _stream(stream)), "qdpx_shift_chain")
 
 
 def qdpx_ape_smear(ctx, L, prec, fmt, U_in, U_out, alpha, n_steps, plaq=None, work=None, stream=None,
                    smear_mask=0xF, projection=0):
-    _check(lib().qdpx_ape_smear(ctx.handle, ctypes.byref(geom(L)), prec, fmt, _ptr(U_in), _ptr(U_out),
+    _check(lib().qdpx_ape_smear(ctx.handle, _geom_ref(L), prec, fmt, _ptr(U_in), _ptr(U_out),
                                 float(alpha), int(n_steps), int(smear_mask), int(projection), _ptr(plaq),
                                 _ptr(work), _nbytes(work), _stream(stream)), "qdpx_ape_smear")
 
 
 def qdpx_plaquette(ctx, L, prec, fmt, U, plaq, work, stream=None):
-    _check(lib().qdpx_plaquette(ctx.handle, ctypes.byref(geom(L)), prec, fmt, _ptr(U), _ptr(plaq), _ptr(work),
+    _check(lib().qdpx_plaquette(ctx.handle, _geom_ref(L), prec, fmt, _ptr(U), _ptr(plaq), _ptr(work),
                                 _nbytes(work), _stream(stream)), "qdpx_plaquette")
 
 
@@ -287,12 +298,12 @@ def qdpx_ape_smear_batched(ctx, Ls, prec, fmt, U_in, U_out, alpha, n_steps, plaq
 
 
 def qdpx_eval_hop(ctx, L, prec, fmt, U, psi, out, dir_mask=0xF, stream=None):
-    _check(lib().qdpx_eval_hop(ctx.handle, ctypes.byref(geom(L)), prec, fmt, _ptr(U), _ptr(psi), _ptr(out),
+    _check(lib().qdpx_eval_hop(ctx.handle, _geom_ref(L), prec, fmt, _ptr(U), _ptr(psi), _ptr(out),
                                int(dir_mask), _stream(stream)), "qdpx_eval_hop")
 
 
 def qdpx_jacobi_smear(ctx, L, prec, fmt, U, chi, kappa, n_iter, norm=1.0, dir_mask=0xF, work=None, stream=None):
-    _check(lib().qdpx_jacobi_smear(ctx.handle, ctypes.byref(geom(L)), prec, fmt, _ptr(U), _ptr(chi), float(kappa),
+    _check(lib().qdpx_jacobi_smear(ctx.handle, _geom_ref(L), prec, fmt, _ptr(U), _ptr(chi), float(kappa),
                                    int(n_iter), float(norm), int(dir_mask), _ptr(work), _nbytes(work),
                                    _stream(stream)), "qdpx_jacobi_smear")
 
@@ -326,12 +337,12 @@ def qdpx_jit_info(ctx, kernel):
 def qdpx_jit_eval(ctx, kernel, L, U, fields, scalars, out, norm2=None, work=None, stream=None):
     ptrs = (ctypes.c_void_p * max(1, len(fields)))(*[_ptr(f) for f in fields])
     sc = (ctypes.c_double * max(1, len(scalars)))(*[float(x) for x in scalars])
-    _check(lib().qdpx_jit_eval(ctx.handle, kernel, ctypes.byref(geom(L)), _ptr(U), ptrs, sc, _ptr(out), _ptr(norm2),
+    _check(lib().qdpx_jit_eval(ctx.handle, kernel, _geom_ref(L), _ptr(U), ptrs, sc, _ptr(out), _ptr(norm2),
                                _ptr(work), _nbytes(work), _stream(stream)), "qdpx_jit_eval")
 
 
 def qdpx_tune(ctx, op, L, prec, fmt, stream=None):
-    _check(lib().qdpx_tune(ctx.handle, op, ctypes.byref(geom(L)), prec, fmt, _stream(stream)), "qdpx_tune")
+    _check(lib().qdpx_tune(ctx.handle, op, _geom_ref(L), prec, fmt, _stream(stream)), "qdpx_tune")
 
 
 def qdpx_tune_batched(ctx, Ls, prec, fmt, n_steps, stream=None):
@@ -346,7 +357,7 @@ TUNE_SOURCES = ("default", "table", "tuned", "set")
 
 def _tune_get(ctx, op, L, prec, fmt):
     b, n, x, t, d, src = (ctypes.c_int32() for _ in range(6))
-    _check(lib().qdpx_tune_get(ctx.handle, op, ctypes.byref(geom(L)), prec, fmt, ctypes.byref(b), ctypes.byref(n),
+    _check(lib().qdpx_tune_get(ctx.handle, op, _geom_ref(L), prec, fmt, ctypes.byref(b), ctypes.byref(n),
                                ctypes.byref(x), ctypes.byref(t), ctypes.byref(d), ctypes.byref(src)),
            "qdpx_tune_get")
     return (int(b.value), int(n.value), int(x.value), int(t.value), int(d.value)), TUNE_SOURCES[src.value]
@@ -370,7 +381,7 @@ def qdpx_tune_set(ctx, op, L, prec, fmt, block, sites_per_thread, xcd_map, t_win
     """lds_tile None: the default (4 for the FP32 APE step, else 0)."""
     if lds_tile is None:
         lds_tile = 4 if (op == OP_APE and prec == F32) else 0
-    _check(lib().qdpx_tune_set(ctx.handle, op, ctypes.byref(geom(L)), prec, fmt, int(block),
+    _check(lib().qdpx_tune_set(ctx.handle, op, _geom_ref(L), prec, fmt, int(block),
                                int(sites_per_thread), int(xcd_map), int(t_window), int(lds_tile)), "qdpx_tune_set")
 
 

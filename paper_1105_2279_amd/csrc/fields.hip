@@ -2,6 +2,8 @@
 // expression chi = sum_mu U_mu(x) psi(x+mu) + a phi(x) with its fused FP64
 // norm, the chain update psi - c chi, and the deterministic finalisation of
 // FP64 partial sums.
+#include <type_traits>
+
 #include "qdpx_impl.hpp"
 #include "reduce_device.hpp"
 
@@ -310,6 +312,11 @@ hipError_t launch_unpack_fermion(const Geo &g, int prec, const void *soa, double
     return hipGetLastError();
 }
 
+// What a kernel with and without the slab walk takes of the geometry (a
+// launch copies its arguments: a tenth of its cost on the host for the walk's
+// 84 bytes).
+template <bool SLAB> using launch_geo = std::conditional_t<SLAB, Geo, GeoBase>;
+
 // ------------------------------------------------------- shift expression
 // chi(x) = sum_{mu in mask} h_mu(x) + a phi(x), with the forward hop
 // h_mu = U_mu(x) psi(x+mu) or (bwd) the backward hop
@@ -325,7 +332,7 @@ hipError_t launch_unpack_fermion(const Geo &g, int prec, const void *soa, double
 // order and reduced by a wave butterfly into one partial per group, so
 // every sum has a fixed order and nothing depends on the launch geometry.
 template <typename R, int NR, int MODE, int NS, bool SLAB>
-__global__ void __launch_bounds__(256) k_shift(Geo g, LinksRO<R, NR> U, FermRO<R> psi, FermRO<R> phi, R a, R c,
+__global__ void __launch_bounds__(256) k_shift(launch_geo<SLAB> g, LinksRO<R, NR> U, FermRO<R> psi, FermRO<R> phi, R a, R c,
                                                 unsigned mask, int bwd, FermWO<R> out, double *__restrict__ partials,
                                                 int xcd, int tw) {
     __shared__ vec2_t<R> part[4][12][64];  // [direction][component][lane]
@@ -338,8 +345,13 @@ __global__ void __launch_bounds__(256) k_shift(Geo g, LinksRO<R, NR> U, FermRO<R
     for (int j = 0; j < NS; ++j) {
         const int i = tile * NS + j;  // the same for the four waves
         if (!SLAB && i >= ngroups) return;
-        const int grp = SLAB ? slabwalk(g, i, NS) : traverse(g, i, tw);
-        if (SLAB && grp < 0) continue;
+        int grp;
+        if constexpr (SLAB) {
+            grp = slabwalk(g, i, NS);
+            if (grp < 0) continue;
+        } else {
+            grp = traverse(g, i, tw);
+        }
         Site x;
         const bool live = group_site(g, grp, lane, x);
         const int s = x.s;
@@ -497,7 +509,7 @@ hipError_t launch_shift(const Geo &g, int prec, int nrows, const void *U, const 
 // SLAB: the slab walk, compiled apart: its decoding in the same kernel took
 // 1.5 % off the other orders on small lattices (20^3x40 in x, y, z: 52 us).
 template <typename R, int NR, int NS, bool DIV, bool SLAB>
-__global__ void __launch_bounds__(256) k_hop(Geo g, LinksRO<R, NR> U, FermRO<R> psi, FermRO<R> s0, R kappa, R norm,
+__global__ void __launch_bounds__(256) k_hop(launch_geo<SLAB> g, LinksRO<R, NR> U, FermRO<R> psi, FermRO<R> s0, R kappa, R norm,
                                               unsigned mask, FermWO<R> out, int xcd, int tw) {
     __shared__ vec2_t<R> part[4][12][64];  // [direction][component][lane]
     const int tile = xcd == 1 ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
@@ -508,8 +520,13 @@ __global__ void __launch_bounds__(256) k_hop(Geo g, LinksRO<R, NR> U, FermRO<R> 
     for (int j = 0; j < NS; ++j) {
         const int i = tile * NS + j;  // the same for the four waves
         if (!SLAB && i >= ngroups) return;
-        const int grp = SLAB ? slabwalk(g, i, NS) : traverse(g, i, tw);
-        if (SLAB && grp < 0) continue;
+        int grp;
+        if constexpr (SLAB) {
+            grp = slabwalk(g, i, NS);
+            if (grp < 0) continue;
+        } else {
+            grp = traverse(g, i, tw);
+        }
         Site x;
         const bool live = group_site(g, grp, lane, x);
         const int s = x.s;

@@ -48,7 +48,7 @@ struct FastDiv {
 // number they are numbered as columns: group = column + ncol t, column =
 // p + P z.  The mapping depends only on the extents, so per-group partial
 // sums never depend on the launch.
-struct Geo {
+struct GeoBase {
     int L[4];
     int st[4];  // 1, Lx, Lx*Ly, Lx*Ly*Lz
     int V;
@@ -57,6 +57,8 @@ struct Geo {
     int64_t S;  // padded site count: V rounded up to 256
     // divisors of the site decoding: Lx, Ly, Lz, P, ncol
     FastDiv dL0, dL1, dL2, dP, dncol;
+};
+struct Geo : GeoBase {
     // The XCD slab walk (slabwalk): the ncol columns as nz layers of pz, cut
     // into tiles of wp columns by wz layers, nyt tiles a layer; a unit is one
     // tile in one of 2^wseg equal t ranges.
@@ -69,7 +71,7 @@ struct Geo {
 struct Site {
     int s;
     int c[4];
-    __device__ __forceinline__ void init(const Geo &g, int site) {
+    __device__ __forceinline__ void init(const GeoBase &g, int site) {
         s = site;
         const int q0 = g.dL0.div(site), q1 = g.dL1.div(q0), q2 = g.dL2.div(q1);
         c[0] = site - q0 * g.L[0];
@@ -79,12 +81,12 @@ struct Site {
     }
 };
 
-__device__ __forceinline__ int num_groups(const Geo &g) { return (g.V + 63) >> 6; }
+__device__ __forceinline__ int num_groups(const GeoBase &g) { return (g.V + 63) >> 6; }
 
 // Site of lane `lane` of group `grp` (grp is wave-uniform, so the divisions
 // run on the scalar unit).  Returns false for the padding lanes of the last
 // linear group.
-__device__ __forceinline__ bool group_site(const Geo &g, int grp, int lane, Site &x) {
+__device__ __forceinline__ bool group_site(const GeoBase &g, int grp, int lane, Site &x) {
     if (g.P) {  // z and t of the whole group, one division per lane
         const int r = g.dP.div(grp), p = grp - r * g.P, t = g.dL2.div(r);
         const int q = p * 64 + lane;
@@ -107,7 +109,7 @@ __device__ __forceinline__ bool group_site(const Geo &g, int grp, int lane, Site
 // each other's t neighbours in L2.  tw = 1 (or no columns) is the identity.
 // A bijection on [0, num_groups).
 // tw is a power of two (checked on the host).
-__device__ __forceinline__ int traverse(const Geo &g, int i, int tw) {
+__device__ __forceinline__ int traverse(const GeoBase &g, int i, int tw) {
     if (!g.ncol || tw <= 1) return i;
     const int tin = i & (tw - 1), rest = i >> __builtin_ctz(tw);
     const int tc = g.dncol.div(rest), c = rest - tc * g.ncol;
@@ -145,10 +147,10 @@ __device__ __forceinline__ int coord(const Site &x, int mu) {
     return mu == 0 ? x.c[0] : mu == 1 ? x.c[1] : mu == 2 ? x.c[2] : x.c[3];
 }
 
-__device__ __forceinline__ int hop_fwd(const Geo &g, int s, int cmu, int mu) {
+__device__ __forceinline__ int hop_fwd(const GeoBase &g, int s, int cmu, int mu) {
     return (cmu == g.L[mu] - 1) ? s - (g.L[mu] - 1) * g.st[mu] : s + g.st[mu];
 }
-__device__ __forceinline__ int hop_bwd(const Geo &g, int s, int cmu, int mu) {
+__device__ __forceinline__ int hop_bwd(const GeoBase &g, int s, int cmu, int mu) {
     return (cmu == 0) ? s + (g.L[mu] - 1) * g.st[mu] : s - g.st[mu];
 }
 
