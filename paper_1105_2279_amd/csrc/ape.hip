@@ -81,6 +81,24 @@ k_ape_step(Geo g, LinksRO<R, NR> U, LinksWO<R, NR> out, double c1, double c2, un
     }
 }
 
+// The step on a lattice of few groups: a block for each group and direction,
+// three waves (ape_split).  Taken while all of its blocks run at once, two a
+// CU in FP64 (185 registers) and six in FP32 (100): from there on the other
+// kernels' sharing between directions is worth more than the shorter chain.
+// A step against theirs: 4^4 FP64 5.1 / 7.9 us, FP32-12 5.3 / 8.5; 8^3x16 6.9 /
+// 9.2 and 5.5 / 8.8; 8^2x16^2 (256 groups) FP64 10.6 / 10.1, FP32-12 6.5 / 9.2;
+// 12^4 (324) FP32-12 8.2 / 10.4; 16^4 (1024) 31.4 / 26.6 and 15.6 / 13.9.
+constexpr int kSplitGroups64 = 128, kSplitGroups32 = 384;
+
+template <typename R, int NR, int MODE>
+__global__ void __launch_bounds__(192) k_ape_split(Geo g, LinksRO<R, NR> U, LinksWO<R, NR> out, double c1, double c2,
+                                                   unsigned mask, double *__restrict__ partials) {
+    __shared__ R part[2 * split_parts<R>() * 64];
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int b = xcd_tile(blockIdx.x, gridDim.x);
+    ape_split<R, NR, MODE>(g, U, out, c1, c2, mask, partials, b >> 2, b & 3, w, (int)(threadIdx.x & 63), part);
+}
+
 int ape_num_partials(const Geo &g) { return 4 * ((g.V + 63) / 64); }
 
 hipError_t launch_ape_step(const Geo &g, int prec, int nrows, const void *Uin, void *Uout, double c1, double c2,
@@ -90,6 +108,18 @@ hipError_t launch_ape_step(const Geo &g, int prec, int nrows, const void *Uin, v
     if (mode == kApePlaq && mask != 0xFu) return hipErrorInvalidValue;  // owned planes need every staple
     if (proj && mode != kApe) return hipErrorInvalidValue;             // polar: plaquettes in their own pass
     if (prec != 0 && mode != kApe) return hipErrorInvalidValue;        // FP32: plaquettes from k_plaquette
+    const int groups = (g.V + 63) / 64;
+    if (!proj && groups <= (prec == 0 ? kSplitGroups64 : kSplitGroups32)) {
+#define QDPX_SPLIT_LAUNCH(R, NR, M)                                                                        \
+    k_ape_split<R, NR, M><<<4 * groups, 192, 0, st>>>(g, LinksRO<R, NR>{(const vec2_t<R> *)Uin, g.S},      \
+                                                      LinksWO<R, NR>{(vec2_t<R> *)Uout, g.S}, c1, c2, mask, partials)
+        if (prec != 0 && nrows == 2) QDPX_SPLIT_LAUNCH(float, 2, kApe);
+        else if (prec != 0) QDPX_SPLIT_LAUNCH(float, 3, kApe);
+        else if (mode == kApePlaq) QDPX_SPLIT_LAUNCH(double, 3, kApePlaq);
+        else QDPX_SPLIT_LAUNCH(double, 3, kApe);
+#undef QDPX_SPLIT_LAUNCH
+        return hipGetLastError();
+    }
     const int gpb = cfg.block / 256;
     const int grid = cfg.grid, xcd = cfg.xcd;
     const int lds_level = (prec != 0 && !proj) ? cfg.lds : 0;

@@ -312,23 +312,24 @@ template <typename R> __device__ __forceinline__ void back_cols01(const nv4_t<R>
 // U_c(x+d)^dag, row 2 rebuilt as conj(row0 x row1), P being SU(3) to
 // rounding.  d is the lower direction in even groups and the higher one in
 // odd groups, so two neighbouring groups form equally many products per
-// direction.  The staple sum of U_mu(x) takes the planes nu = mu^1, mu^2,
-// mu^3 in that order; in each the lower staple is added to the sum and then
-// the upper one, formed on its own: U_c(x) P_d for the producer,
+// direction.  The staple sum of U_mu(x) is the sum of three plane sums, nu =
+// mu^1, mu^2, mu^3 in that order; in each the lower staple comes first and
+// the upper one is accumulated onto it: U_c(x) P_d for the producer,
 // U_d(x) P_d^dag for the consumer.  Whether each wave forms the products it
-// needs (staple_sum_rows01) or a plane's product is formed once and passed
-// to the consumer through LDS (staple_sum_rows01_shared), the arithmetic
-// and its order are the same, so every path gives the same bits.
+// needs (staple_sum_rows01), a plane's product is formed once and passed to
+// the consumer through LDS (staple_sum_rows01_shared), or three waves take a
+// plane each (ape_split), the arithmetic and its order are the same, so every
+// path gives the same bits.
 __device__ __forceinline__ bool plane_producer(int mu, int nu, int grp) { return (mu < nu) != ((grp & 1) != 0); }
 
 // P = U_d(x+c) U_c(x+d)^dag, rows 0 and 1 formed, row 2 rebuilt.
-template <typename R, int NR>
+template <typename R, int NR, bool SEL = false>
 __device__ __forceinline__ void plane_product(const Geo &g, const LinksRO<R, NR> &U, const Site &x, int d, int c,
                                               M3<R> &P) {
     M23<R> B;
-    U.rows01(d, hop_fwd(g, x.s, site_coord<R>(x, c), c), B);
+    U.rows01(d, hop_fwd<SEL>(g, x.s, site_coord<R>(x, c), c), B);
     M3<R> C;
-    U.full(c, hop_fwd(g, x.s, site_coord<R>(x, d), d), C);
+    U.full(c, hop_fwd<SEL>(g, x.s, site_coord<R>(x, d), d), C);
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -341,16 +342,18 @@ __device__ __forceinline__ void plane_product(const Geo &g, const LinksRO<R, NR>
     rebuild_row2(P);
 }
 
-// X = rows 0 and 1 of the upper staple from the plane's product: A P_d for
+// Q += rows 0 and 1 of the upper staple from the plane's product: A P_d for
 // the producer, A P_d^dag for the consumer (A = rows 0 and 1 of U_nu(x)).
 template <typename R>
-__device__ __forceinline__ void upper_staple(const M23<R> &A, const M3<R> &P, bool prod, M23<R> &X) {
+__device__ __forceinline__ void add_upper_staple(const M23<R> &A, const M3<R> &P, bool prod, M23<R> &Q) {
+    if (prod) acc_23_33(Q, A, P);  // wave-uniform
+    else acc_23_33dag(Q, A, P);
+}
+template <typename R> __device__ __forceinline__ void zero_23(M23<R> &S) {
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 3; ++j) X.e[i][j] = Cx<R>{(R)0, (R)0};
-    if (prod) acc_23_33(X, A, P);  // wave-uniform
-    else acc_23_33dag(X, A, P);
+        for (int j = 0; j < 3; ++j) S.e[i][j] = Cx<R>{(R)0, (R)0};
 }
 // S += X
 template <typename R> __device__ __forceinline__ void add_23(M23<R> &S, const M23<R> &X) {
@@ -366,10 +369,10 @@ template <typename R> __device__ __forceinline__ void add_23(M23<R> &S, const M2
 // S += rows 0 and 1 of the lower staple U_nu(y)^dag U_mu(y) U_nu(y+mu),
 // y = x - nu.  back: the group's backward links staged in LDS (FP32), or
 // nullptr to load U_nu(y).
-template <typename R, int NR>
+template <typename R, int NR, bool SEL = false>
 __device__ __forceinline__ void add_lower_staple(const Geo &g, const LinksRO<R, NR> &U, const Site &x, int mu, int nu,
                                                  M23<R> &S, const nv4_t<R> *back) {
-    const int y = hop_bwd(g, x.s, site_coord<R>(x, nu), nu);
+    const int y = hop_bwd<SEL>(g, x.s, site_coord<R>(x, nu), nu);
     M3<R> A;
     if (back) back_cols01(back, nu, A);  // wave nu's backward link, staged in LDS
     else U.full(nu, y, A);
@@ -378,8 +381,24 @@ __device__ __forceinline__ void add_lower_staple(const Geo &g, const LinksRO<R, 
     M23<R> T;
     mul_dag23_33(A, B, T);
     M3<R> C;
-    U.full(nu, hop_fwd(g, y, site_coord<R>(x, mu), mu), C);  // y has the same mu-coordinate as x
+    U.full(nu, hop_fwd<SEL>(g, y, site_coord<R>(x, mu), mu), C);  // y has the same mu-coordinate as x
     acc_23_33(S, T, C);
+}
+
+// Q = the two staples (rows 0 and 1) of link (x, mu) of group grp in the plane
+// (mu, nu), every product formed by this wave.
+template <typename R, int NR, bool SEL = false>
+__device__ __forceinline__ void plane_sum(const Geo &g, const LinksRO<R, NR> &U, const Site &x, int mu, int nu, int grp,
+                                          M23<R> &Q, const nv4_t<R> *own = nullptr, const nv4_t<R> *back = nullptr) {
+    const bool prod = plane_producer(mu, nu, grp);
+    zero_23(Q);
+    add_lower_staple<R, NR, SEL>(g, U, x, mu, nu, Q, back);
+    M3<R> P;
+    plane_product<R, NR, SEL>(g, U, x, prod ? mu : nu, prod ? nu : mu, P);
+    M23<R> A;                         // rows 0 and 1 of U_nu(x)
+    if (own) own_rows01(own, nu, A);  // wave nu's own link, staged in LDS
+    else U.rows01(nu, x.s, A);
+    add_upper_staple(A, P, prod, Q);
 }
 
 // Staple sum (rows 0 and 1) of link (x, mu) of group grp over the planes
@@ -390,27 +409,14 @@ template <typename R, int NR>
 __device__ __forceinline__ void staple_sum_rows01(const Geo &g, const LinksRO<R, NR> &U, const Site &x, int mu,
                                                   int grp, unsigned mask, M23<R> &S, const nv4_t<R> *own = nullptr,
                                                   const nv4_t<R> *back = nullptr) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) S.e[i][j] = Cx<R>{(R)0, (R)0};
+    zero_23(S);
 #pragma unroll 1
     for (int p = 0; p < 3; ++p) {
         const int nu = mu ^ (p + 1);
         if (!((mask >> nu) & 1u)) continue;  // wave-uniform
-        const bool prod = plane_producer(mu, nu, grp);
-        // the upper staple X is formed on its own, the lower one added to S,
-        // then X: in this order the compiler keeps 77 registers (LDS tile 2,
-        // FP32-12) instead of 105 with the lower staple first
-        M3<R> P;
-        plane_product(g, U, x, prod ? mu : nu, prod ? nu : mu, P);
-        M23<R> A;                         // rows 0 and 1 of U_nu(x)
-        if (own) own_rows01(own, nu, A);  // wave nu's own link, staged in LDS
-        else U.rows01(nu, x.s, A);
-        M23<R> X;
-        upper_staple(A, P, prod, X);
-        add_lower_staple(g, U, x, mu, nu, S, back);
-        add_23(S, X);
+        M23<R> Q;
+        plane_sum(g, U, x, mu, nu, grp, Q, own, back);
+        add_23(S, Q);
     }
 }
 
@@ -446,12 +452,11 @@ __device__ __forceinline__ void staple_sum_rows01_shared(const Geo &g, const Lin
                                                          const nv4_t<R> *own, const nv4_t<R> *back,
                                                          nv4_t<R> *slots) {
     const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) S.e[i][j] = Cx<R>{(R)0, (R)0};
+    zero_23(S);
 #pragma unroll 1
     for (int p = 0; p < 3; ++p) {
+        M23<R> Q;  // the plane sum
+        zero_23(Q);
         const int nu = mu ^ (p + 1);
         const bool act = work && ((mask >> nu) & 1u);  // wave-uniform; the same for both waves of the plane
         const bool prod = plane_producer(mu, nu, grp);
@@ -472,7 +477,7 @@ __device__ __forceinline__ void staple_sum_rows01_shared(const Geo &g, const Lin
                     slot[k * 64 + lane] = v;
                 }
             }
-            add_lower_staple(g, U, x, mu, nu, S, back);
+            add_lower_staple(g, U, x, mu, nu, Q, back);
         }
         __syncthreads();  // this phase's products are in LDS
         if (act) {
@@ -486,9 +491,8 @@ __device__ __forceinline__ void staple_sum_rows01_shared(const Geo &g, const Lin
             rebuild_row2(P);
             M23<R> A;  // rows 0 and 1 of U_nu(x)
             own_rows01(own, nu, A);
-            M23<R> X;
-            upper_staple(A, P, prod, X);
-            add_23(S, X);
+            add_upper_staple(A, P, prod, Q);
+            add_23(S, Q);
         }
     }
 }
@@ -539,15 +543,11 @@ __device__ __forceinline__ void store_narrowed(const LinksWO<R, NR> &out, int mu
     out.store(mu, s, o);
 }
 
-// W = c1 U_mu(x) + c2 S (rows 0 and 1, in FP64), projected by rows in FP64
-// and stored in link precision.  own: the group's own links in LDS, or
-// nullptr to load U_mu(x).
+// W = c1 u0 + c2 S (rows 0 and 1, in FP64), projected by rows in FP64 and
+// stored in link precision.
 template <typename R, int NR>
-__device__ __forceinline__ void finish_rows01(const LinksRO<R, NR> &U, const LinksWO<R, NR> &out, double c1,
-                                              double c2, int mu, int s, const M23<R> &S, const nv4_t<R> *own) {
-    M23<R> u0;
-    if (own) own_rows01(own, mu, u0);
-    else U.rows01(mu, s, u0);
+__device__ __forceinline__ void project_rows01(const LinksWO<R, NR> &out, double c1, double c2, int mu, int s,
+                                               const M23<R> &S, const M23<R> &u0) {
     Cx<double> wm[2][3], v[3][3];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -558,6 +558,15 @@ __device__ __forceinline__ void finish_rows01(const LinksRO<R, NR> &U, const Lin
         }
     reunitarise(wm, v);
     store_narrowed(out, mu, s, v);
+}
+// u0 = U_mu(x) from the group's own links in LDS, or loaded (own nullptr).
+template <typename R, int NR>
+__device__ __forceinline__ void finish_rows01(const LinksRO<R, NR> &U, const LinksWO<R, NR> &out, double c1,
+                                              double c2, int mu, int s, const M23<R> &S, const nv4_t<R> *own) {
+    M23<R> u0;
+    if (own) own_rows01(own, mu, u0);
+    else U.rows01(mu, s, u0);
+    project_rows01<R, NR>(out, c1, c2, mu, s, S, u0);
 }
 
 // What one (64-site group, direction) wave computes.
@@ -774,7 +783,7 @@ __device__ __forceinline__ void ape_group_f64(const Geo &g, const LinksRO<double
             // lower: U_nu(y)^dag U_mu(y) U_nu(y+mu) by rows k:
             // T_ij = sum_k conj(LA_ki) LB_kj with LA = U_nu(x-nu), the
             // partner's backward link (columns 0 and 1 from LDS), then
-            // S_ij += sum_k T_ik LC_kj
+            // S_ij += (sum_k T_ik LC_kj), formed on its own as the upper one
             rebuild_row2(LB);
 #pragma unroll
             for (int i = 0; i < 2; ++i)
@@ -800,11 +809,15 @@ __device__ __forceinline__ void ape_group_f64(const Geo &g, const LinksRO<double
         if (act) {
             rebuild_row2(LC);
 #pragma unroll
-            for (int k = 0; k < 3; ++k)
+            for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int i = 0; i < 2; ++i)
+                for (int j = 0; j < 3; ++j) {
+                    Cx<double> y{0.0, 0.0};
 #pragma unroll
-                    for (int j = 0; j < 3; ++j) cmac(S[i][j], T[i][k], LC.e[k][j]);
+                    for (int k = 0; k < 3; ++k) cmac(y, T[i][k], LC.e[k][j]);
+                    S[i][j].re += y.re;
+                    S[i][j].im += y.im;
+                }
         }
     }
     {
@@ -850,6 +863,119 @@ __device__ __forceinline__ void ape_group_f64(const Geo &g, const LinksRO<double
             partials[4 * ngroups + grp * 4 + w] = tp;
         }
     }
+}
+
+// ------------------------------------------------- small lattices: ape_split
+// On a lattice of few groups a step takes as long as one wave's chain of
+// loads and products, with most of the chip idle.  There three waves share a
+// link's staples: wave p of (group, direction mu) forms the two of the plane
+// nu = mu ^ (p + 1), all its loads in flight at once; waves 1 and 2 pass
+// theirs to wave 0 through LDS, which adds them in the order of the other
+// paths, so the bits are the same, and projects and stores the link.
+// part: split_parts R per lane and wave.  Contains a block barrier.
+// FP64: the upper and the lower staple, added one after the other; FP32: their sum.
+template <typename R> __host__ __device__ constexpr int split_parts() { return sizeof(R) == 8 ? 24 : 12; }
+
+// FP64: X = U_nu(x) U_mu(x+nu) U_nu(x+mu)^dag and Y = U_nu(y)^dag U_mu(y) U_nu(y+mu),
+// y = x - nu (rows 0 and 1), each product in the order of ape_group_f64.
+__device__ __forceinline__ void plane_staples_f64(const Geo &g, const LinksRO<double, 3> &U, const Site &x, int mu,
+                                                  int nu, M23<double> &X, M23<double> &Y) {
+    const int y = hop_bwd<true>(g, x.s, coord(x, nu), nu);
+    M3<double> B, C, LA, LB, LC;
+    M23<double> A, T;
+    U.rows01(nu, x.s, A);
+    U.load_rows<false, 2>(mu, hop_fwd<true>(g, x.s, coord(x, nu), nu), B.e);
+    U.load_rows<false, 2>(nu, hop_fwd<true>(g, x.s, coord(x, mu), mu), C.e);
+    U.load_rows<false, 2>(nu, y, LA.e);
+    U.load_rows<false, 2>(mu, y, LB.e);
+    U.load_rows<false, 2>(nu, hop_fwd<true>(g, y, coord(x, mu), mu), LC.e);
+    rebuild_row2(B);
+    mul_23_33(A, B, T);
+    rebuild_row2(C);
+    zero_23(X);
+    acc_23_33dag(X, T, C);
+    rebuild_row2(LA);
+    rebuild_row2(LB);
+    mul_dag23_33(LA, LB, T);
+    rebuild_row2(LC);
+    zero_23(Y);
+    acc_23_33(Y, T, LC);
+}
+
+template <typename R, int NR, int MODE>
+__device__ __forceinline__ void ape_split(const Geo &g, const LinksRO<R, NR> &U, const LinksWO<R, NR> &out, double c1,
+                                          double c2, unsigned mask, double *__restrict__ partials, int grp, int mu,
+                                          int p, int lane, R *part) {
+    static_assert(MODE == kApe || sizeof(R) == 8, "plaquettes of FP32 links come from the plaquette pass");
+    Site x;
+    const bool live = group_site(g, grp, lane, x);
+    if (!live) x.init(g, 0);  // padding lanes load from site 0 and store nothing
+    const int nu = mu ^ (p + 1);
+    const bool smear = (mask >> mu) & 1u;
+    // all wave-uniform
+    auto active = [&](int q) { return smear && ((mask >> (mu ^ (q + 1))) & 1u); };
+    M23<R> u0;
+    if (p == 0) U.rows01(mu, x.s, u0);
+    M23<R> q0, q1;  // FP32: the plane sum; FP64: the upper and the lower staple
+    if (active(p)) {
+        if constexpr (sizeof(R) == 8) plane_staples_f64(g, U, x, mu, nu, q0, q1);
+        else plane_sum<R, NR, true>(g, U, x, mu, nu, grp, q0);
+    }
+    if constexpr (MODE != kApe) {  // the plane's traces: spatial (0,1), (0,2), (1,2) and temporal (0,3), (1,3), (2,3)
+        if (mu < nu) {             // in entries 0, 1, 2 of the group's four
+            M23<R> own;
+            U.rows01(mu, x.s, own);
+            RowTrace<R> tr;
+#pragma unroll
+            for (int j = 0; j < 3; ++j) tr.add(own.e[0][j], own.e[1][j], q0.e[0][j], q0.e[1][j]);
+            const double t = wave_sum(live ? tr.value() : 0.0);
+            const int n4 = 4 * num_groups(g);
+            if (lane == 0) partials[nu == 3 ? n4 + 4 * grp + mu : 4 * grp + mu + nu - 1] = t;
+        } else if (mu == 3 && p == 0) {
+            if (lane == 0) partials[4 * grp + 3] = partials[4 * num_groups(g) + 4 * grp + 3] = 0.0;
+        }
+    }
+    constexpr int kParts = sizeof(R) == 8 ? 2 : 1;
+    if (p > 0 && active(p)) {
+        R *mine = part + (p - 1) * split_parts<R>() * 64 + lane;
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            mine[(2 * k) * 64] = q0.e[k / 3][k % 3].re;
+            mine[(2 * k + 1) * 64] = q0.e[k / 3][k % 3].im;
+            if constexpr (kParts == 2) {
+                mine[(12 + 2 * k) * 64] = q1.e[k / 3][k % 3].re;
+                mine[(13 + 2 * k) * 64] = q1.e[k / 3][k % 3].im;
+            }
+        }
+    }
+    __syncthreads();
+    if (p > 0 || !live) return;
+    if (!smear) {
+        M3<R> u;
+        U.full(mu, x.s, u);
+        out.store(mu, x.s, u.e);
+        return;
+    }
+    M23<R> S;
+    zero_23(S);
+    if (active(0)) {
+        add_23(S, q0);
+        if constexpr (kParts == 2) add_23(S, q1);
+    }
+#pragma unroll
+    for (int q = 1; q < 3; ++q) {
+        if (!active(q)) continue;
+        const R *theirs = part + (q - 1) * split_parts<R>() * 64 + lane;
+#pragma unroll
+        for (int h = 0; h < kParts; ++h) {
+            M23<R> v;
+#pragma unroll
+            for (int k = 0; k < 6; ++k)
+                v.e[k / 3][k % 3] = Cx<R>{theirs[(12 * h + 2 * k) * 64], theirs[(12 * h + 2 * k + 1) * 64]};
+            add_23(S, v);
+        }
+    }
+    project_rows01<R, NR>(out, c1, c2, mu, x.s, S, u0);
 }
 
 // One wave's share of a step: direction mu of the 64 sites of group grp,

@@ -154,6 +154,23 @@ __device__ __forceinline__ int hop_bwd(const GeoBase &g, int s, int cmu, int mu)
     return (cmu == 0) ? s + (g.L[mu] - 1) * g.st[mu] : s - g.st[mu];
 }
 
+// The same with the geometry read by selects: where a kernel's whole body is
+// one straight line (ape_split) the compiler takes the indexed reads of a
+// run-time mu for per-lane values.
+__device__ __forceinline__ int pick4(int mu, const int (&v)[4]) {
+    return mu == 0 ? v[0] : mu == 1 ? v[1] : mu == 2 ? v[2] : v[3];
+}
+template <bool SEL> __device__ __forceinline__ int hop_fwd(const GeoBase &g, int s, int cmu, int mu) {
+    if constexpr (!SEL) return hop_fwd(g, s, cmu, mu);
+    const int L = pick4(mu, g.L), st = pick4(mu, g.st);
+    return (cmu == L - 1) ? s - (L - 1) * st : s + st;
+}
+template <bool SEL> __device__ __forceinline__ int hop_bwd(const GeoBase &g, int s, int cmu, int mu) {
+    if constexpr (!SEL) return hop_bwd(g, s, cmu, mu);
+    const int L = pick4(mu, g.L), st = pick4(mu, g.st);
+    return (cmu == 0) ? s + (L - 1) * st : s - st;
+}
+
 // ------------------------------------------------------------------ complex
 template <typename R> struct V2;
 template <> struct V2<double> { using T = double2; };
