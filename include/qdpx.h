@@ -349,7 +349,8 @@ int qdpx_plaquette(qdpx_ctx *ctx, const qdpx_geom *geom, qdpx_prec prec, qdpx_li
  * one z plane each) are split into 8 contiguous ranges, one per XCD queue,
  * walked t-row by t-row.  Threads per block (256 or 512) and groups per
  * ticket come from qdpx_tune_batched, or qdpx_tune_set(ctx, QDPX_OP_BATCHED,
- * &geoms[0], prec, fmt, block, groups, 1, 1, 0) (default 256 and 1).  The
+ * &geoms[0], prec, fmt, block, groups, 1, 1, 0) (default 256 and 1
+ * in FP64, 512 and 2 in FP32).  The
  * final plaquettes are qdpx_plaquette's pass on each lattice's output. */
 int qdpx_ape_smear_batched(qdpx_ctx *ctx, int n_lat, const qdpx_geom *geoms, qdpx_prec prec,
                            qdpx_linkfmt fmt, const void *const *U_in, void *const *U_out,

@@ -362,7 +362,14 @@ static int groups_per_block(qdpx_op op, const LaunchCfg &c) { return op == QDPX_
 
 static LaunchCfg cfg_for(qdpx_ctx *ctx, qdpx_op op, const qdpx_geom *geom, qdpx_prec prec, qdpx_linkfmt fmt) {
     LaunchCfg c;
-    if (op == QDPX_OP_BATCHED) c.nsite = 1;  // groups per ticket
+    // nsite: groups per ticket.  FP32: two at a time, so that a block's two
+    // groups stage and wait together (24 uneven lattices FP32-12 6.4 to 6.0 ms, 32
+    // lattices FP32-18 10.8 to 10.5 ms); FP64 blocks of 512 threads leave a third
+    // of the registers idle (64 lattices 29.3 against 30.6 ms).
+    if (op == QDPX_OP_BATCHED && prec == QDPX_F32) {
+        c.block = 512;
+        c.nsite = 2;
+    }
     c.lds = default_lds(op, prec);
     if (ctx) {
         TuneKey k{(int)op, (int)prec, (int)fmt, {geom->L[0], geom->L[1], geom->L[2], geom->L[3]}};
