@@ -622,13 +622,18 @@ extern "C" int qdpx_jacobi_smear(qdpx_ctx *ctx, const qdpx_geom *geom, qdpx_prec
     void *s0 = work;
     void *tmp = (char *)work + round256(fb);
     // E_0: s0 = chi.  Iteration k reads the previous iterate (s0 for k = 0)
-    // and the last one lands in chi.
-    QDPX_TRY_HIP(launch_copy_fermion(g, prec, chi, s0, st), fn);
-    const void *src = s0;
+    // and the last one lands in chi.  With an even number the first writes to
+    // tmp, so that it can read chi itself and keep its copy on the way; with an
+    // odd one it writes to chi, and s0 is copied before.
+    const bool copied = n_iter & 1;
+    if (copied) QDPX_TRY_HIP(launch_copy_fermion(g, prec, chi, s0, st), fn);
+    const void *src = copied ? s0 : chi;
     for (int k = 0; k < n_iter; ++k) {
         void *dst = (((n_iter - 1 - k) & 1) == 0) ? chi : tmp;
         const bool last = (k == n_iter - 1);
-        QDPX_TRY_HIP(launch_hop(g, prec, nrows_of(fmt), U, src, s0, kappa, norm, last, dir_mask, dst, cfg, st), fn);
+        QDPX_TRY_HIP(launch_hop(g, prec, nrows_of(fmt), U, src, k == 0 ? src : s0, kappa, norm, last, dir_mask, dst, cfg,
+                                st, k == 0 && !copied ? s0 : nullptr),
+                     fn);
         src = dst;
     }
     return QDPX_OK;

@@ -495,7 +495,8 @@ hipError_t launch_shift(const Geo &g, int prec, int nrows, const void *U, const 
 // out(x) = [s0(x) + kappa * (H psi)(x)] / norm, with
 // (H psi)(x) = sum_{mu in mask} [U_mu(x) psi(x+mu) + U_mu(x-mu)^dag psi(x-mu)],
 // the hopping term of the smearing operator K.  s0 may be absent (then
-// out = kappa H psi / norm); DIV selects the division by norm.
+// out = kappa H psi / norm); DIV selects the division by norm.  keep, where
+// given, receives a copy of s0.
 //
 // A block of 256 threads holds one 64-site group per iteration and wave w
 // computes direction mu = w: its forward and backward hop for all 12 spinor
@@ -510,7 +511,7 @@ hipError_t launch_shift(const Geo &g, int prec, int nrows, const void *U, const 
 // 1.5 % off the other orders on small lattices (20^3x40 in x, y, z: 52 us).
 template <typename R, int NR, int NS, bool DIV, bool SLAB>
 __global__ void __launch_bounds__(256) k_hop(launch_geo<SLAB> g, LinksRO<R, NR> U, FermRO<R> psi, FermRO<R> s0, R kappa, R norm,
-                                              unsigned mask, FermWO<R> out, int xcd, int tw) {
+                                              unsigned mask, FermWO<R> out, FermWO<R> keep, int xcd, int tw) {
     __shared__ vec2_t<R> part[4][12][64];  // [direction][component][lane]
     const int tile = xcd == 1 ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
     const int lane = threadIdx.x & 63;
@@ -606,23 +607,24 @@ __global__ void __launch_bounds__(256) k_hop(launch_geo<SLAB> g, LinksRO<R, NR> 
                 o[t] = v;
             }
             out.st_owned(mu, s, o);
+            if (keep.p) keep.st_owned(mu, s, z);
         }
     }
 }
 
 template <typename R, int NR, bool DIV>
 static void hop_dispatch_ns(const Geo &g, const void *U, const void *psi, const void *s0, double kappa, double norm,
-                            unsigned mask, void *out, const LaunchCfg &cfg, hipStream_t st) {
+                            unsigned mask, void *out, const LaunchCfg &cfg, hipStream_t st, void *keep) {
     using V = vec2_t<R>;
     LinksRO<R, NR> u{(const V *)U, g.S};
     FermRO<R> p{(const V *)psi, g.S}, z{(const V *)s0, g.S};
-    FermWO<R> o{(V *)out, g.S};
+    FermWO<R> o{(V *)out, g.S}, c{(V *)keep, g.S};
     const int grid = cfg.grid, xcd = cfg.xcd;
 #define QDPX_HOP_LAUNCH(NS)                                                                                  \
     if (xcd == 2)                                                                                            \
-        k_hop<R, NR, NS, DIV, true><<<grid, 256, 0, st>>>(g, u, p, z, (R)kappa, (R)norm, mask, o, 2, 1);     \
+        k_hop<R, NR, NS, DIV, true><<<grid, 256, 0, st>>>(g, u, p, z, (R)kappa, (R)norm, mask, o, c, 2, 1);  \
     else                                                                                                     \
-        k_hop<R, NR, NS, DIV, false><<<grid, 256, 0, st>>>(g, u, p, z, (R)kappa, (R)norm, mask, o, xcd, cfg.tw)
+        k_hop<R, NR, NS, DIV, false><<<grid, 256, 0, st>>>(g, u, p, z, (R)kappa, (R)norm, mask, o, c, xcd, cfg.tw)
     switch (cfg.nsite) {
     case 2: QDPX_HOP_LAUNCH(2); break;
     case 4: QDPX_HOP_LAUNCH(4); break;
@@ -634,16 +636,18 @@ static void hop_dispatch_ns(const Geo &g, const void *U, const void *psi, const 
 
 template <bool DIV>
 static void hop_dispatch(const Geo &g, int prec, int nrows, const void *U, const void *psi, const void *s0,
-                         double kappa, double norm, unsigned mask, void *out, const LaunchCfg &cfg, hipStream_t st) {
-    if (prec == 0) hop_dispatch_ns<double, 3, DIV>(g, U, psi, s0, kappa, norm, mask, out, cfg, st);
-    else if (nrows == 3) hop_dispatch_ns<float, 3, DIV>(g, U, psi, s0, kappa, norm, mask, out, cfg, st);
-    else hop_dispatch_ns<float, 2, DIV>(g, U, psi, s0, kappa, norm, mask, out, cfg, st);
+                         double kappa, double norm, unsigned mask, void *out, const LaunchCfg &cfg, hipStream_t st,
+                         void *keep) {
+    if (prec == 0) hop_dispatch_ns<double, 3, DIV>(g, U, psi, s0, kappa, norm, mask, out, cfg, st, keep);
+    else if (nrows == 3) hop_dispatch_ns<float, 3, DIV>(g, U, psi, s0, kappa, norm, mask, out, cfg, st, keep);
+    else hop_dispatch_ns<float, 2, DIV>(g, U, psi, s0, kappa, norm, mask, out, cfg, st, keep);
 }
 
 hipError_t launch_hop(const Geo &g, int prec, int nrows, const void *U, const void *psi, const void *s0, double kappa,
-                      double norm, bool divide, unsigned mask, void *out, const LaunchCfg &cfg, hipStream_t st) {
-    if (divide) hop_dispatch<true>(g, prec, nrows, U, psi, s0, kappa, norm, mask, out, cfg, st);
-    else hop_dispatch<false>(g, prec, nrows, U, psi, s0, kappa, norm, mask, out, cfg, st);
+                      double norm, bool divide, unsigned mask, void *out, const LaunchCfg &cfg, hipStream_t st,
+                      void *keep) {
+    if (divide) hop_dispatch<true>(g, prec, nrows, U, psi, s0, kappa, norm, mask, out, cfg, st, keep);
+    else hop_dispatch<false>(g, prec, nrows, U, psi, s0, kappa, norm, mask, out, cfg, st, keep);
     return hipGetLastError();
 }
 
