@@ -345,13 +345,14 @@ int qdpx_plaquette(qdpx_ctx *ctx, const qdpx_geom *geom, qdpx_prec prec, qdpx_li
  * and replays of a graph that captured one, reuse the table and only enqueue
  * the kernels.  Links and plaquettes are identical, bit for bit, to
  * qdpx_ape_smear on each lattice with plaquettes requested.  Work items are
- * runs of 64-site groups of one lattice: each lattice's columns (one brick of
- * one z plane each) are split into 8 contiguous ranges, one per XCD queue,
+ * runs of 64-site groups of one lattice: each lattice's columns (one group of
+ * a t plane each; a single row of all groups where a t plane is no whole
+ * number of them) are split into 8 contiguous ranges, one per XCD queue,
  * walked t-row by t-row.  Threads per block (256 or 512) and groups per
  * ticket come from qdpx_tune_batched, or qdpx_tune_set(ctx, QDPX_OP_BATCHED,
- * &geoms[0], prec, fmt, block, groups, 1, 1, 0) (default 256 and 1
- * in FP64, 512 and 2 in FP32).  The
- * final plaquettes are qdpx_plaquette's pass on each lattice's output. */
+ * &geoms[0], prec, fmt, block, groups, 1, 1, 0) (default 256 and 1;
+ * 512 and 2 for a batch of at most 16384 groups, 2^20 sites).  The final
+ * plaquettes are qdpx_plaquette's pass on each lattice's output. */
 int qdpx_ape_smear_batched(qdpx_ctx *ctx, int n_lat, const qdpx_geom *geoms, qdpx_prec prec,
                            qdpx_linkfmt fmt, const void *const *U_in, void *const *U_out,
                            double alpha, int n_steps, double *plaq, void *work, size_t work_bytes,
@@ -409,18 +410,20 @@ int qdpx_jit_eval(qdpx_ctx *ctx, int32_t kernel, const qdpx_geom *geom, const vo
  * wave, the block order over the 8 XCDs (xcd_map 0: dispatch order; 1: each
  * XCD a contiguous range of groups; 2: each XCD tiles of the (y, z) cross
  * section that its L2 holds, each walked t plane by t plane, used where the
- * groups of a t plane are a whole number, else order 0), the number of t planes walked together, and the LDS
- * tile of the FP32 APE step with the Gram-Schmidt projection (lds_tile 0:
- * every link loaded through the caches; 1: each 64-site group's own links,
- * rows 0 and 1, staged in LDS once for the four direction waves; 2: also
- * every site's backward links U_mu(x-mu), columns 0 and 1, which the lower
- * staples of the other three directions read; 3: also the plane products
- * U_mu(x+nu) U_nu(x+mu)^dag, which the upper staples of U_mu(x) and U_nu(x)
- * share, formed by one of the two direction waves and passed to the other
- * through LDS; 4: the own links and the plane products, the backward links
- * loaded; 0 in every other case: the FP64 step always exchanges backward
- * links through LDS, and the shift, hop and chain kernels meet their
- * per-direction partial sums there).
+ * groups of a t plane are a whole number, else order 0), the number of t
+ * planes walked together, and the LDS tile of the FP32 APE step with the
+ * Gram-Schmidt projection (lds_tile 0: every link loaded through the caches;
+ * 1: each 64-site group's own links, rows 0 and 1, staged in LDS once for the
+ * four direction waves; 2: also every site's backward links U_mu(x-mu),
+ * columns 0 and 1, which the lower staples of the other three directions
+ * read; 3: also the plane products U_mu(x+nu) U_nu(x+mu)^dag, which the upper
+ * staples of U_mu(x) and U_nu(x) share, formed by one of the two direction
+ * waves and passed to the other through LDS; 4: the own links and the plane
+ * products, the backward links loaded; 0 in every other case: the FP64 step
+ * always exchanges its own and backward links through LDS, and the shift, hop
+ * and chain kernels meet their per-direction partial sums there).  The APE
+ * step of a lattice of few groups takes a kernel of its own, whatever the
+ * geometry.
  * This is the auto-tuning of the thread geometry the paper proposes
  * (sections 5.4 and 9).  Allocates and frees temporary device buffers and
  * synchronises the device, so it returns QDPX_ECAPTURE on a capturing
@@ -431,10 +434,11 @@ int qdpx_jit_eval(qdpx_ctx *ctx, int32_t kernel, const qdpx_geom *geom, const vo
  * for the default geometry, 1 for one read from the launch table, 2 for one
  * qdpx_tune found, 3 for one qdpx_tune_set gave; a launch table written
  * without lds_tile gives the default, 4 for the FP32 APE step, else 0);
- * t_window must divide Lt and only matters when Lx Ly Lz is a multiple of 64.  For QDPX_OP_BATCHED (tuned by
- * qdpx_tune_batched, which qdpx_tune refuses with QDPX_EUNSUPPORTED) block is
- * 256 or 512 and sites_per_thread is the number of 64-site groups per work
- * ticket, keyed by the first lattice's extents. */
+ * t_window must divide Lt and only matters when Lx Ly Lz is a multiple of 64.
+ * For QDPX_OP_BATCHED (tuned by qdpx_tune_batched, which qdpx_tune refuses
+ * with QDPX_EUNSUPPORTED) block is 256 or 512 and sites_per_thread is the
+ * number of 64-site groups per work ticket, keyed by the first lattice's
+ * extents. */
 int qdpx_tune(qdpx_ctx *ctx, qdpx_op op, const qdpx_geom *geom, qdpx_prec prec, qdpx_linkfmt fmt,
               void *stream);
 int qdpx_tune_get(qdpx_ctx *ctx, qdpx_op op, const qdpx_geom *geom, qdpx_prec prec, qdpx_linkfmt fmt,

@@ -362,14 +362,7 @@ static int groups_per_block(qdpx_op op, const LaunchCfg &c) { return op == QDPX_
 
 static LaunchCfg cfg_for(qdpx_ctx *ctx, qdpx_op op, const qdpx_geom *geom, qdpx_prec prec, qdpx_linkfmt fmt) {
     LaunchCfg c;
-    // nsite: groups per ticket.  FP32: two at a time, so that a block's two
-    // groups stage and wait together (24 uneven lattices FP32-12 6.4 to 6.0 ms, 32
-    // lattices FP32-18 10.8 to 10.5 ms); FP64 blocks of 512 threads leave a third
-    // of the registers idle (64 lattices 29.3 against 30.6 ms).
-    if (op == QDPX_OP_BATCHED && prec == QDPX_F32) {
-        c.block = 512;
-        c.nsite = 2;
-    }
+    if (op == QDPX_OP_BATCHED) c.nsite = 1;  // groups per ticket
     c.lds = default_lds(op, prec);
     if (ctx) {
         TuneKey k{(int)op, (int)prec, (int)fmt, {geom->L[0], geom->L[1], geom->L[2], geom->L[3]}};
@@ -778,6 +771,27 @@ static unsigned spin_limit_from_env() {
     return (unsigned)strtoul(e, nullptr, 10);
 }
 
+// A batch of few groups without a stored geometry takes blocks of 512 threads
+// and two groups a ticket: half as many blocks meet at the end of a phase.  3
+// lattices, 68280 sites, three steps: FP32-12 113 against 151 us with 256 and 1,
+// FP64 154 against 180; 836096 sites FP32-18 807 / 835; 664574 FP64 1021 / 1039.
+// From 1.7 million sites on the larger blocks' coarser balance costs more: FP64
+// 2366 / 2265 us, FP32-12 1238 / 1242; 64 lattices of 14.4 million 15.3 / 15.0 ms.
+constexpr int64_t kBatchSmallGroups = 16384;
+
+static LaunchCfg batched_cfg(qdpx_ctx *ctx, int n_lat, const qdpx_geom *geoms, qdpx_prec prec, qdpx_linkfmt fmt) {
+    LaunchCfg c = cfg_for(ctx, QDPX_OP_BATCHED, &geoms[0], prec, fmt);
+    const int32_t *L = geoms[0].L;
+    if (ctx->tuned.count(TuneKey{(int)QDPX_OP_BATCHED, (int)prec, (int)fmt, {L[0], L[1], L[2], L[3]}})) return c;
+    int64_t groups = 0;
+    for (int i = 0; i < n_lat; ++i) groups += (make_geo(geoms[i].L).V + 63) / 64;
+    if (groups <= kBatchSmallGroups) {
+        c.block = 512;
+        c.nsite = 2;
+    }
+    return c;
+}
+
 extern "C" int qdpx_ape_smear_batched(qdpx_ctx *ctx, int n_lat, const qdpx_geom *geoms, qdpx_prec prec,
                                       qdpx_linkfmt fmt, const void *const *U_in, void *const *U_out, double alpha,
                                       int n_steps, double *plaq, void *work, size_t work_bytes, void *stream) {
@@ -814,7 +828,7 @@ extern "C" int qdpx_ape_smear_batched(qdpx_ctx *ctx, int n_lat, const qdpx_geom 
     // launch geometry: threads per block (256 or 512: one or two groups at a
     // time) and groups per ticket, tuned per (first lattice's extents,
     // precision, format)
-    const LaunchCfg bcfg = cfg_for(ctx, QDPX_OP_BATCHED, &geoms[0], prec, fmt);
+    const LaunchCfg bcfg = batched_cfg(ctx, n_lat, geoms, prec, fmt);
     const int block = bcfg.block == 512 ? 512 : 256;
     const int group_chunk = std::max(1, bcfg.nsite);
     // host table: each lattice's groups as a (column, t-row) grid, its
@@ -885,6 +899,7 @@ extern "C" int qdpx_ape_smear_batched(qdpx_ctx *ctx, int n_lat, const qdpx_geom 
     memset(&a, 0, sizeof a);
     a.lats = (const BatchLat *)dtab;
     a.counters = (unsigned *)work;
+    a.stride = batched_ticket_stride(n_steps, batched_counter_words(kBatchMaxSteps + 1));
     a.plaq = plaq;
     a.c1 = 1.0 - alpha;
     a.c2 = alpha / 6.0;

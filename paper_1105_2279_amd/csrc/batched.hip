@@ -3,23 +3,30 @@
 //
 // The persistent launch walks through phases, one per APE step.  Within a
 // phase the work items are runs of 64-site groups of one lattice.  A
-// lattice's groups form a (column, t-row) grid, a column being one brick (or
-// run of 64 sites) of one z plane; its columns are split into 8 contiguous
-// ranges, one per XCD, and XCD x's queue (ticket counter) walks its range
-// t-row by t-row, so a group's x, y and z neighbours are queued a few items
-// away and its t neighbours one range further, all on the XCD whose L2 holds
-// them (the slab walk of the single-lattice step, per lattice).  A block
-// reads its XCD from the XCC_ID hardware register, drains its own queue first
-// and then takes items from the other queues, so the load still balances;
-// which queue a block uses only affects speed.
+// lattice's groups form a (column, t-row) grid, a column being one group of a
+// t plane (where those are a whole number; else all groups form one row); its
+// columns are split into 8 contiguous ranges, one per XCD, and XCD x's queue
+// (ticket counter) walks its range t-row by t-row, so a group's x, y and z
+// neighbours are queued a few items away and its t neighbours one range
+// further, all on the XCD whose L2 holds them (the slab walk of the
+// single-lattice step, per lattice).  A block reads its XCD from the XCC_ID
+// hardware register, drains its own queue first and then takes items from the
+// other queues, so the load still balances; which queue a block uses only
+// affects speed.
 //
 // When a block finds every queue of the phase empty it publishes how many
-// items it finished (one release) and waits until the phase's completion
-// counter reaches the item count (one acquire).  Every item it waits for
-// was already taken by a running block, so the wait always ends and no
-// co-residency assumption is needed.  Fencing once per block and phase, not
-// per item, matters on the multi-XCD MI355X: an agent-scope acquire
-// invalidates the XCD's L2.  Every wait is bounded; on timeout the block
+// items it finished and waits until the count of finished items reaches the
+// phase's (one acquire).  Every item it waits for was already taken by a
+// running block, so the wait always ends and no co-residency assumption is
+// needed.  Fencing once per phase, not per item, matters on the multi-XCD
+// MI355X: an agent-scope acquire invalidates the XCD's L2 and a release
+// writes it back.  What a phase costs beyond its items is therefore one
+// write-back per XCD for all of its blocks that are ready (publish), one
+// acquire per block, polls without one, and counters on lines of their own:
+// 35 us with 512 blocks, where a release and an acquire by every wave, an
+// acquire with every poll and the counters of a phase side by side took 170
+// (3 lattices, 68280 sites, FP32-12, five steps: 774 to 174 us; 64 lattices of
+// 14.4 million sites 15.4 to 15.0 ms).  Every wait is bounded; on timeout the block
 // records the failure in the status word and leaves, so the grid drains.
 //
 // The plaquettes of the outputs follow as two ordinary launches (the traces
@@ -43,6 +50,15 @@ constexpr int kBatchedLds = 3;
 // partials per group).
 constexpr int kBatchMaxStage = 64;
 
+// Counters, in words of the workspace: [1] the status; [32] the count of
+// finished items; [64 + 32 x] XCD x's pending items; from kTicketWord on 8
+// ticket counters a phase.  Atomics of all XCDs on one 128-byte line run
+// one after another, so each counter has a line of its own, as far as the
+// workspace has room for the phases (batched_ticket_stride).  With the counters
+// of a phase side by side a phase of 3 lattices (68280 sites, FP32-12) took 67
+// us, apart 35.
+constexpr int kTicketWord = 64 + 32 * kXcds;
+
 __global__ void __launch_bounds__(256) k_batched_init(unsigned *__restrict__ counters, int n) {
     for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) counters[i] = 0u;
 }
@@ -52,13 +68,63 @@ __device__ __forceinline__ int xcd_id() {
     return (int)(__builtin_amdgcn_s_getreg((20) | (0 << 6) | ((4 - 1) << 11)) & (kXcds - 1));
 }
 
-// Take the next ticket of counter (thread 0) and broadcast it to the block.
-__device__ __forceinline__ unsigned take_ticket(unsigned *counter, unsigned *s_ticket) {
-    if (threadIdx.x == 0) *s_ticket = atomicAdd(counter, 1u);
+// Take the next ticket (thread 0) and broadcast it to the block: of queue q,
+// or, when that is empty, of the first of the others, in cyclic order, that
+// is not.  Returns the ticket with q the queue it came from, or -1 when every
+// queue was seen empty.  One read of the counters finds the queues that are
+// left, where an atomic on each, 8 in a row with two barriers each for every
+// block and phase, made them wait for one another.
+__device__ __forceinline__ int take_ticket(unsigned *counters, int stride, const int (&total)[kXcds], int &q,
+                                           int2 *s_ticket) {
+    if (threadIdx.x == 0) {
+        int r = -1, from = q;
+        unsigned left = (1u << kXcds) - 1;  // queues not seen empty
+        while (left) {
+            const unsigned n =
+                __hip_atomic_fetch_add(counters + stride * from, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (n < (unsigned)total[from]) {
+                r = (int)n;
+                break;
+            }
+            left &= ~(1u << from);
+            unsigned seen[kXcds];
+#pragma unroll
+            for (int k = 0; k < kXcds; ++k)
+                seen[k] = __hip_atomic_load(counters + stride * k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+            for (int k = 0; k < kXcds; ++k)
+                if (seen[k] >= (unsigned)total[k]) left &= ~(1u << k);
+            if (left) {  // the next one after `from`
+                const unsigned after = left >> from;
+                from = after ? from + __builtin_ctz(after) : __builtin_ctz(left);
+            }
+        }
+        *s_ticket = int2{r, from};
+    }
     __syncthreads();
-    const unsigned r = __builtin_amdgcn_readfirstlane(*s_ticket);
+    const int r = __builtin_amdgcn_readfirstlane(s_ticket->x);
+    q = __builtin_amdgcn_readfirstlane(s_ticket->y);
     __syncthreads();  // s_ticket is rewritten by the next call
     return r;
+}
+
+// Count `items` finished items of this block as done, device-wide.  Every
+// store of theirs is in the XCD's L2 (its wave has waited for it); what makes
+// it visible to the other XCDs is the write-back of that L2, which covers all
+// of the XCD's blocks (XCC_ID names the L2).  So the blocks of an XCD share
+// write-backs: `pending` holds the XCD's items that are in L2 and not yet
+// counted; the block that finds it empty writes back and counts for all,
+// until nothing is left.  A write-back by every block: 60 us a phase with 512
+// blocks (3 lattices, 68280 sites, FP32-12), this 35.
+__device__ __forceinline__ void publish(unsigned *pending, unsigned *done, unsigned items) {
+    if (__hip_atomic_fetch_add(pending, items, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return;
+    unsigned n = __hip_atomic_load(pending, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    while (n) {
+        asm volatile("" ::"v"(n) : "memory");  // n has arrived before the write-back begins
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        __hip_atomic_fetch_add(done, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        n = __hip_atomic_fetch_sub(pending, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - n;
+    }
 }
 
 // Lattice whose entry base(q) is the last one <= r (bases ascending).
@@ -81,7 +147,7 @@ template <typename F> __device__ __forceinline__ int find_lattice(int n_lat, int
 template <typename R, int NR, int GPB>
 __global__ void __launch_bounds__(256 * GPB) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 4 ? 4 : 3)))
 k_ape_batched(BatchArgs a, const BatchLat *__restrict__ lats) {
-    __shared__ unsigned s_ticket;
+    __shared__ int2 s_ticket;
     __shared__ int s_ok;
     // FP32: the LDS tile of the single-lattice step at level kBatchedLds,
     // each group's own links, backward links and plane-product slots
@@ -95,72 +161,73 @@ k_ape_batched(BatchArgs a, const BatchLat *__restrict__ lats) {
     const int xid = __builtin_amdgcn_readfirstlane(xcd_id());
     const int nph = a.n_steps;
     unsigned *status = a.counters + 1;
-    unsigned *tickets = a.counters + 2;             // [nph][kXcds]
-    unsigned *done = a.counters + 2 + nph * kXcds;  // [nph]
+    unsigned *done = a.counters + 32;  // items finished, over all phases (modulo 2^32)
+    unsigned *pending = a.counters + 64 + 32 * xid;
+    unsigned *tickets = a.counters + kTicketWord;  // [nph][kXcds], a.stride words apart
     const int per_ticket = a.group_chunk;           // groups per ticket
     for (int phase = 0; phase < nph; ++phase) {
         unsigned mine = 0;
         // step p reads the output of step p-1: step k writes to U_out when
         // n_steps-1-k is even, else to the lattice's scratch links
         const int src_odd = (a.n_steps - phase) & 1, dst_odd = (a.n_steps - 1 - phase) & 1;
-        for (int k = 0; k < kXcds; ++k) {
-            const int q = (xid + k) & (kXcds - 1);  // own queue first, then the others
-            for (;;) {
-                const unsigned r = take_ticket(tickets + phase * kXcds + q, &s_ticket);
-                if (r >= (unsigned)a.xtotal[q]) break;
-                ++mine;
-                const BatchLat &L =
-                    lats[find_lattice(a.n_lat, (int)r, [&](int i) { return lats[i].xbase[q]; })];  // read in place
-                const int ncols = L.xcol1[q] - L.xcol0[q];
-                const int j0 = ((int)r - L.xbase[q]) * per_ticket;
-                const int j1 = min(j0 + per_ticket, ncols * L.nrow);
-                const void *src = (phase == 0) ? L.in : (src_odd == 0 ? L.out : L.tmp);
-                void *dst = dst_odd == 0 ? L.out : L.tmp;
-                const LinksRO<R, NR> U{(const vec2_t<R> *)src, L.g.S};
-                const LinksWO<R, NR> O{(vec2_t<R> *)dst, L.g.S};
-                // GPB groups at a time, half h of the block taking j0 + h, ...
-                // (no early exit: every wave meets every barrier)
+        int q = xid;  // own queue first, then the others
+        for (;;) {
+            const int r = take_ticket(tickets + phase * kXcds * a.stride, a.stride, a.xtotal, q, &s_ticket);
+            if (r < 0) break;
+            ++mine;
+            const BatchLat &L =
+                lats[find_lattice(a.n_lat, r, [&](int i) { return lats[i].xbase[q]; })];  // read in place
+            const int ncols = L.xcol1[q] - L.xcol0[q];
+            const int j0 = (r - L.xbase[q]) * per_ticket;
+            const int j1 = min(j0 + per_ticket, ncols * L.nrow);
+            const void *src = (phase == 0) ? L.in : (src_odd == 0 ? L.out : L.tmp);
+            void *dst = dst_odd == 0 ? L.out : L.tmp;
+            const LinksRO<R, NR> U{(const vec2_t<R> *)src, L.g.S};
+            const LinksWO<R, NR> O{(vec2_t<R> *)dst, L.g.S};
+            // GPB groups at a time, half h of the block taking j0 + h, ...
+            // (no early exit: every wave meets every barrier)
 #pragma unroll 1
-                for (int jj = j0; jj < j1; jj += GPB) {
-                    const int j = jj + half;
-                    const bool valid = j < j1;
-                    int grp = 0;
+            for (int jj = j0; jj < j1; jj += GPB) {
+                const int j = jj + half;
+                const bool valid = j < j1;
+                int grp = 0;
+                if (valid) {
+                    const int row = L.dcols[q].div(j);
+                    grp = (L.xcol0[q] + (j - row * ncols)) + L.ncol * row;
+                }
+                if constexpr (sizeof(R) == 4) {  // links staged in LDS, as the single-lattice step
+                    nv4_t<R> *bk = ape_lds_back(kBatchedLds) ? back[half] : nullptr;
+                    if (jj > j0) __syncthreads();  // take_ticket's barriers separate items
                     if (valid) {
-                        const int row = L.dcols[q].div(j);
-                        grp = (L.xcol0[q] + (j - row * ncols)) + L.ncol * row;
+                        stage_own_link(L.g, U, grp, mu, lane, own[half]);
+                        if constexpr (ape_lds_back(kBatchedLds)) stage_back_link(L.g, U, grp, mu, lane, bk);
                     }
-                    if constexpr (sizeof(R) == 4) {  // links staged in LDS, as the single-lattice step
-                        nv4_t<R> *bk = ape_lds_back(kBatchedLds) ? back[half] : nullptr;
-                        if (jj > j0) __syncthreads();  // take_ticket's barriers separate items
-                        if (valid) {
-                            stage_own_link(L.g, U, grp, mu, lane, own[half]);
-                            if constexpr (ape_lds_back(kBatchedLds)) stage_back_link(L.g, U, grp, mu, lane, bk);
-                        }
-                        __syncthreads();
-                        if constexpr (ape_lds_slots(kBatchedLds))  // block barriers inside: every wave takes part
-                            ape_group_shared<R, NR>(L.g, U, O, a.c1, a.c2, 0xFu, grp, valid, mu, lane, own[half], bk,
-                                                    slots[half]);
-                        else if (valid)
-                            ape_group<R, NR, kApe>(L.g, U, O, a.c1, a.c2, 0xFu, nullptr, grp, mu, lane, own[half],
-                                                   nullptr, bk);
-                    } else {
-                        if (valid)
-                            ape_group<R, NR, kApe>(L.g, U, O, a.c1, a.c2, 0xFu, nullptr, grp, mu, lane, nullptr,
-                                                   lds64 + w * f64_lds_per_wave(kApe));
-                    }
+                    __syncthreads();
+                    if constexpr (ape_lds_slots(kBatchedLds))  // block barriers inside: every wave takes part
+                        ape_group_shared<R, NR>(L.g, U, O, a.c1, a.c2, 0xFu, grp, valid, mu, lane, own[half], bk,
+                                                slots[half]);
+                    else if (valid)
+                        ape_group<R, NR, kApe>(L.g, U, O, a.c1, a.c2, 0xFu, nullptr, grp, mu, lane, own[half],
+                                               nullptr, bk);
+                } else {
+                    if (valid)
+                        ape_group<R, NR, kApe>(L.g, U, O, a.c1, a.c2, 0xFu, nullptr, grp, mu, lane, nullptr,
+                                               lds64 + w * f64_lds_per_wave(kApe));
                 }
             }
         }
         if (phase + 1 == nph) break;
         const unsigned nitems = (unsigned)a.items_per_phase;
-        __syncthreads();  // every wave of the block has issued its stores
+        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's stores have reached the XCD's L2
+        __syncthreads();
         if (threadIdx.x == 0) {
-            __threadfence();  // release this block's links of the phase device-wide
-            atomicAdd(done + phase, mine);
+            if (mine) publish(pending, done, mine);
+            const unsigned target = (unsigned)(phase + 1) * nitems;
             unsigned spins = 0;
             int ok = 1;
-            while (__hip_atomic_load(done + phase, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) < nitems) {
-                __builtin_amdgcn_s_sleep(2);
+            // relaxed: an acquire on every poll would drop the L2 of the blocks still at work
+            while ((int)(__hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - target) < 0) {
+                __builtin_amdgcn_s_sleep(8);
                 if (++spins > a.spin_limit) {
                     ok = 0;
                     break;
@@ -168,10 +235,11 @@ k_ape_batched(BatchArgs a, const BatchLat *__restrict__ lats) {
             }
             if (!ok) atomicOr(status, 1u);
             s_ok = ok;
+            // the phase's results, for the whole block: its waves share the CU's L1
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         }
         __syncthreads();
         if (!s_ok) return;  // block-uniform
-        __threadfence();    // acquire the phase's results
     }
 }
 
@@ -234,6 +302,12 @@ int batched_resident_blocks(int prec, int nrows, int block) {
 
 int batched_counter_words(int max_phases) { return 2 + (kXcds + 1) * (max_phases + 1); }
 
+int batched_ticket_stride(int n_steps, int words) {
+    int stride = 32;
+    while (stride > 1 && kTicketWord + n_steps * kXcds * stride > words) stride /= 2;
+    return stride;
+}
+
 template <typename R, int NR>
 static void launch_all(const BatchArgs &a, int block, int grid, hipStream_t st) {
     if (block == 512) k_ape_batched<R, NR, 2><<<grid, 512, 0, st>>>(a, a.lats);
@@ -245,7 +319,7 @@ static void launch_all(const BatchArgs &a, int block, int grid, hipStream_t st) 
 }
 
 hipError_t launch_ape_batched(const BatchArgs &a, int prec, int nrows, int block, int grid, hipStream_t st) {
-    const int ncount = batched_counter_words(a.n_steps);
+    const int ncount = kTicketWord + a.n_steps * kXcds * a.stride;
     k_batched_init<<<std::min((ncount + 255) / 256, 1024), 256, 0, st>>>(a.counters, ncount);
     if (prec == 0) launch_all<double, 3>(a, block, grid, st);
     else if (nrows == 3) launch_all<float, 3>(a, block, grid, st);

@@ -122,10 +122,11 @@ struct BatchLat {
 
 struct BatchArgs {
     const BatchLat *lats;  // device table [n_lat]
-    unsigned *counters;    // [1] status, then per phase 8 ticket counters and a completion counter
+    unsigned *counters;    // [1] status, then the counts of items and the ticket counters
     double *plaq;          // nullable, [n_lat][3]
     double c1, c2;
     int n_lat, n_steps, group_chunk;
+    int stride;            // words between ticket counters
     int xtotal[kXcds];     // tickets in each XCD's queue per phase
     int items_per_phase;   // sum of xtotal
     int plaq_blocks;       // blocks of the plaquette launch
@@ -134,6 +135,8 @@ struct BatchArgs {
 
 int batched_max_stage_groups();
 int batched_counter_words(int max_phases);
+// words between the ticket counters of n_steps phases that `words` have room for
+int batched_ticket_stride(int n_steps, int words);
 int batched_plaq_blocks(int prec, int ngroups);
 // resident blocks of the persistent kernel with `block` (256 or 512) threads
 int batched_resident_blocks(int prec, int nrows, int block);
