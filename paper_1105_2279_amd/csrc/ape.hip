@@ -83,12 +83,12 @@ k_ape_step(Geo g, LinksRO<R, NR> U, LinksWO<R, NR> out, double c1, double c2, un
 
 // The step on a lattice of few groups: a block for each group and direction,
 // three waves (ape_split).  Taken while all of its blocks run at once, two a
-// CU in FP64 (185 registers) and six in FP32 (100): from there on the other
+// CU in FP64 (185 registers) and five in FP32 (120): from there on the other
 // kernels' sharing between directions is worth more than the shorter chain.
-// A step against theirs: 4^4 FP64 5.1 / 7.9 us, FP32-12 5.3 / 8.5; 8^3x16 6.9 /
-// 9.2 and 5.5 / 8.8; 8^2x16^2 (256 groups) FP64 10.6 / 10.1, FP32-12 6.5 / 9.2;
-// 12^4 (324) FP32-12 8.2 / 10.4; 16^4 (1024) 31.4 / 26.6 and 15.6 / 13.9.
-constexpr int kSplitGroups64 = 128, kSplitGroups32 = 384;
+// A step against theirs: 4^4 FP64 5.1 / 7.9 us, FP32-12 4.8 / 8.5; 8^3x16 6.9 /
+// 9.2 and 5.8 / 8.8; 8^2x16^2 (256 groups) FP64 10.6 / 10.1, FP32-12 7.5 / 9.2;
+// 8^2x16x20 (320) FP32-12 8.3; 16^4 (1024) FP64 31.4 / 26.6.
+constexpr int kSplitGroups64 = 128, kSplitGroups32 = 320;
 
 template <typename R, int NR, int MODE>
 __global__ void __launch_bounds__(192) k_ape_split(Geo g, LinksRO<R, NR> U, LinksWO<R, NR> out, double c1, double c2,

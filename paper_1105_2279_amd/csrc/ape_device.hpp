@@ -312,9 +312,9 @@ template <typename R> __device__ __forceinline__ void back_cols01(const nv4_t<R>
 // U_c(x+d)^dag, row 2 rebuilt as conj(row0 x row1), P being SU(3) to
 // rounding.  d is the lower direction in even groups and the higher one in
 // odd groups, so two neighbouring groups form equally many products per
-// direction.  The staple sum of U_mu(x) is the sum of three plane sums, nu =
-// mu^1, mu^2, mu^3 in that order; in each the lower staple comes first and
-// the upper one is accumulated onto it: U_c(x) P_d for the producer,
+// direction.  The staple sum of U_mu(x) takes the planes nu = mu^1, mu^2,
+// mu^3 in that order; in each the lower staple is accumulated onto the sum and
+// then the upper one, formed on its own, added: U_c(x) P_d for the producer,
 // U_d(x) P_d^dag for the consumer.  Whether each wave forms the products it
 // needs (staple_sum_rows01), a plane's product is formed once and passed to
 // the consumer through LDS (staple_sum_rows01_shared), or three waves take a
@@ -342,18 +342,19 @@ __device__ __forceinline__ void plane_product(const Geo &g, const LinksRO<R, NR>
     rebuild_row2(P);
 }
 
-// Q += rows 0 and 1 of the upper staple from the plane's product: A P_d for
-// the producer, A P_d^dag for the consumer (A = rows 0 and 1 of U_nu(x)).
-template <typename R>
-__device__ __forceinline__ void add_upper_staple(const M23<R> &A, const M3<R> &P, bool prod, M23<R> &Q) {
-    if (prod) acc_23_33(Q, A, P);  // wave-uniform
-    else acc_23_33dag(Q, A, P);
-}
 template <typename R> __device__ __forceinline__ void zero_23(M23<R> &S) {
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 3; ++j) S.e[i][j] = Cx<R>{(R)0, (R)0};
+}
+// X = rows 0 and 1 of the upper staple from the plane's product: A P_d for
+// the producer, A P_d^dag for the consumer (A = rows 0 and 1 of U_nu(x)).
+template <typename R>
+__device__ __forceinline__ void upper_staple(const M23<R> &A, const M3<R> &P, bool prod, M23<R> &X) {
+    zero_23(X);
+    if (prod) acc_23_33(X, A, P);  // wave-uniform
+    else acc_23_33dag(X, A, P);
 }
 // S += X
 template <typename R> __device__ __forceinline__ void add_23(M23<R> &S, const M23<R> &X) {
@@ -366,39 +367,43 @@ template <typename R> __device__ __forceinline__ void add_23(M23<R> &S, const M2
         }
 }
 
-// S += rows 0 and 1 of the lower staple U_nu(y)^dag U_mu(y) U_nu(y+mu),
-// y = x - nu.  back: the group's backward links staged in LDS (FP32), or
-// nullptr to load U_nu(y).
+// Rows 0 and 1 of the lower staple U_nu(y)^dag U_mu(y) U_nu(y+mu), y = x - nu,
+// as the factors T C.  back: the group's backward links staged in LDS
+// (FP32), or nullptr to load U_nu(y).
 template <typename R, int NR, bool SEL = false>
-__device__ __forceinline__ void add_lower_staple(const Geo &g, const LinksRO<R, NR> &U, const Site &x, int mu, int nu,
-                                                 M23<R> &S, const nv4_t<R> *back) {
+__device__ __forceinline__ void lower_staple(const Geo &g, const LinksRO<R, NR> &U, const Site &x, int mu, int nu,
+                                             M23<R> &T, M3<R> &C, const nv4_t<R> *back = nullptr) {
     const int y = hop_bwd<SEL>(g, x.s, site_coord<R>(x, nu), nu);
     M3<R> A;
     if (back) back_cols01(back, nu, A);  // wave nu's backward link, staged in LDS
     else U.full(nu, y, A);
     M3<R> B;
     U.full(mu, y, B);
-    M23<R> T;
     mul_dag23_33(A, B, T);
-    M3<R> C;
     U.full(nu, hop_fwd<SEL>(g, y, site_coord<R>(x, mu), mu), C);  // y has the same mu-coordinate as x
+}
+// S += the lower staple
+template <typename R, int NR>
+__device__ __forceinline__ void add_lower_staple(const Geo &g, const LinksRO<R, NR> &U, const Site &x, int mu, int nu,
+                                                 M23<R> &S, const nv4_t<R> *back) {
+    M23<R> T;
+    M3<R> C;
+    lower_staple(g, U, x, mu, nu, T, C, back);
     acc_23_33(S, T, C);
 }
 
-// Q = the two staples (rows 0 and 1) of link (x, mu) of group grp in the plane
-// (mu, nu), every product formed by this wave.
+// X = the upper staple (rows 0 and 1) of link (x, mu) of group grp in the plane
+// (mu, nu), its product formed by this wave.
 template <typename R, int NR, bool SEL = false>
-__device__ __forceinline__ void plane_sum(const Geo &g, const LinksRO<R, NR> &U, const Site &x, int mu, int nu, int grp,
-                                          M23<R> &Q, const nv4_t<R> *own = nullptr, const nv4_t<R> *back = nullptr) {
+__device__ __forceinline__ void plane_upper(const Geo &g, const LinksRO<R, NR> &U, const Site &x, int mu, int nu,
+                                            int grp, M23<R> &X, const nv4_t<R> *own = nullptr) {
     const bool prod = plane_producer(mu, nu, grp);
-    zero_23(Q);
-    add_lower_staple<R, NR, SEL>(g, U, x, mu, nu, Q, back);
     M3<R> P;
     plane_product<R, NR, SEL>(g, U, x, prod ? mu : nu, prod ? nu : mu, P);
     M23<R> A;                         // rows 0 and 1 of U_nu(x)
     if (own) own_rows01(own, nu, A);  // wave nu's own link, staged in LDS
     else U.rows01(nu, x.s, A);
-    add_upper_staple(A, P, prod, Q);
+    upper_staple(A, P, prod, X);
 }
 
 // Staple sum (rows 0 and 1) of link (x, mu) of group grp over the planes
@@ -414,9 +419,12 @@ __device__ __forceinline__ void staple_sum_rows01(const Geo &g, const LinksRO<R,
     for (int p = 0; p < 3; ++p) {
         const int nu = mu ^ (p + 1);
         if (!((mask >> nu) & 1u)) continue;  // wave-uniform
-        M23<R> Q;
-        plane_sum(g, U, x, mu, nu, grp, Q, own, back);
-        add_23(S, Q);
+        // X first: in this order the compiler keeps 77 registers (LDS tile 2,
+        // FP32-12) instead of 105 with the lower staple first
+        M23<R> X;
+        plane_upper(g, U, x, mu, nu, grp, X, own);
+        add_lower_staple(g, U, x, mu, nu, S, back);
+        add_23(S, X);
     }
 }
 
@@ -460,8 +468,6 @@ __device__ __forceinline__ void staple_sum_rows01_shared(const Geo &g, const Lin
     zero_23(S);
 #pragma unroll 1
     for (int p = 0; p < 3; ++p) {
-        M23<R> Q;  // the plane sum
-        zero_23(Q);
         const int nu = mu ^ (p + 1);
         const bool act = work && ((mask >> nu) & 1u);  // wave-uniform; the same for both waves of the plane
         const bool prod = plane_producer(mu, nu, grp);
@@ -496,9 +502,9 @@ __device__ __forceinline__ void staple_sum_rows01_shared(const Geo &g, const Lin
                 M23<R> T;
                 mul_dag23_33(A, LB, T);
                 rebuild_row2(LC);
-                acc_23_33(Q, T, LC);
+                acc_23_33(S, T, LC);
             } else {
-                add_lower_staple(g, U, x, mu, nu, Q, back);
+                add_lower_staple(g, U, x, mu, nu, S, back);
             }
         }
         __syncthreads();  // this phase's products are in LDS
@@ -513,8 +519,9 @@ __device__ __forceinline__ void staple_sum_rows01_shared(const Geo &g, const Lin
             rebuild_row2(P);
             M23<R> A;  // rows 0 and 1 of U_nu(x)
             own_rows01(own, nu, A);
-            add_upper_staple(A, P, prod, Q);
-            add_23(S, Q);
+            M23<R> X;
+            upper_staple(A, P, prod, X);
+            add_23(S, X);
         }
     }
 }
@@ -895,8 +902,10 @@ __device__ __forceinline__ void ape_group_f64(const Geo &g, const LinksRO<double
 // theirs to wave 0 through LDS, which adds them in the order of the other
 // paths, so the bits are the same, and projects and stores the link.
 // part: split_parts R per lane and wave.  Contains a block barrier.
-// FP64: the upper and the lower staple, added one after the other; FP32: their sum.
-template <typename R> __host__ __device__ constexpr int split_parts() { return sizeof(R) == 8 ? 24 : 12; }
+// FP64: the upper and the lower staple, added one after the other; FP32: the
+// upper staple and the lower one's factors, which wave 0 accumulates onto the
+// sum as the other paths do.
+template <typename R> __host__ __device__ constexpr int split_parts() { return sizeof(R) == 8 ? 24 : 42; }
 
 // FP64: X = U_nu(x) U_mu(x+nu) U_nu(x+mu)^dag and Y = U_nu(y)^dag U_mu(y) U_nu(y+mu),
 // y = x - nu (rows 0 and 1), each product in the order of ape_group_f64.
@@ -938,10 +947,15 @@ __device__ __forceinline__ void ape_split(const Geo &g, const LinksRO<R, NR> &U,
     auto active = [&](int q) { return smear && ((mask >> (mu ^ (q + 1))) & 1u); };
     M23<R> u0;
     if (p == 0) U.rows01(mu, x.s, u0);
-    M23<R> q0, q1;  // FP32: the plane sum; FP64: the upper and the lower staple
+    M23<R> q0, q1;  // the upper staple; FP64: the lower one, FP32: its factors q1 q2
+    M3<R> q2;
     if (active(p)) {
-        if constexpr (sizeof(R) == 8) plane_staples_f64(g, U, x, mu, nu, q0, q1);
-        else plane_sum<R, NR, true>(g, U, x, mu, nu, grp, q0);
+        if constexpr (sizeof(R) == 8) {
+            plane_staples_f64(g, U, x, mu, nu, q0, q1);
+        } else {
+            lower_staple<R, NR, true>(g, U, x, mu, nu, q1, q2);
+            plane_upper<R, NR, true>(g, U, x, mu, nu, grp, q0);
+        }
     }
     if constexpr (MODE != kApe) {  // the plane's traces: spatial (0,1), (0,2), (1,2) and temporal (0,3), (1,3), (2,3)
         if (mu < nu) {             // in entries 0, 1, 2 of the group's four
@@ -957,17 +971,20 @@ __device__ __forceinline__ void ape_split(const Geo &g, const LinksRO<R, NR> &U,
             if (lane == 0) partials[4 * grp + 3] = partials[4 * num_groups(g) + 4 * grp + 3] = 0.0;
         }
     }
-    constexpr int kParts = sizeof(R) == 8 ? 2 : 1;
     if (p > 0 && active(p)) {
         R *mine = part + (p - 1) * split_parts<R>() * 64 + lane;
+        auto put = [&](int k, const Cx<R> &z) {
+            mine[(2 * k) * 64] = z.re;
+            mine[(2 * k + 1) * 64] = z.im;
+        };
 #pragma unroll
         for (int k = 0; k < 6; ++k) {
-            mine[(2 * k) * 64] = q0.e[k / 3][k % 3].re;
-            mine[(2 * k + 1) * 64] = q0.e[k / 3][k % 3].im;
-            if constexpr (kParts == 2) {
-                mine[(12 + 2 * k) * 64] = q1.e[k / 3][k % 3].re;
-                mine[(13 + 2 * k) * 64] = q1.e[k / 3][k % 3].im;
-            }
+            put(k, q0.e[k / 3][k % 3]);
+            put(6 + k, q1.e[k / 3][k % 3]);
+        }
+        if constexpr (sizeof(R) == 4) {
+#pragma unroll
+            for (int k = 0; k < 9; ++k) put(12 + k, q2.e[k / 3][k % 3]);
         }
     }
     __syncthreads();
@@ -980,22 +997,31 @@ __device__ __forceinline__ void ape_split(const Geo &g, const LinksRO<R, NR> &U,
     }
     M23<R> S;
     zero_23(S);
-    if (active(0)) {
-        add_23(S, q0);
-        if constexpr (kParts == 2) add_23(S, q1);
-    }
+    auto add = [&]() {
+        if constexpr (sizeof(R) == 8) {
+            add_23(S, q0);
+            add_23(S, q1);
+        } else {
+            acc_23_33(S, q1, q2);
+            add_23(S, q0);
+        }
+    };
+    if (active(0)) add();
 #pragma unroll
     for (int q = 1; q < 3; ++q) {
         if (!active(q)) continue;
         const R *theirs = part + (q - 1) * split_parts<R>() * 64 + lane;
+        auto get = [&](int k) { return Cx<R>{theirs[(2 * k) * 64], theirs[(2 * k + 1) * 64]}; };
 #pragma unroll
-        for (int h = 0; h < kParts; ++h) {
-            M23<R> v;
-#pragma unroll
-            for (int k = 0; k < 6; ++k)
-                v.e[k / 3][k % 3] = Cx<R>{theirs[(12 * h + 2 * k) * 64], theirs[(12 * h + 2 * k + 1) * 64]};
-            add_23(S, v);
+        for (int k = 0; k < 6; ++k) {
+            q0.e[k / 3][k % 3] = get(k);
+            q1.e[k / 3][k % 3] = get(6 + k);
         }
+        if constexpr (sizeof(R) == 4) {
+#pragma unroll
+            for (int k = 0; k < 9; ++k) q2.e[k / 3][k % 3] = get(12 + k);
+        }
+        add();
     }
     project_rows01<R, NR>(out, c1, c2, mu, x.s, S, u0);
 }
