@@ -85,7 +85,7 @@ k_ape_step(Geo g, LinksRO<R, NR> U, LinksWO<R, NR> out, double c1, double c2, un
 // three waves (ape_split).  Taken while all of its blocks run at once, two a
 // CU in FP64 (185 registers) and five in FP32 (120): from there on the other
 // kernels' sharing between directions is worth more than the shorter chain.
-// A step against theirs: 4^4 FP64 5.1 / 7.9 us, FP32-12 4.8 / 8.5; 8^3x16 6.9 /
+// A step against theirs: 4^4 FP64 5.4 / 7.9 us, FP32-12 4.8 / 8.5; 8^3x16 7.6 /
 // 9.2 and 5.8 / 8.8; 8^2x16^2 (256 groups) FP64 10.6 / 10.1, FP32-12 7.5 / 9.2;
 // 8^2x16x20 (320) FP32-12 8.3; 16^4 (1024) FP64 31.4 / 26.6.
 constexpr int kSplitGroups64 = 128, kSplitGroups32 = 320;
@@ -93,7 +93,7 @@ constexpr int kSplitGroups64 = 128, kSplitGroups32 = 320;
 template <typename R, int NR, int MODE>
 __global__ void __launch_bounds__(192) k_ape_split(Geo g, LinksRO<R, NR> U, LinksWO<R, NR> out, double c1, double c2,
                                                    unsigned mask, double *__restrict__ partials) {
-    __shared__ R part[2 * split_parts<R>() * 64];
+    __shared__ R part[2 * kSplitParts * 64];
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int b = xcd_tile(blockIdx.x, gridDim.x);
     ape_split<R, NR, MODE>(g, U, out, c1, c2, mask, partials, b >> 2, b & 3, w, (int)(threadIdx.x & 63), part);

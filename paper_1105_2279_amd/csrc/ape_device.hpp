@@ -812,7 +812,7 @@ __device__ __forceinline__ void ape_group_f64(const Geo &g, const LinksRO<double
             // lower: U_nu(y)^dag U_mu(y) U_nu(y+mu) by rows k:
             // T_ij = sum_k conj(LA_ki) LB_kj with LA = U_nu(x-nu), the
             // partner's backward link (columns 0 and 1 from LDS), then
-            // S_ij += (sum_k T_ik LC_kj), formed on its own as the upper one
+            // S_ij += sum_k T_ik LC_kj
             rebuild_row2(LB);
 #pragma unroll
             for (int i = 0; i < 2; ++i)
@@ -838,15 +838,11 @@ __device__ __forceinline__ void ape_group_f64(const Geo &g, const LinksRO<double
         if (act) {
             rebuild_row2(LC);
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
+            for (int k = 0; k < 3; ++k)
 #pragma unroll
-                for (int j = 0; j < 3; ++j) {
-                    Cx<double> y{0.0, 0.0};
+                for (int i = 0; i < 2; ++i)
 #pragma unroll
-                    for (int k = 0; k < 3; ++k) cmac(y, T[i][k], LC.e[k][j]);
-                    S[i][j].re += y.re;
-                    S[i][j].im += y.im;
-                }
+                    for (int j = 0; j < 3; ++j) cmac(S[i][j], T[i][k], LC.e[k][j]);
         }
     }
     {
@@ -901,19 +897,21 @@ __device__ __forceinline__ void ape_group_f64(const Geo &g, const LinksRO<double
 // nu = mu ^ (p + 1), all its loads in flight at once; waves 1 and 2 pass
 // theirs to wave 0 through LDS, which adds them in the order of the other
 // paths, so the bits are the same, and projects and stores the link.
-// part: split_parts R per lane and wave.  Contains a block barrier.
-// FP64: the upper and the lower staple, added one after the other; FP32: the
-// upper staple and the lower one's factors, which wave 0 accumulates onto the
-// sum as the other paths do.
-template <typename R> __host__ __device__ constexpr int split_parts() { return sizeof(R) == 8 ? 24 : 42; }
+// part: kSplitParts R per lane and wave.  Contains a block barrier.
+// A part is the upper staple and the lower one's two factors, which wave 0
+// accumulates onto the sum as the other paths do (FP64: the upper staple
+// first, FP32: the lower one).
+constexpr int kSplitParts = 42;
 
-// FP64: X = U_nu(x) U_mu(x+nu) U_nu(x+mu)^dag and Y = U_nu(y)^dag U_mu(y) U_nu(y+mu),
-// y = x - nu (rows 0 and 1), each product in the order of ape_group_f64.
+// FP64: X = U_nu(x) U_mu(x+nu) U_nu(x+mu)^dag and the factors of T LC =
+// U_nu(y)^dag U_mu(y) U_nu(y+mu), y = x - nu (rows 0 and 1), each product in the
+// order of ape_group_f64.
 __device__ __forceinline__ void plane_staples_f64(const Geo &g, const LinksRO<double, 3> &U, const Site &x, int mu,
-                                                  int nu, M23<double> &X, M23<double> &Y) {
+                                                  int nu, M23<double> &X, M23<double> &T,
+                                                  M3<double> &LC) {
     const int y = hop_bwd<true>(g, x.s, coord(x, nu), nu);
-    M3<double> B, C, LA, LB, LC;
-    M23<double> A, T;
+    M3<double> B, C, LA, LB;
+    M23<double> A;
     U.rows01(nu, x.s, A);
     U.load_rows<false, 2>(mu, hop_fwd<true>(g, x.s, coord(x, nu), nu), B.e);
     U.load_rows<false, 2>(nu, hop_fwd<true>(g, x.s, coord(x, mu), mu), C.e);
@@ -929,8 +927,6 @@ __device__ __forceinline__ void plane_staples_f64(const Geo &g, const LinksRO<do
     rebuild_row2(LB);
     mul_dag23_33(LA, LB, T);
     rebuild_row2(LC);
-    zero_23(Y);
-    acc_23_33(Y, T, LC);
 }
 
 template <typename R, int NR, int MODE>
@@ -947,11 +943,11 @@ __device__ __forceinline__ void ape_split(const Geo &g, const LinksRO<R, NR> &U,
     auto active = [&](int q) { return smear && ((mask >> (mu ^ (q + 1))) & 1u); };
     M23<R> u0;
     if (p == 0) U.rows01(mu, x.s, u0);
-    M23<R> q0, q1;  // the upper staple; FP64: the lower one, FP32: its factors q1 q2
+    M23<R> q0, q1;  // the upper staple; the lower one's factors q1 q2
     M3<R> q2;
     if (active(p)) {
         if constexpr (sizeof(R) == 8) {
-            plane_staples_f64(g, U, x, mu, nu, q0, q1);
+            plane_staples_f64(g, U, x, mu, nu, q0, q1, q2);
         } else {
             lower_staple<R, NR, true>(g, U, x, mu, nu, q1, q2);
             plane_upper<R, NR, true>(g, U, x, mu, nu, grp, q0);
@@ -972,7 +968,7 @@ __device__ __forceinline__ void ape_split(const Geo &g, const LinksRO<R, NR> &U,
         }
     }
     if (p > 0 && active(p)) {
-        R *mine = part + (p - 1) * split_parts<R>() * 64 + lane;
+        R *mine = part + (p - 1) * kSplitParts * 64 + lane;
         auto put = [&](int k, const Cx<R> &z) {
             mine[(2 * k) * 64] = z.re;
             mine[(2 * k + 1) * 64] = z.im;
@@ -982,10 +978,8 @@ __device__ __forceinline__ void ape_split(const Geo &g, const LinksRO<R, NR> &U,
             put(k, q0.e[k / 3][k % 3]);
             put(6 + k, q1.e[k / 3][k % 3]);
         }
-        if constexpr (sizeof(R) == 4) {
 #pragma unroll
-            for (int k = 0; k < 9; ++k) put(12 + k, q2.e[k / 3][k % 3]);
-        }
+        for (int k = 0; k < 9; ++k) put(12 + k, q2.e[k / 3][k % 3]);
     }
     __syncthreads();
     if (p > 0 || !live) return;
@@ -1000,7 +994,7 @@ __device__ __forceinline__ void ape_split(const Geo &g, const LinksRO<R, NR> &U,
     auto add = [&]() {
         if constexpr (sizeof(R) == 8) {
             add_23(S, q0);
-            add_23(S, q1);
+            acc_23_33(S, q1, q2);
         } else {
             acc_23_33(S, q1, q2);
             add_23(S, q0);
@@ -1010,17 +1004,15 @@ __device__ __forceinline__ void ape_split(const Geo &g, const LinksRO<R, NR> &U,
 #pragma unroll
     for (int q = 1; q < 3; ++q) {
         if (!active(q)) continue;
-        const R *theirs = part + (q - 1) * split_parts<R>() * 64 + lane;
+        const R *theirs = part + (q - 1) * kSplitParts * 64 + lane;
         auto get = [&](int k) { return Cx<R>{theirs[(2 * k) * 64], theirs[(2 * k + 1) * 64]}; };
 #pragma unroll
         for (int k = 0; k < 6; ++k) {
             q0.e[k / 3][k % 3] = get(k);
             q1.e[k / 3][k % 3] = get(6 + k);
         }
-        if constexpr (sizeof(R) == 4) {
 #pragma unroll
-            for (int k = 0; k < 9; ++k) q2.e[k / 3][k % 3] = get(12 + k);
-        }
+        for (int k = 0; k < 9; ++k) q2.e[k / 3][k % 3] = get(12 + k);
         add();
     }
     project_rows01<R, NR>(out, c1, c2, mu, x.s, S, u0);
