@@ -372,7 +372,15 @@ static LaunchCfg cfg_for(qdpx_ctx *ctx, qdpx_op op, const qdpx_geom *geom, qdpx_
     if (op == QDPX_OP_APE || op == QDPX_OP_SHIFT || op == QDPX_OP_CHAIN || op == QDPX_OP_JACOBI) {
         Geo g = make_geo(geom->L);
         const int bytes = reread_bytes(op, prec, fmt);
-        if ((int64_t)g.V / kXcds * bytes > kXcdL2 && tile_plan(g, bytes, fwd_only(op), groups_per_block(op, c))) c.xcd = 2;
+        // Tiles where an XCD's share no longer fits its L2.  Smearing steps, shift
+        // and chain: from 6 MB on, as contiguous ranges lose little to 4 MB and
+        // balance better on so few groups (us, ranges / tiles: FP32-18 step 16^3x32,
+        // 4.5 MB, 32.7 / 35.4; FP64 6 MB 47.8 / 48.9; 20^3x40 11 MB 77.4 / 76.2; FP64
+        // chain 16x20^2x36, 5.3 MB, 47.3 / 49.7).  The Jacobi hop, to both sides in
+        // every direction: from 4 MB (FP64 12x24x16x28, 5.9 MB, 27.7 / 24.2).
+        const int64_t room = op == QDPX_OP_JACOBI ? kXcdL2 : kXcdL2 * 3 / 2;
+        const bool far = (int64_t)g.V / kXcds * bytes > room;
+        if (far && tile_plan(g, bytes, fwd_only(op), groups_per_block(op, c))) c.xcd = 2;
     }
     return c;
 }
