@@ -393,8 +393,10 @@ int qdpx_ape_smear_batched(qdpx_ctx *ctx, int n_lat, const qdpx_geom *geoms, qdp
  *   array of n_fields device pointers; scalars: host array of n_scalars
  *   doubles (passed in the field precision).  out must not overlap U or any
  *   field.  norm2 (nullable, device double) receives |out|^2 in FP64 (fixed
- *   order; then work >= qdpx_workspace_bytes(QDPX_OP_SHIFT, ...)).  One site
- *   per thread, 256 threads per block; enqueues only, so it can be captured. */
+ *   order; then work >= qdpx_workspace_bytes(QDPX_OP_SHIFT, ...)).  256 threads
+ *   per block, one site per lane; where the expression has one sum with only
+ *   componentwise terms around it, two or four waves share 64 sites, a direction
+ *   of the sum each.  Enqueues only, so it can be captured. */
 int qdpx_jit_generate(const char *expr, qdpx_prec prec, qdpx_linkfmt fmt, int32_t n_fields, int32_t n_scalars,
                       char *buf, size_t buf_bytes, size_t *needed);
 int qdpx_jit_compile(qdpx_ctx *ctx, const char *expr, qdpx_prec prec, qdpx_linkfmt fmt, int32_t n_fields,

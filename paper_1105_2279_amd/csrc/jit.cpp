@@ -10,13 +10,12 @@
 //   (sum MASK E)        sum over the directions in MASK (hex) of E, the
 //                       direction variable m standing for each in turn
 //
-// The generator writes one HIP kernel per expression (one site per lane, the
-// 64-site groups taken in the block order of the hand-written kernels; each
+// The generator writes one HIP kernel per expression (one site per lane; each
 // node becomes straight-line code on a 12-component spinor, a shift moves the
 // site index and coordinates; the directions of an expression's sum go to the
-// four waves of a group where that can be, else a sum becomes a loop over
-// them), compiles it with
-// hipRTC for the device's architecture with packed FP32 disabled, and keeps
+// waves of a group where that can be, else a sum becomes a loop over them; the
+// 64-site groups in the block order of the hand-written kernels where an array
+// is read at several sites), compiles it with hipRTC for the device's architecture with packed FP32 disabled, and keeps
 // the code object in an on-disk cache keyed by a hash of the source and
 // options, so a later process loads it without compiling (the paper's
 // kernel cache, made persistent).  The |out|^2 reduction, when asked for,
@@ -24,6 +23,7 @@
 #include <hip/hip_runtime.h>
 #include <hip/hiprtc.h>
 
+#include <array>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -207,6 +207,7 @@ struct Gen {
     // The part of a split expression outside its sum, in each wave for the
     // components it owns: first the loads of its (shifted) fields, then, once
     // the partial sums have met in LDS, the arithmetic.
+    unsigned wave_mask = 0;  // the waves of a group that hold a direction
     std::map<const Node *, std::string> owned;
     void emit_loads(const Node &n, const std::string &s, const std::string c[4]) {
         if (n.kind == Node::Sum) return;
@@ -229,7 +230,7 @@ struct Gen {
         if (owned.count(&n)) return owned[&n];
         const std::string v = fresh("v");
         if (n.kind == Node::Sum) {
-            body << "    own " << v << "; gather(part, " << n.mask << "u, w, lane, " << v << ");\n";
+            body << "    own " << v << "; gather(part + first, " << wave_mask << "u, w, lane, " << v << ");\n";
         } else if (n.kind == Node::Scale) {
             const std::string a = emit_owned(*n.kids[0]);
             body << "    own " << v << "; oscale(scal" << n.idx << ", " << a << ", " << v << ");\n";
@@ -307,6 +308,12 @@ struct spinor { cx c[4][3]; };
 struct link { cx e[3][3]; };
 // The launch's block order and site decoding (JitGeo on the host); a division
 // by d is (mulhi(m, n) + n) >> l for 0 <= n < 2^31.
+// Block order of a kernel without one of those (FlatGeo on the host): tile
+// x q + min(x, r) + (blk >> shift), x = blk & mask.
+struct flatgeo {
+    long long S;
+    int mask, shift, q, r;
+};
 struct divisor { unsigned d, m, l; };
 struct jitgeo {
     long long S;
@@ -467,29 +474,29 @@ __device__ __forceinline__ void sscale(real k, const spinor &a, spinor &r) {
         for (int i = 0; i < 3; ++i) r.c[sp][i] = cx{k * a.c[sp][i].re, k * a.c[sp][i].im};
 }
 #if SPLIT
-// The components a wave of a split kernel finishes and stores: double, spin
-// w; float, the whole pairs k = w and, for w < 2, k = w + 4 (slot t is
-// component 2k + (t & 1) of pair k = w + 4 (t >> 1)).
+// The components that wave w of a group of SPLIT waves finishes and stores:
+// double, NOWN consecutive ones; float, the whole pairs k = w + SPLIT h below 6
+// (slot t is component 2k + (t & 1) of pair h = t >> 1).
 #if PAIRED
-#define NOWN 4
+#define NOWN (2 * ((5 + SPLIT) / SPLIT))
 #else
-#define NOWN 3
+#define NOWN (12 / SPLIT)
 #endif
 struct own { cx c[NOWN]; };
 __device__ __forceinline__ int component(int w, int t) {
 #if PAIRED
-    const int k = w + 4 * (t >> 1);
+    const int k = w + SPLIT * (t >> 1);
     return k < 6 ? 2 * k + (t & 1) : -1;
 #else
-    return 3 * w + t;
+    return NOWN * w + t;
 #endif
 }
 __device__ __forceinline__ void ldown(const real2 *__restrict__ f, long long S, int s, int w, own &r) {
 #if PAIRED
     const real4 *P = (const real4 *)f;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int k = w + 4 * h;
+    for (int h = 0; h < NOWN / 2; ++h) {
+        const int k = w + SPLIT * h;
         real4 v = {0, 0, 0, 0};
         if (k < 6) v = P[(long long)k * S + s];
         r.c[2 * h] = cx{v.x, v.y};
@@ -497,36 +504,37 @@ __device__ __forceinline__ void ldown(const real2 *__restrict__ f, long long S, 
     }
 #else
 #pragma unroll
-    for (int t = 0; t < 3; ++t) r.c[t] = ldc(f, S, 3 * w + t, s);
+    for (int t = 0; t < NOWN; ++t) r.c[t] = ldc(f, S, NOWN * w + t, s);
 #endif
 }
 __device__ __forceinline__ void stown(real2 *__restrict__ f, long long S, int s, int w, const own &r) {
 #if PAIRED
     real4 *P = (real4 *)f;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int k = w + 4 * h;
+    for (int h = 0; h < NOWN / 2; ++h) {
+        const int k = w + SPLIT * h;
         const cx a = r.c[2 * h], b = r.c[2 * h + 1];
         const real4 v = {a.re, a.im, b.re, b.im};
         if (k < 6) __builtin_nontemporal_store(v, P + ((long long)k * S + s));
     }
 #else
 #pragma unroll
-    for (int t = 0; t < 3; ++t) {
+    for (int t = 0; t < NOWN; ++t) {
         const real2 v = {r.c[t].re, r.c[t].im};
-        __builtin_nontemporal_store(v, f + ((long long)(3 * w + t) * S + s));
+        __builtin_nontemporal_store(v, f + ((long long)(NOWN * w + t) * S + s));
     }
 #endif
 }
-// the directions' partial sums, in order
-__device__ __forceinline__ void gather(const real2 (&part)[4][12][64], unsigned mask, int w, int lane, own &r) {
+// the directions' partial sums, in order: the group's waves in mask, part those
+// of its first wave
+__device__ __forceinline__ void gather(const real2 (*part)[12][64], unsigned mask, int w, int lane, own &r) {
 #pragma unroll
     for (int t = 0; t < NOWN; ++t) {
         cx z{(real)0, (real)0};
         const int q = component(w, t);
         if (q >= 0)
 #pragma unroll
-            for (int d = 0; d < 4; ++d)
+            for (int d = 0; d < SPLIT; ++d)
                 if ((mask >> d) & 1u) {
                     const real2 e = part[d][q][lane];
                     z.re += e.x;
@@ -550,7 +558,7 @@ __device__ __forceinline__ void oscale(real k, const own &a, own &r) {
 #endif
 )HIP";
 
-// The sum whose directions go to the four waves of a 64-site group: the
+// The sum whose directions go to the waves of a 64-site group: the
 // expression's only one, of two directions or more, with nothing but sums,
 // differences, scalings and (shifted) fields around it (all componentwise, so
 // that each wave can finish its share of the components).  Null: none.
@@ -580,8 +588,48 @@ const Node *split_sum(const Node &n) {
     }
 }
 
-// 64-site groups a block of 256 threads takes.
-int groups_per_block(const Node &root) { return split_sum(root) ? 1 : 4; }
+// Whether an array (a field, or the links of a direction) is read at several
+// sites by the lane of one site, so that neighbouring lanes read it again.  seen:
+// where each array is read first, as the steps of the shift from the site.
+bool rereads(const Node &n, int m, std::array<int, 4> at, std::map<int, std::array<int, 4>> &seen) {
+    auto again = [&](int array) { return !seen.emplace(array, at).second && seen[array] != at; };
+    const int dir = n.dir < 0 ? m : n.dir;
+    switch (n.kind) {
+    case Node::Field: return again(4 + n.idx);
+    case Node::Umul:
+    case Node::Uadj:
+        if (again(dir)) return true;
+        break;
+    case Node::Shift: at[dir] += n.sign; break;
+    case Node::Sum:
+        for (int d = 0; d < 4; ++d)
+            if (((n.mask >> d) & 1u) && rereads(*n.kids[0], d, at, seen)) return true;
+        return false;
+    default: break;
+    }
+    for (const auto &k : n.kids)
+        if (rereads(*k, m, at, seen)) return true;
+    return false;
+}
+
+// The form of an expression's kernel.
+struct Form {
+    const Node *sum = nullptr;  // its directions go to the waves of a group
+    int split = 0;              // waves a group then
+    bool flat = false;          // no array read at several sites: blocks in plain order
+    int groups() const { return split ? 4 / split : 4; }  // 64-site groups a block of 256 threads takes
+};
+Form form_of(const Node &root) {
+    Form f;
+    f.sum = split_sum(root);
+    if (f.sum) {
+        f.split = 4;
+    } else {
+        std::map<int, std::array<int, 4>> seen;
+        f.flat = !rereads(root, 0, {0, 0, 0, 0}, seen);
+    }
+    return f;
+}
 
 // A kernel with a split sum has the hand-written hop's shape: wave w computes
 // direction w, so that four directions' loads are in flight at once and not
@@ -589,15 +637,22 @@ int groups_per_block(const Node &root) { return split_sum(root) ? 1 : 4; }
 // finishes the components it owns.  The smearing update with its norm, one
 // site per lane and the directions in a loop of two at a time, against split:
 // 205 / 158 us at 24^3x48 in FP64, 520 / 466 us at 32^3x64, 277 / 241 us there
-// in FP32-12, 58 / 43 us at 14x18x22x30 in FP64.
-std::string generate(const Node &root, int prec, int nrows, int n_fields, int n_scalars) {
+// in FP32-12, 58 / 43 us at 14x18x22x30 in FP64. 
+//
+// An expression that reads every array at one site only (a single hop, an
+// axpy) finds nothing in a cache whatever the block order, and what a wave
+// does before its first load counts most there.  Its kernel is flat: without
+// the geometry of the block orders, whose fields took a hop in t from 10.4 to
+// 11.2 us at 16^3x32 and from 155 to 159 us at 30^3x62 (FP64), from 11.8 to 12.3
+// us at 20^3x40 (FP32-12).
+std::string generate(const Node &root, const Form &form, int prec, int nrows, int n_fields, int n_scalars) {
     std::ostringstream src;
-    const Node *sum = split_sum(root);
+    const Node *sum = form.sum;
     const std::string real = prec == QDPX_F64 ? "double" : "float";
     src << "#define REAL " << real << "\n#define NROWS " << nrows << "\n#define PAIRED " << (prec == QDPX_F32 ? 1 : 0)
-        << "\n#define SPLIT " << (sum ? 1 : 0) << "\n" << kPrelude;
+        << "\n#define SPLIT " << form.split << "\n" << kPrelude;
     src << "extern \"C\" __global__ void __launch_bounds__(256) qdpx_jit_kernel(int L0, int L1, int L2, int L3, "
-           "jitgeo geo, const real2 *__restrict__ U";
+        << (form.flat ? "flatgeo" : "jitgeo") << " geo, const real2 *__restrict__ U";
     for (int i = 0; i < n_fields; ++i) src << ", const real2 *__restrict__ f" << i;
     src << ", real2 *__restrict__ out";
     // scalar K is the parameter scalK: generated locals are named by fresh()
@@ -607,54 +662,89 @@ std::string generate(const Node &root, int prec, int nrows, int n_fields, int n_
     src << "    const int st0 = 1, st1 = L0, st2 = L0 * L1, st3 = L0 * L1 * L2;\n"
            "    (void)st0; (void)st1; (void)st2; (void)st3; (void)L3;\n"
            "    const long long S = geo.S;\n"
-           "    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));\n";
-    src << (sum ? "    __shared__ real2 part[4][12][64];\n    __shared__ double nrm[4][64];\n"
-                  "    const int grp = group_of(geo, (int)blockIdx.x, (int)gridDim.x, 0, 1);\n"
-                : "    const int grp = group_of(geo, (int)blockIdx.x, (int)gridDim.x, w, 4);\n");
-    src << "    if (grp < 0) return;\n"
-           "    const int last = L0 * L1 * L2 * L3 - 1;\n"
-           "    const int at = grp * 64 + lane, site = min(at, last);\n"  // padding lanes load from the last site
-           "    const int q0 = quot(geo.L0, site), q1 = quot(geo.L1, q0), x3 = quot(geo.L2, q1);\n"
-           "    const int x0 = site - q0 * L0, x1 = q0 - q1 * L1, x2 = q1 - x3 * L2;\n"
+           "    const int blk = (int)blockIdx.x, lane = threadIdx.x & 63;\n"
            "    double n2 = 0.0;\n";
+    const std::string n2_of =
+        "        n2 = fma((double)z.re, (double)z.re, fma((double)z.im, (double)z.im, n2));\n";
+    const std::string butterfly = "#pragma unroll\n"
+                                  "        for (int off = 32; off >= 1; off >>= 1) n2 += __shfl_xor(n2, off, 64);\n";
     Gen g;
     const std::string c[4] = {"x0", "x1", "x2", "x3"};
+    // the result of a kernel with one site per lane, and its part of the norm
+    auto store_site = [&](const std::string &res) {
+        return "    stspinor(out, S, site, " + res +
+               ");\n#pragma unroll\n    for (int sp = 0; sp < 4; ++sp)\n#pragma unroll\n"
+               "        for (int a = 0; a < 3; ++a) {\n        const cx z = " +
+               res + ".c[sp][a];\n" + n2_of + "        }\n";
+    };
+    if (form.flat) {
+        src << "    const int x = blk & geo.mask, tile = x * geo.q + min(x, geo.r) + (blk >> geo.shift);\n"
+               "    const int V = L0 * L1 * L2 * L3, site = tile * 256 + (int)threadIdx.x;\n"
+               "    if (site < V) {\n"
+               "    int r = site;\n"
+               "    const int x0 = r % L0; r /= L0;\n"
+               "    const int x1 = r % L1; r /= L1;\n"
+               "    const int x2 = r % L2, x3 = r / L2;\n";
+        const std::string res = g.emit(root, "site", c);
+        src << g.body.str() << store_site(res)
+            << "    }\n"
+               // a wave whose first site is past the end has no partial
+               "    if (partials) {  // |out|^2 of each group, a fixed butterfly\n"
+            << butterfly << "        if (lane == 0 && site < V) partials[site >> 6] = n2;\n    }\n}\n";
+        return src.str();
+    }
+    // Every argument that the way to the first load needs, asked for at once:
+    // the compiler loads arguments where they are used, one branch after
+    // another, each a trip to memory for the first waves of a launch.
+    src << "    const int nblk = (int)gridDim.x;\n"
+           "    asm volatile(\"\" ::\"s\"(L0), \"s\"(L1), \"s\"(L2), \"s\"(L3), \"s\"(S), \"s\"(geo.order), "
+           "\"s\"(geo.ngroups), \"s\"(nblk));\n"
+           "    asm volatile(\"\" ::\"s\"(geo.L0.m), \"s\"(geo.L0.l), \"s\"(geo.L1.m), \"s\"(geo.L1.l), "
+           "\"s\"(geo.L2.m), \"s\"(geo.L2.l));\n"
+           "    asm volatile(\"\" ::\"s\"(U), \"s\"(out), \"s\"(partials)";
+    for (int i = 0; i < n_fields; ++i) src << ", \"s\"(f" << i << ")";
+    src << ");\n";
+    const int split = form.split ? form.split : 1;  // waves a group
+    src << "    const int bw = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), w = bw & " << split - 1
+        << ", first = bw - w;\n    (void)first;\n"
+        << (sum ? "    __shared__ real2 part[4][12][64];\n    __shared__ double nrm[4][64];\n" : "")
+        << "    const int grp = group_of(geo, blk, nblk, bw / " << split << ", " << form.groups() << ");\n"
+        // a block of one group ends together, and so may a wave that meets no barrier
+        << (split == 2 ? "" : "    if (grp < 0) return;\n")
+        << "    const int last = L0 * L1 * L2 * L3 - 1;\n"
+        << (split == 2 ? "    const int at = grp < 0 ? last + 1 : grp * 64 + lane;\n" : "    const int at = grp * 64 + lane;\n")
+        << "    const int site = min(at, last);\n"  // padding lanes load from the last site
+           "    const int q0 = quot(geo.L0, site), q1 = quot(geo.L1, q0), x3 = quot(geo.L2, q1);\n"
+           "    const int x0 = site - q0 * L0, x1 = q0 - q1 * L1, x2 = q1 - x3 * L2;\n";
     if (sum) {
+        g.wave_mask = split == 2 ? 3u : sum->mask;
         g.emit_loads(root, "site", c);
-        g.body << "    spinor acc; szero(acc);\n    if ((" << sum->mask << "u >> w) & 1u) {\n    const int m = w;\n";
+        g.body << "    spinor acc; szero(acc);\n    if ((" << g.wave_mask << "u >> w) & 1u) {\n    const int m = ";
+        if (split == 2) g.body << "w ? " << 31 - __builtin_clz(sum->mask) << " : " << __builtin_ctz(sum->mask) << ";\n";
+        else g.body << "w;\n";
         const std::string a = g.emit(*sum->kids[0], "site", c);
         g.body << "    acc = " << a
                << ";\n    }\n"
                   "#pragma unroll\n    for (int q = 0; q < 12; ++q) "
-                  "part[w][q][lane] = real2{acc.c[q / 3][q % 3].re, acc.c[q / 3][q % 3].im};\n"
+                  "part[bw][q][lane] = real2{acc.c[q / 3][q % 3].re, acc.c[q / 3][q % 3].im};\n"
                   "    __syncthreads();\n";
         const std::string res = g.emit_owned(root);
         src << g.body.str() << "    if (at <= last) {\n    stown(out, S, site, w, " << res
             << ");\n#pragma unroll\n    for (int t = 0; t < NOWN; ++t) {\n        if (component(w, t) < 0) continue;\n"
                "        const cx z = "
-            << res
-            << ".c[t];\n"
-               "        n2 = fma((double)z.re, (double)z.re, fma((double)z.im, (double)z.im, n2));\n    }\n    }\n"
+            << res << ".c[t];\n" << n2_of << "    }\n    }\n"
                "    if (partials) {  // |out|^2 of the group: the waves' shares in order, a fixed butterfly\n"
-               "        nrm[w][lane] = n2;\n"
+               "        nrm[bw][lane] = n2;\n"
                "        __syncthreads();\n"
-               "        n2 = ((nrm[0][lane] + nrm[1][lane]) + nrm[2][lane]) + nrm[3][lane];\n";
+               "        n2 = nrm[first][lane];\n"
+               "        for (int k = 1; k < SPLIT; ++k) n2 += nrm[first + k][lane];\n"
+            << butterfly << "        if (w == 0 && lane == 0 && grp >= 0) partials[grp] = n2;\n    }\n}\n";
     } else {
         const std::string res = g.emit(root, "site", c);
-        src << g.body.str() << "    if (at <= last) {\n    stspinor(out, S, site, " << res
-            << ");\n#pragma unroll\n    for (int sp = 0; sp < 4; ++sp)\n#pragma unroll\n"
-               "        for (int a = 0; a < 3; ++a) {\n"
-               "            const cx z = "
-            << res
-            << ".c[sp][a];\n"
-               "            n2 = fma((double)z.re, (double)z.re, fma((double)z.im, (double)z.im, n2));\n"
-               "        }\n    }\n"
-               "    if (partials) {  // |out|^2 of each group, a fixed butterfly\n";
+        src << g.body.str() << "    if (at <= last) {\n" << store_site(res)
+            << "    }\n    if (partials) {  // |out|^2 of each group, a fixed butterfly\n"
+            << butterfly << "        if (lane == 0) partials[grp] = n2;\n    }\n}\n";
     }
-    src << "#pragma unroll\n"
-           "        for (int off = 32; off >= 1; off >>= 1) n2 += __shfl_xor(n2, off, 64);\n"
-        << (sum ? "        if (threadIdx.x == 0) partials[grp] = n2;\n" : "        if (lane == 0) partials[grp] = n2;\n")
-        << "    }\n}\n";
     return src.str();
 }
 
@@ -754,7 +844,11 @@ void write_entry_atomic(const std::string &p, const std::string &key, const std:
     else std::remove(tmp.c_str());
 }
 
-// The kernels' `jitgeo` argument.
+// The kernels' `flatgeo` and `jitgeo` arguments.
+struct FlatGeo {
+    long long S;
+    int mask, shift, q, r;
+};
 struct JitGeo {
     long long S;
     int ngroups, order, ncol, pz, nz, wp, wz, wseg, tlen;
@@ -765,12 +859,28 @@ JitGeo jit_geo(const Geo &g, int order) {
                   g.L[3] >> g.wseg, g.dL0, g.dL1,  g.dL2, g.dunit, g.dwc, g.dwp, g.dnyt, g.dtiles};
 }
 
+// Block order of a flat kernel, by precision and the bytes of its fields: each
+// XCD one contiguous range of blocks, or, for FP64 fields beyond the 256 MB
+// cache, the order of dispatch, in which the XCDs stream through memory side
+// by side.  Us, ranges / dispatch: a hop in t of 16^3x32 (75 MB) 10.7 / 10.9 and
+// of 20^3x40 (184 MB) 22.9 / 23.3; an axpy of 24^3x48 (382 MB) 79.1 / 76.4 and of
+// 30^3x62 (964 MB) 190 / 184, a hop there 159 / 156.  Power-of-two extents differ
+// (32^3x64, 1.2 GB: a hop 195 / 204).  FP32 has too little to gain (24^3x48 23.9 /
+// 24.1, 32^3x64 97 / 100, 30^3x62 80 / 75).
+constexpr size_t kFlatCache = (size_t)256 << 20;
+FlatGeo flat_geo(const Geo &g, int prec, size_t bytes) {
+    const int nblk = (g.V + 255) / 256;
+    if (prec == QDPX_F64 && bytes > kFlatCache) return FlatGeo{(long long)g.S, 0, 0, 0, 0};
+    return FlatGeo{(long long)g.S, kXcds - 1, 3, nblk / kXcds, nblk % kXcds};
+}
+
 struct JitKernel {
     std::string source;
     hipModule_t module = nullptr;
     hipFunction_t fn = nullptr;
     int prec = 0, nrows = 3, n_fields = 0, n_scalars = 0;
-    int groups = 4;  // 64-site groups per block
+    int groups = 4;     // 64-site groups per block
+    bool flat = false;  // takes FlatGeo
     bool from_cache = false;
 };
 
@@ -781,7 +891,7 @@ const char *kOptions[] = {"-O3", "-std=c++17", "-Xclang", "-target-feature", "-X
 constexpr int kNumOptions = sizeof(kOptions) / sizeof(kOptions[0]);
 
 int parse_and_generate(const char *expr, qdpx_prec prec, qdpx_linkfmt fmt, int n_fields, int n_scalars,
-                       std::string &source, int &groups, const char *fn) {
+                       JitKernel &k, const char *fn) {
     char msg[512];
     if (!expr) return set_error(QDPX_EINVAL, (std::string(fn) + ": expression is NULL").c_str());
     if ((prec != QDPX_F64 && prec != QDPX_F32) || (fmt != QDPX_LINK18 && fmt != QDPX_LINK12) ||
@@ -800,8 +910,10 @@ int parse_and_generate(const char *expr, qdpx_prec prec, qdpx_linkfmt fmt, int n
         std::snprintf(msg, sizeof msg, "%s: %s", fn, p.err.c_str());
         return set_error(QDPX_EINVAL, msg);
     }
-    source = generate(*root, prec, fmt == QDPX_LINK12 ? 2 : 3, n_fields, n_scalars);
-    groups = groups_per_block(*root);
+    const Form form = form_of(*root);
+    k.source = generate(*root, form, prec, fmt == QDPX_LINK12 ? 2 : 3, n_fields, n_scalars);
+    k.groups = form.groups();
+    k.flat = form.flat;
     return QDPX_OK;
 }
 
@@ -820,9 +932,9 @@ void jit_release(const qdpx_ctx *ctx) {
 
 extern "C" int qdpx_jit_generate(const char *expr, qdpx_prec prec, qdpx_linkfmt fmt, int32_t n_fields,
                                  int32_t n_scalars, char *buf, size_t buf_bytes, size_t *needed) {
-    std::string src;
-    int groups = 0;
-    if (int r = parse_and_generate(expr, prec, fmt, n_fields, n_scalars, src, groups, "qdpx_jit_generate")) return r;
+    JitKernel k;
+    if (int r = parse_and_generate(expr, prec, fmt, n_fields, n_scalars, k, "qdpx_jit_generate")) return r;
+    const std::string &src = k.source;
     if (needed) *needed = src.size() + 1;
     if (buf && buf_bytes) {
         const size_t n = std::min(buf_bytes - 1, src.size());
@@ -839,7 +951,7 @@ extern "C" int qdpx_jit_compile(qdpx_ctx *ctx, const char *expr, qdpx_prec prec,
     if (!ctx || !kernel) return set_error(QDPX_EINVAL, "qdpx_jit_compile: ctx or kernel is NULL");
     if (int r = device_ok(ctx, fn)) return r;
     JitKernel k;
-    if (int r = parse_and_generate(expr, prec, fmt, n_fields, n_scalars, k.source, k.groups, fn)) return r;
+    if (int r = parse_and_generate(expr, prec, fmt, n_fields, n_scalars, k, fn)) return r;
     k.prec = prec;
     k.nrows = (fmt == QDPX_LINK12) ? 2 : 3;
     k.n_fields = n_fields;
@@ -947,6 +1059,7 @@ extern "C" int qdpx_jit_eval(qdpx_ctx *ctx, int32_t kernel, const qdpx_geom *geo
         k.n_fields = src.n_fields;
         k.n_scalars = src.n_scalars;
         k.groups = src.groups;
+        k.flat = src.flat;
     }
     if (!U || !out || !fields) return set_error(QDPX_EINVAL, "qdpx_jit_eval: NULL pointer");
     if ((uintptr_t)U & 15u) return set_error(QDPX_EINVAL, "qdpx_jit_eval: link field not 16-byte aligned");
@@ -974,9 +1087,10 @@ extern "C" int qdpx_jit_eval(qdpx_ctx *ctx, int32_t kernel, const qdpx_geom *geo
     // the fields and half the links is beyond its L2.
     LaunchCfg cfg;
     const int bytes = k.prec == QDPX_F64 ? 192 + 192 : 96 + (k.nrows == 2 ? 96 : 144);
-    if ((int64_t)g.V / kXcds * bytes > kXcdL2 && tile_plan(g, bytes, false, k.groups)) cfg.xcd = 2;
+    if (!k.flat && (int64_t)g.V / kXcds * bytes > kXcdL2 && tile_plan(g, bytes, false, k.groups)) cfg.xcd = 2;
     order_blocks(g, cfg, k.groups, bytes, false);
     JitGeo geo = jit_geo(g, cfg.xcd);
+    FlatGeo flat = flat_geo(g, k.prec, fb * (k.n_fields + 1));
     int L0 = geom->L[0], L1 = geom->L[1], L2 = geom->L[2], L3 = geom->L[3];
     double *partials = norm2 ? (double *)work : nullptr;
     // kernel arguments in declaration order
@@ -988,7 +1102,7 @@ extern "C" int qdpx_jit_eval(qdpx_ctx *ctx, int32_t kernel, const qdpx_geom *geo
     args.push_back(&L1);
     args.push_back(&L2);
     args.push_back(&L3);
-    args.push_back(&geo);
+    args.push_back(k.flat ? (void *)&flat : (void *)&geo);
     args.push_back(&U);
     for (int i = 0; i < k.n_fields; ++i) {
         fptr[i] = fields[i];
