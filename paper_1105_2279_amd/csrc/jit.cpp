@@ -615,7 +615,7 @@ bool rereads(const Node &n, int m, std::array<int, 4> at, std::map<int, std::arr
 // The form of an expression's kernel.
 struct Form {
     const Node *sum = nullptr;  // its directions go to the waves of a group
-    int split = 0;              // waves a group then
+    int split = 0;              // waves a group then: 2 for two directions, else 4
     bool flat = false;          // no array read at several sites: blocks in plain order
     int groups() const { return split ? 4 / split : 4; }  // 64-site groups a block of 256 threads takes
 };
@@ -623,7 +623,7 @@ Form form_of(const Node &root) {
     Form f;
     f.sum = split_sum(root);
     if (f.sum) {
-        f.split = 4;
+        f.split = __builtin_popcount(f.sum->mask) == 2 ? 2 : 4;
     } else {
         std::map<int, std::array<int, 4>> seen;
         f.flat = !rereads(root, 0, {0, 0, 0, 0}, seen);
@@ -637,7 +637,11 @@ Form form_of(const Node &root) {
 // finishes the components it owns.  The smearing update with its norm, one
 // site per lane and the directions in a loop of two at a time, against split:
 // 205 / 158 us at 24^3x48 in FP64, 520 / 466 us at 32^3x64, 277 / 241 us there
-// in FP32-12, 58 / 43 us at 14x18x22x30 in FP64. 
+// in FP32-12, 58 / 43 us at 14x18x22x30 in FP64.  A sum of two directions takes
+// two waves a group, as two of four have nothing to do (in a loop / four waves /
+// two): two forward hops in FP64 13.3 / 14.6 / 12.3 us at 16^3x32, 79 / 56 / 54 us
+// at 24^3x48; the smearing update over two directions in FP32-12 9.2 / 10.3 / 7.9
+// us at 16^3x32.
 //
 // An expression that reads every array at one site only (a single hop, an
 // axpy) finds nothing in a cache whatever the block order, and what a wave

@@ -1,6 +1,7 @@
-"""Generated kernels by form against the reference evaluator: flat kernels in
-ranges and in dispatch order (FP64 fields of more than 256 MB in all), with the
-norm."""
+"""Generated kernels by form against the reference evaluator: two waves a group
+(a block of two groups, the second past the end or ragged, in contiguous and
+tile order) and flat kernels in ranges and in dispatch order (FP64 fields of
+more than 256 MB in all), with the norm."""
 
 import numpy as np
 import pytest
@@ -13,8 +14,11 @@ from oracle import expr
 
 pytestmark = pytest.mark.gpu
 
+TWO = ["(sum 0x9 (umul m (shift f0 + m)))",
+       "(sub (shift f1 - 2) (scale s0 (sum 0x6 (add (umul m (shift f0 + m)) (shift (uadj m f0) - m)))))"]
 FLAT = ["(umul 3 (shift f0 + 3))", "(add f0 (scale s0 (shift (uadj 0 f1) - 0)))"]
-# 1 group; 3 and 7, the last ragged; 2 and 130; FP64 fields of 270 MB
+# 1 group; 3 and 7, the last ragged; 2 and 130 of columns; the tile order in
+# FP64 (from 88 K sites on) and in all formats (175 K), and FP64 fields of 270 MB
 LATTICES = [(4, 4, 2, 2), (3, 5, 4, 3), (3, 5, 4, 7), (4, 4, 4, 2), (8, 8, 13, 10), (24, 16, 24, 20)]
 
 
@@ -27,7 +31,7 @@ def test_forms(L, prec, fmt, tmp_path, monkeypatch):
     fields = [latgen.dirac_field(L, 7801 + i) for i in range(2)]
     Ud = q.links_to_device(c, L, U, prec, fmt, dev())
     fd = [q.fermion_to_device(c, L, f, prec, dev()) for f in fields]
-    for e in FLAT:
+    for e in TWO + FLAT:
         k = q.qdpx_jit_compile(c, e, prec, fmt, n_fields, 1)
         out, n2 = q.alloc_fermion(L, prec, dev()), torch.zeros(1, dtype=torch.float64, device=dev())
         q.qdpx_jit_eval(c, k, L, Ud, fd + [fd[1]] * (n_fields - 2), sc, out, n2,

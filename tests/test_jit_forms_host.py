@@ -1,6 +1,7 @@
 """The form of a generated kernel by its expression: an array read at several
 sites asks for the block orders' geometry, an expression that reads every
-array at one site does without it (it precedes the first load of every wave)."""
+array at one site does without it (it precedes the first load of every wave),
+and a sum of two directions takes two waves of a group, not two of four."""
 
 import pytest
 
@@ -12,7 +13,8 @@ FLAT = ["f0", "(add f0 (scale s0 f1))", "(umul 0 (shift f0 + 0))", "(shift (uadj
 GEOMETRY = ["(add f0 (shift f0 + 1))", "(umul 1 (shift (umul 1 f0) + 1))", "(add (umul 0 f0) (shift (uadj 0 f1) - 0))",
             "(sub (sum 0x3 (umul m (shift f0 + m))) (sum 0x3 (shift (uadj m f0) - m)))",
             "(umul 2 (sum 0x5 (shift f0 + m)))"]
-SPLIT = [("(sum 0x7 (umul m (shift f0 + m)))", 4), ("(scale s0 (sum 0xF (umul m (shift f0 + m))))", 4)]
+SPLIT = [("(sum 0x9 (umul m (shift f0 + m)))", 2), ("(add f1 (sum 0x6 (shift (uadj m f0) - m)))", 2),
+         ("(sum 0x7 (umul m (shift f0 + m)))", 4), ("(scale s0 (sum 0xF (umul m (shift f0 + m))))", 4)]
 
 
 @pytest.mark.parametrize("prec,fmt", [(q.F64, q.LINK18), (q.F32, q.LINK12)], ids=["f64", "f32_12"])
