@@ -633,6 +633,18 @@ enum ApeMode { kApe = 0, kApePlaq = 1 };
 constexpr int kF64LinkLds = 6 * 64;
 __host__ __device__ constexpr int f64_lds_per_wave(int mode) { return 2 * kF64LinkLds + (mode ? 64 : 0); }
 
+// The phases in which a plane of mask lies, bit p for phase p.  The others are
+// passed over: with two directions smeared two of the three (24^3x48 in x and
+// y: 243 to 177 us; a copy of 32^3x64, no direction smeared, 869 to 495).
+__device__ __forceinline__ unsigned f64_phases(unsigned mask) {
+    const unsigned n1 = mask & (mask >> 1), n2 = mask & (mask >> 2), n3 = mask & (mask >> 3);
+    return ((n1 & 5u) ? 1u : 0u) | ((n2 & 3u) ? 2u : 0u) | (((n3 & 1u) | (n1 & 2u)) ? 4u : 0u);
+}
+__device__ __forceinline__ int next_phase(unsigned phases, int p) {  // the first from p on, or 3
+    const unsigned rest = phases >> p;
+    return rest ? p + __builtin_ctz(rest) : 3;
+}
+
 // v[i] for a per-lane i in 0..3, by the two bits of i
 __device__ __forceinline__ int sel4(int i, int a, int b, int c, int d) {
     const int lo = (i & 1) ? b : a, hi = (i & 1) ? d : c;
@@ -709,14 +721,17 @@ __device__ __forceinline__ void ape_group_f64(const Geo &g, const LinksRO<double
     int f_mu, f_nu, b_nu;
     auto active = [&](int nu) { return smear && ((mask >> nu) & 1u); };
     M3<double> B;          // U_mu(x+nu) of the coming phase
+    const unsigned phases = MODE != kApe ? 7u : f64_phases(mask);  // wave-uniform; traces: every plane
+    int p = next_phase(phases, 0);
     {
+        const int nu = mu ^ (p < 3 ? p + 1 : 1);
         int b_mu;
         hops_v(g, edges, mu, f_mu, b_mu);
-        hops_v(g, edges, mu ^ 1, f_nu, b_nu);
+        hops_v(g, edges, nu, f_nu, b_nu);
         M3<double> bl, u;
         ld_lane_rows01(dmu, U.S, s + b_mu, bl);
         ld_lane_rows01(dmu, U.S, s, u);
-        ld_lane_rows01(dmu, U.S, active(mu ^ 1) ? s + f_nu : s, B);
+        ld_lane_rows01(dmu, U.S, active(nu) ? s + f_nu : s, B);
         __builtin_amdgcn_sched_barrier(0);  // every load first
         // columns 0 and 1 of the backward link U_mu(x-mu) (all the lower
         // staple reads), entry 2k + i holding element (k, i), and rows 0 and
@@ -739,7 +754,8 @@ __device__ __forceinline__ void ape_group_f64(const Geo &g, const LinksRO<double
         for (int j = 0; j < 3; ++j) S[i][j] = Cx<double>{0.0, 0.0};
     if constexpr (MODE != kApe) trace[0] = trace[64] = 0.0;
 #pragma unroll 1
-    for (int p = 0; p < 3; ++p) {
+    for (int pn; p < 3; p = pn) {
+        pn = next_phase(phases, p + 1);
         const int xm = 16 * (p + 1), pl = lane ^ xm;  // the partner's lane
         const int nu = mu ^ (p + 1);
         // plane (mu, nu) is smeared for this lane exactly when it is for the
@@ -830,9 +846,9 @@ __device__ __forceinline__ void ape_group_f64(const Geo &g, const LinksRO<double
             }
         }
         __builtin_amdgcn_sched_barrier(0);
-        if (p < 2) {
-            hops_v(g, edges, mu ^ (p + 2), f_nu, b_nu);
-            ld_lane_rows01(dmu, U.S, active(mu ^ (p + 2)) ? s + f_nu : s, B);
+        if (pn < 3) {
+            hops_v(g, edges, mu ^ (pn + 1), f_nu, b_nu);
+            ld_lane_rows01(dmu, U.S, active(mu ^ (pn + 1)) ? s + f_nu : s, B);
         }
         __builtin_amdgcn_sched_barrier(0);
         if (act) {
