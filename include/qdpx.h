@@ -412,8 +412,10 @@ int qdpx_jit_eval(qdpx_ctx *ctx, int32_t kernel, const qdpx_geom *geom, const vo
  * wave, the block order over the 8 XCDs (xcd_map 0: dispatch order; 1: each
  * XCD a contiguous range of groups; 2: each XCD tiles of the (y, z) cross
  * section that its L2 holds, each walked t plane by t plane, used where the
- * groups of a t plane are a whole number, else order 0), the number of t
- * planes walked together, and the LDS tile of the FP32 APE step with the
+ * groups of a t plane are a whole number, else order 0; a call in fewer than
+ * all directions takes order 1 in its place where that is the faster one for
+ * those directions and that size, unless qdpx_tune_set gave the geometry), the
+ * number of t planes walked together, and the LDS tile of the FP32 APE step with the
  * Gram-Schmidt projection (lds_tile 0: every link loaded through the caches;
  * 1: each 64-site group's own links, rows 0 and 1, staged in LDS once for the
  * four direction waves; 2: also every site's backward links U_mu(x-mu),

@@ -372,31 +372,18 @@ static LaunchCfg cfg_for(qdpx_ctx *ctx, qdpx_op op, const qdpx_geom *geom, qdpx_
     if (op == QDPX_OP_APE || op == QDPX_OP_SHIFT || op == QDPX_OP_CHAIN || op == QDPX_OP_JACOBI) {
         Geo g = make_geo(geom->L);
         const int bytes = reread_bytes(op, prec, fmt);
-        // Tiles where an XCD's share no longer fits its L2.  Smearing steps, shift
-        // and chain: from 6 MB on, as contiguous ranges lose little to 4 MB and
-        // balance better on so few groups (us, ranges / tiles: FP32-18 step 16^3x32,
-        // 4.5 MB, 32.7 / 35.4; FP64 6 MB 47.8 / 48.9; 20^3x40 11 MB 77.4 / 76.2; FP64
-        // chain 16x20^2x36, 5.3 MB, 47.3 / 49.7).  The Jacobi hop, to both sides in
-        // every direction: from 4 MB (FP64 12x24x16x28, 5.9 MB, 27.7 / 24.2).
-        const int64_t room = op == QDPX_OP_JACOBI ? kXcdL2 : kXcdL2 * 3 / 2;
-        const bool far = (int64_t)g.V / kXcds * bytes > room;
-        if (far && tile_plan(g, bytes, fwd_only(op), groups_per_block(op, c))) c.xcd = 2;
+        if (tiles_by_default(op, (int64_t)g.V / kXcds * bytes) && tile_plan(g, bytes, fwd_only(op), groups_per_block(op, c)))
+            c.xcd = 2;
     }
     return c;
 }
 
 // The launch of op in the directions of mask on g: its geometry and, in g,
-// the tiles of its block order.  Without the t direction the slab walk has
-// nothing to keep for the next t plane and its tiles' halos are read for
-// nothing: contiguous ranges, unless the lattice is so large (kFarRanges an
-// XCD) that eight ranges that far apart cost more than the halos (FP64 Jacobi
-// hop in x, y, z: 51.8 against 55.1 us at 20^3x40, 15 MB; 127.9 against 117.6
-// us at 24^3x48, 32 MB).
-constexpr int64_t kFarRanges = 28 << 20;
-
+// the tiles of its block order.
 static LaunchCfg plan_launch(Geo &g, LaunchCfg c, qdpx_op op, qdpx_prec prec, qdpx_linkfmt fmt, uint32_t mask = 0xF) {
-    if (c.xcd == 2 && !(mask & 8) && (int64_t)g.V / kXcds * reread_bytes(op, prec, fmt) <= kFarRanges) c.xcd = 1;
-    order_blocks(g, c, groups_per_block(op, c), reread_bytes(op, prec, fmt), fwd_only(op));
+    const int bytes = reread_bytes(op, prec, fmt);
+    if (c.xcd == 2 && !c.given && ranges_for_mask(op, g.P != 0, (int64_t)g.V / kXcds * bytes, mask)) c.xcd = 1;
+    order_blocks(g, c, groups_per_block(op, c), bytes, fwd_only(op));
     return c;
 }
 
@@ -973,6 +960,7 @@ extern "C" int qdpx_tune_set(qdpx_ctx *ctx, qdpx_op op, const qdpx_geom *geom, q
     c.xcd = xcd_map;
     c.tw = t_window;
     c.lds = lds_tile;
+    c.given = true;
     if (!cfg_valid(op, prec, c) || geom->L[3] % c.tw != 0)
         return fail(QDPX_EINVAL,
                     "%s: geometry (block %d, sites %d, xcd %d, t window %d, LDS tile %d) not valid for op %d", fn,

@@ -4,6 +4,7 @@
 // FP64 partial sums.
 #include <type_traits>
 
+#include "../../include/qdpx.h"
 #include "qdpx_impl.hpp"
 #include "reduce_device.hpp"
 
@@ -111,6 +112,42 @@ bool tile_plan(Geo &g, int bytes, bool fwd_only, int groups_per_block) {
     g.dnyt = FastDiv::make(nyt);
     g.dtiles = FastDiv::make(nyt * nzt);
     return true;
+}
+
+// Tiles where an XCD's share no longer fits its L2.  The Jacobi hop, to both
+// sides in every direction: from 4 MB (FP64 12x24x16x28, 5.9 MB, ranges / tiles
+// 27.7 / 24.2 us).  Smearing steps, shift and chain: from 6 MB on, as contiguous
+// ranges lose little to 4 MB and balance better on so few groups (FP32-18 step
+// 16^3x32, 4.5 MB, 32.7 / 35.4; FP64 6 MB 47.8 / 48.9; 20^3x40 11 MB 77.4 / 76.2;
+// FP64 chain 16x20^2x36, 5.3 MB, 47.3 / 49.7).  The shift also keeps ranges where
+// its field as a whole is within the 256 MB cache but not much smaller, so that
+// the t neighbours come from there (FP32: 36^4, 19 MB, 1.07 times the time in
+// tiles, 16^2x256x32 and 32^3x64, 24 MB, 1.04 to 1.08; below and above tiles win:
+// 128^2x8^2, 12 MB, 118 / 92 us; FP64 28^3x56, 28 MB, 1.12 times the time in
+// ranges).
+bool tiles_by_default(int op, int64_t share) {
+    if (op == QDPX_OP_JACOBI) return share > kXcdL2;
+    if (op == QDPX_OP_SHIFT && share > 16 << 20 && share <= 26 << 20) return false;
+    return share > kXcdL2 * 3 / 2;
+}
+
+// A slab walk keeps a t plane for the next; without the t direction, or for the
+// shift in t alone, its tiles only have their halos to read twice.  Contiguous
+// ranges then, unless the lattice is so large that eight ranges that far apart
+// cost more.  Ranges over tiles, time: the shift (to one side) 0.88 to 1.0 up to
+// 24 MB, 1.06 and more from 27 MB on; the hop in x, y and z 0.90 to 1.0 up to 28
+// MB, 1.02 to 1.11 at 30 to 38; in one or two of them 0.80 to 0.97 up to 48 MB,
+// 1.02 to 1.1 from 54 on; the smearing step 0.87 to 1.0 up to 38 MB, 1.01 to 1.08
+// from 40 on, where the groups of an xy plane are not a whole number and a tile
+// is a stretch of z planes 0.95 to 1.0 up to 58 MB.
+bool ranges_for_mask(int op, bool planes, int64_t share, unsigned mask) {
+    const int n = __builtin_popcount(mask & 7u);
+    int mb = 0;
+    if (op == QDPX_OP_SHIFT) mb = !(mask & 8u) || n == 0 ? 26 : 0;
+    else if (mask & 8u) mb = 0;
+    else if (op == QDPX_OP_JACOBI) mb = n == 3 ? 28 : 50;
+    else mb = planes ? 40 : 60;
+    return share <= (int64_t)mb << 20;
 }
 
 void order_blocks(Geo &g, LaunchCfg &cfg, int groups_per_block, int bytes, bool fwd_only) {

@@ -21,6 +21,7 @@ struct LaunchCfg {
     int lds = 0;      // LDS tile of the FP32 APE step: 0 none, 1 own links, 2 also backward links,
                       // 3 also the plane products, 4 own links and plane products
     int grid = 0;     // blocks of the launch (order_blocks)
+    bool given = false;  // by qdpx_tune_set: its block order holds for every direction mask
 };
 
 // Threads per block of the fixed-shape reduction kernels (plaquette,
@@ -52,6 +53,13 @@ bool tile_plan(Geo &g, int bytes, bool fwd_only, int groups_per_block);
 // beyond the L2 once, and a lattice of few groups has no tiles); above, the
 // slab walk.
 constexpr int64_t kXcdL2 = 4 << 20;
+// Whether operation op takes tiles by default in all directions, where a plan
+// exists and an XCD's share of what it reads again is `share` bytes; and
+// whether in the directions of mask it takes contiguous ranges instead,
+// although its geometry (default, tuned in all directions, or stored) says
+// tiles.
+bool tiles_by_default(int op, int64_t share);
+bool ranges_for_mask(int op, bool planes, int64_t share, unsigned mask);
 // Settles the order of a launch of groups_per_block 64-site groups a block:
 // the tiles of the slab walk in g, and in cfg the order and the grid.  Every
 // launch of a kernel that takes a LaunchCfg takes both from here.
