@@ -131,7 +131,8 @@ typedef struct qdpx_ctx qdpx_ctx;
  *   "fmt": "LINK12", "L": [Lx, Ly, Lz, Lt], "launch": [block,
  *   groups_per_wave, xcd_map, t_window, lds_tile]}, ...]}, op one of SHIFT
  *   CHAIN APE PLAQ BATCHED JACOBI, prec F64 or F32, fmt LINK18 or LINK12
- *   (a four-element "launch" is read with the default lds_tile).
+ *   (a four-element "launch" is read with the default lds_tile; a BATCHED
+ *   entry may have "groups", the 64-site groups of the batch it was tuned on).
  *   With the environment variable QDPX_LOG set (not "" or "0") the library
  *   prints one line on stderr per table read or write and per tuned geometry.
  * Returns QDPX_EINVAL for a null `out`, a device that does not exist, or a
@@ -351,8 +352,11 @@ int qdpx_plaquette(qdpx_ctx *ctx, const qdpx_geom *geom, qdpx_prec prec, qdpx_li
  * walked t-row by t-row.  Threads per block (256 or 512) and groups per
  * ticket come from qdpx_tune_batched, or qdpx_tune_set(ctx, QDPX_OP_BATCHED,
  * &geoms[0], prec, fmt, block, groups, 1, 1, 0) (default 256 and 1;
- * 512 and 2 for a batch of at most 16384 groups, 2^20 sites).  The final
- * plaquettes are qdpx_plaquette's pass on each lattice's output. */
+ * 512 and 2 for a batch of at most 16384 groups, 2^20 sites).  A geometry that
+ * qdpx_tune_batched found, or a launch table holds with "groups", is used for
+ * batches on the same side of 16384 groups as its own, others take the
+ * default; one that qdpx_tune_set gave, or a table holds without, for all.  The
+ * final plaquettes are qdpx_plaquette's pass on each lattice's output. */
 int qdpx_ape_smear_batched(qdpx_ctx *ctx, int n_lat, const qdpx_geom *geoms, qdpx_prec prec,
                            qdpx_linkfmt fmt, const void *const *U_in, void *const *U_out,
                            double alpha, int n_steps, double *plaq, void *work, size_t work_bytes,
@@ -442,7 +446,8 @@ int qdpx_jit_eval(qdpx_ctx *ctx, int32_t kernel, const qdpx_geom *geom, const vo
  * For QDPX_OP_BATCHED (tuned by qdpx_tune_batched, which qdpx_tune refuses
  * with QDPX_EUNSUPPORTED) block is 256 or 512 and sites_per_thread is the
  * number of 64-site groups per work ticket, keyed by the first lattice's
- * extents. */
+ * extents; qdpx_tune_get does not know the batch and gives the geometry
+ * remembered for those extents, else the default of a large batch. */
 int qdpx_tune(qdpx_ctx *ctx, qdpx_op op, const qdpx_geom *geom, qdpx_prec prec, qdpx_linkfmt fmt,
               void *stream);
 int qdpx_tune_get(qdpx_ctx *ctx, qdpx_op op, const qdpx_geom *geom, qdpx_prec prec, qdpx_linkfmt fmt,

@@ -74,6 +74,7 @@ enum { kSrcDefault = 0, kSrcTable = 1, kSrcTuned = 2, kSrcSet = 3 };
 struct Tuned {
     LaunchCfg cfg;
     int source = kSrcDefault;
+    int groups = 0;  // TuneEntry::groups
 };
 
 struct qdpx_ctx {
@@ -176,7 +177,7 @@ extern "C" int qdpx_create(qdpx_ctx **out, int device, const char *tune_cache_pa
     c->scratch = (double *)sp;
     for (const TuneEntry &t : entries) {
         const TuneKey k{t.op, t.prec, t.fmt, {t.L[0], t.L[1], t.L[2], t.L[3]}};
-        c->tuned[k] = Tuned{t.cfg, kSrcTable};
+        c->tuned[k] = Tuned{t.cfg, kSrcTable, t.groups};
         log_cfg("table", k, t.cfg);
     }
     *out = c;
@@ -190,10 +191,11 @@ static int save_table(qdpx_ctx *ctx, const std::string &path, const char *fn) {
     std::string err;
     const int r = tune_table_read(path.c_str(), ctx->arch.c_str(), merged, err);
     if (r < 0) return fail(QDPX_EINVAL, "%s: launch table %s", fn, err.c_str());
-    std::map<TuneKey, LaunchCfg> all;
-    for (const TuneEntry &t : merged) all[TuneKey{t.op, t.prec, t.fmt, {t.L[0], t.L[1], t.L[2], t.L[3]}}] = t.cfg;
+    std::map<TuneKey, Tuned> all;
+    for (const TuneEntry &t : merged)
+        all[TuneKey{t.op, t.prec, t.fmt, {t.L[0], t.L[1], t.L[2], t.L[3]}}] = Tuned{t.cfg, kSrcTable, t.groups};
     for (const auto &kv : ctx->tuned)
-        if (kv.second.source != kSrcDefault) all[kv.first] = kv.second.cfg;
+        if (kv.second.source != kSrcDefault) all[kv.first] = kv.second;
     std::vector<TuneEntry> rows;
     for (const auto &kv : all) {
         TuneEntry t;
@@ -201,7 +203,8 @@ static int save_table(qdpx_ctx *ctx, const std::string &path, const char *fn) {
         t.prec = kv.first.prec;
         t.fmt = kv.first.fmt;
         for (int d = 0; d < 4; ++d) t.L[d] = kv.first.L[d];
-        t.cfg = kv.second;
+        t.cfg = kv.second.cfg;
+        t.groups = kv.second.groups;
         rows.push_back(t);
     }
     if (tune_table_write(path.c_str(), ctx->arch.c_str(), rows, err) != 0)
@@ -766,7 +769,7 @@ static unsigned spin_limit_from_env() {
     return (unsigned)strtoul(e, nullptr, 10);
 }
 
-// A batch of few groups without a stored geometry takes blocks of 512 threads
+// A batch of few groups without a geometry of its own takes blocks of 512 threads
 // and two groups a ticket: half as many blocks meet at the end of a phase.  3
 // lattices, 68280 sites, three steps: FP32-12 113 against 151 us with 256 and 1,
 // FP64 154 against 180; 836096 sites FP32-18 807 / 835; 664574 FP64 1021 / 1039.
@@ -774,12 +777,25 @@ static unsigned spin_limit_from_env() {
 // 2366 / 2265 us, FP32-12 1238 / 1242; 64 lattices of 14.4 million 15.3 / 15.0 ms.
 constexpr int64_t kBatchSmallGroups = 16384;
 
-static LaunchCfg batched_cfg(qdpx_ctx *ctx, int n_lat, const qdpx_geom *geoms, qdpx_prec prec, qdpx_linkfmt fmt) {
-    LaunchCfg c = cfg_for(ctx, QDPX_OP_BATCHED, &geoms[0], prec, fmt);
-    const int32_t *L = geoms[0].L;
-    if (ctx->tuned.count(TuneKey{(int)QDPX_OP_BATCHED, (int)prec, (int)fmt, {L[0], L[1], L[2], L[3]}})) return c;
+static int64_t batch_groups(int n_lat, const qdpx_geom *geoms) {
     int64_t groups = 0;
     for (int i = 0; i < n_lat; ++i) groups += (make_geo(geoms[i].L).V + 63) / 64;
+    return groups;
+}
+
+// An entry is kept by the first lattice's extents alone; one that was tuned on a
+// batch on the other side of that line is not for this one (a single 8^4 lattice
+// in FP32-12, one step: 18.0 us with the geometry of the 64 lattices, 12.1).
+static LaunchCfg batched_cfg(qdpx_ctx *ctx, int n_lat, const qdpx_geom *geoms, qdpx_prec prec, qdpx_linkfmt fmt) {
+    const int32_t *L = geoms[0].L;
+    const int64_t groups = batch_groups(n_lat, geoms);
+    const auto it = ctx->tuned.find(TuneKey{(int)QDPX_OP_BATCHED, (int)prec, (int)fmt, {L[0], L[1], L[2], L[3]}});
+    if (it != ctx->tuned.end()) {
+        const int on = it->second.groups;
+        if (!on || (on <= kBatchSmallGroups) == (groups <= kBatchSmallGroups)) return it->second.cfg;
+    }
+    LaunchCfg c;
+    c.nsite = 1;
     if (groups <= kBatchSmallGroups) {
         c.block = 512;
         c.nsite = 2;
@@ -1177,7 +1193,7 @@ extern "C" int qdpx_tune_batched(qdpx_ctx *ctx, int n_lat, const qdpx_geom *geom
     const float best = best_ms[bi];
     cleanup();
     if (best >= 1e30f) return fail(QDPX_EHIP, "%s: no candidate geometry ran", fn);
-    ctx->tuned[key] = Tuned{cands[bi], kSrcTuned};
+    ctx->tuned[key] = Tuned{cands[bi], kSrcTuned, (int)std::min<int64_t>(batch_groups(n_lat, geoms), INT32_MAX)};
     log_cfg("tuned", key, cands[bi]);
     if (!ctx->cache_path.empty()) return save_table(ctx, ctx->cache_path, fn);
     return QDPX_OK;

@@ -35,6 +35,7 @@ struct TuneEntry {
     int op = 0, prec = 0, fmt = 0;
     int L[4] = {0, 0, 0, 0};
     LaunchCfg cfg;
+    int groups = 0;  // BATCHED: 64-site groups of the batch it was tuned on, 0: for any
 };
 // 0: read; 1: no such file; 2: the file was recorded on another
 // architecture (out stays empty); -1: unreadable or malformed (err set).

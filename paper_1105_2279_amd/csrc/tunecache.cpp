@@ -5,7 +5,8 @@
 //   {"device": "gfx950:...", "entries": [
 //     {"op": "APE", "prec": "F32", "fmt": "LINK12", "L": [32, 32, 32, 64],
 //      "launch": [block, groups_per_wave, xcd_map, t_window, lds_tile]}, ...]}
-// (a four-element "launch" leaves lds_tile at -1: the operation's default).
+// (a four-element "launch" leaves lds_tile at -1: the operation's default; a
+// BATCHED entry may have "groups", the 64-site groups of its batch).
 // Entries recorded on another architecture (the part of "device" before the
 // first ':') are ignored.  This reader accepts any JSON value where the
 // schema does not care (unknown keys are skipped) and rejects everything
@@ -262,6 +263,9 @@ int tune_table_read(const char *path, const char *arch, std::vector<TuneEntry> &
         t.cfg.xcd = launch[2];
         t.cfg.tw = launch[3];
         t.cfg.lds = launch[4];
+        const JVal *groups = e.get("groups");
+        if (groups && groups->kind == JVal::kNum && groups->num >= 1.0 && groups->num < 2147483648.0)
+            t.groups = (int)groups->num;
         out.push_back(t);
     }
     return 0;
@@ -275,12 +279,13 @@ int tune_table_write(const char *path, const char *arch, const std::vector<TuneE
     bool first = true;
     for (const TuneEntry &t : in) {
         if (t.op < 0 || t.op >= 6 || t.prec < 0 || t.prec >= 2 || t.fmt < 0 || t.fmt >= 2) continue;
-        char line[256];
+        char line[288], groups[32] = "";
+        if (t.groups > 0) snprintf(groups, sizeof groups, ", \"groups\": %d", t.groups);
         snprintf(line, sizeof line,
                  "%s\n  {\"op\": \"%s\", \"prec\": \"%s\", \"fmt\": \"%s\", \"L\": [%d, %d, %d, %d], "
-                 "\"launch\": [%d, %d, %d, %d, %d]}",
+                 "\"launch\": [%d, %d, %d, %d, %d]%s}",
                  first ? "" : ",", kOpNames[t.op], kPrecNames[t.prec], kFmtNames[t.fmt], t.L[0], t.L[1], t.L[2], t.L[3],
-                 t.cfg.block, t.cfg.nsite, t.cfg.xcd, t.cfg.tw, t.cfg.lds);
+                 t.cfg.block, t.cfg.nsite, t.cfg.xcd, t.cfg.tw, t.cfg.lds, groups);
         s += line;
         first = false;
     }
