@@ -430,8 +430,9 @@ int qdpx_jit_eval(qdpx_ctx *ctx, int32_t kernel, const qdpx_geom *geom, const vo
  * products, the backward links loaded; 0 in every other case: the FP64 step
  * always exchanges its own and backward links through LDS, and the shift, hop
  * and chain kernels meet their per-direction partial sums there).  The APE
- * step of a lattice of few groups takes a kernel of its own, whatever the
- * geometry.
+ * step of a lattice of few groups takes a kernel of its own with the
+ * Gram-Schmidt projection, whatever the geometry; qdpx_tune then times the
+ * polar step.
  * This is the auto-tuning of the thread geometry the paper proposes
  * (sections 5.4 and 9).  Allocates and frees temporary device buffers and
  * synchronises the device, so it returns QDPX_ECAPTURE on a capturing

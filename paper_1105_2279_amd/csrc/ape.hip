@@ -99,6 +99,10 @@ __global__ void __launch_bounds__(192) k_ape_split(Geo g, LinksRO<R, NR> U, Link
     ape_split<R, NR, MODE>(g, U, out, c1, c2, mask, partials, b >> 2, b & 3, w, (int)(threadIdx.x & 63), part);
 }
 
+bool ape_splits(const Geo &g, int prec, int proj) {
+    return !proj && (g.V + 63) / 64 <= (prec == 0 ? kSplitGroups64 : kSplitGroups32);
+}
+
 int ape_num_partials(const Geo &g) { return 4 * ((g.V + 63) / 64); }
 
 hipError_t launch_ape_step(const Geo &g, int prec, int nrows, const void *Uin, void *Uout, double c1, double c2,
@@ -109,7 +113,7 @@ hipError_t launch_ape_step(const Geo &g, int prec, int nrows, const void *Uin, v
     if (proj && mode != kApe) return hipErrorInvalidValue;             // polar: plaquettes in their own pass
     if (prec != 0 && mode != kApe) return hipErrorInvalidValue;        // FP32: plaquettes from k_plaquette
     const int groups = (g.V + 63) / 64;
-    if (!proj && groups <= (prec == 0 ? kSplitGroups64 : kSplitGroups32)) {
+    if (ape_splits(g, prec, proj)) {
 #define QDPX_SPLIT_LAUNCH(R, NR, M)                                                                        \
     k_ape_split<R, NR, M><<<4 * groups, 192, 0, st>>>(g, LinksRO<R, NR>{(const vec2_t<R> *)Uin, g.S},      \
                                                       LinksWO<R, NR>{(vec2_t<R> *)Uout, g.S}, c1, c2, mask, partials)

@@ -1029,6 +1029,10 @@ extern "C" int qdpx_tune(qdpx_ctx *ctx, qdpx_op op, const qdpx_geom *geom, qdpx_
         release();
         return fail(QDPX_ENOMEM, "%s: could not allocate tuning buffers", fn);
     }
+    // on a lattice of few groups only the polar step has a geometry, and no LDS tile
+    const int proj = op == QDPX_OP_APE && ape_splits(geo, prec, 0) ? 1 : 0;
+    const int lds_default = default_lds(op, prec);
+    const int lds_first = proj ? lds_default : 0, lds_last = proj ? lds_default : prec == QDPX_F32 ? 4 : 0;
     std::vector<LaunchCfg> cands;
     const int blocks_ape[] = {256, 512};
     const int ns_ape[] = {1, 2, 4};
@@ -1040,7 +1044,7 @@ extern "C" int qdpx_tune(qdpx_ctx *ctx, qdpx_op op, const qdpx_geom *geom, qdpx_
             if (op == QDPX_OP_APE) {
                 for (int b : blocks_ape)
                     for (int n : ns_ape)
-                        for (int t = 0; t <= (prec == QDPX_F32 ? 4 : 0); ++t) cands.push_back(LaunchCfg{b, n, x, tw, t});
+                        for (int t = lds_first; t <= lds_last; ++t) cands.push_back(LaunchCfg{b, n, x, tw, t});
             } else {
                 for (int n : ns_shift) cands.push_back(LaunchCfg{256, n, x, tw});
             }
@@ -1055,7 +1059,7 @@ extern "C" int qdpx_tune(qdpx_ctx *ctx, qdpx_op op, const qdpx_geom *geom, qdpx_
     auto run = [&](const LaunchCfg &cand) -> hipError_t {
         Geo g = geo;
         const LaunchCfg c = plan_launch(g, cand, op, prec, fmt);
-        if (op == QDPX_OP_APE) return launch_ape_step(g, prec, nrows, U, A, 0.5, 0.5 / 6.0, 0xFu, nullptr, 0, c, st);
+        if (op == QDPX_OP_APE) return launch_ape_step(g, prec, nrows, U, A, 0.5, 0.5 / 6.0, 0xFu, nullptr, 0, c, st, proj);
         if (op == QDPX_OP_JACOBI) return launch_hop(g, prec, nrows, U, A, B, 0.1, 1.0, false, 0xFu, C, c, st);
         return launch_shift(g, prec, nrows, U, A, B, 0.3, op == QDPX_OP_CHAIN ? 1 : 0, 0.1, C, (double *)part, c, st);
     };

@@ -101,6 +101,8 @@ hipError_t launch_finalize(const double *partials, int n, int mode, double volum
 // partials hold ape_num_partials(g) values per component (spatial,
 // temporal), reduced by launch_finalize(partials, ape_num_partials(g), 1, V, out).
 int ape_num_partials(const Geo &g);
+// Whether a step takes the kernel for few groups, which has no launch geometry.
+bool ape_splits(const Geo &g, int prec, int proj);
 hipError_t launch_ape_step(const Geo &g, int prec, int nrows, const void *Uin, void *Uout, double c1, double c2,
                            unsigned mask, double *partials, int mode, const LaunchCfg &cfg, hipStream_t st,
                            int proj = 0);  // proj 1: polar projection (mode 0 only)
