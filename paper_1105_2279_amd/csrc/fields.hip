@@ -63,8 +63,15 @@ constexpr double kTilePlane = 1.25e6;
 // Added to the cost where the XCDs do not all work on tiles to the end.
 constexpr double kTilesUneven = 0.25;
 
-bool tile_plan(Geo &g, int bytes, bool fwd_only, int groups_per_block) {
-    if (!g.ncol) return false;
+// The search takes 1 to 11 us of the host, once or twice a call, so a thread
+// keeps its last few plans by what they depend on (a smearing call with two
+// steps and their plaquettes on 64^3x16 in FP32: 48 us on the host with a search
+// for each launch, 37 before there were plans).
+struct TilePlan {
+    int L[4], bytes, fwd_only, groups_per_block;
+    int by, bz, bseg;  // by 0: no plan
+};
+static TilePlan search_tiles(const Geo &g, int bytes, bool fwd_only, int groups_per_block) {
     const int Lt = g.L[3];
     const int nz = g.P ? g.L[2] : 1, pz = g.ncol / nz;  // Lz layers, or one of whole z planes
     const double sides = fwd_only ? 1.0 : 2.0;
@@ -99,16 +106,35 @@ bool tile_plan(Geo &g, int bytes, bool fwd_only, int groups_per_block) {
                 bseg = seg;
             }
         }
-    if (!by) return false;
-    const int nyt = (pz + by - 1) / by, nzt = (nz + bz - 1) / bz;
+    return TilePlan{{g.L[0], g.L[1], g.L[2], g.L[3]}, bytes, fwd_only, groups_per_block, by, bz, bseg};
+}
+
+bool tile_plan(Geo &g, int bytes, bool fwd_only, int groups_per_block) {
+    if (!g.ncol) return false;
+    constexpr int kKept = 8;
+    static thread_local TilePlan kept[kKept] = {};  // L 0: none
+    static thread_local int oldest = 0;
+    const TilePlan *p = nullptr;
+    for (const TilePlan &k : kept)
+        if (k.L[0] == g.L[0] && k.L[1] == g.L[1] && k.L[2] == g.L[2] && k.L[3] == g.L[3] && k.bytes == bytes &&
+            k.fwd_only == (int)fwd_only && k.groups_per_block == groups_per_block)
+            p = &k;
+    if (!p) {
+        kept[oldest] = search_tiles(g, bytes, fwd_only, groups_per_block);
+        p = &kept[oldest];
+        oldest = (oldest + 1) % kKept;
+    }
+    if (!p->by) return false;
+    const int nz = g.P ? g.L[2] : 1, pz = g.ncol / nz;
+    const int nyt = (pz + p->by - 1) / p->by, nzt = (nz + p->bz - 1) / p->bz;
     g.pz = pz;
     g.nz = nz;
-    g.wp = by;
-    g.wz = bz;
-    g.wseg = bseg;
+    g.wp = p->by;
+    g.wz = p->bz;
+    g.wseg = p->bseg;
     g.dwp = FastDiv::make(g.wp);
-    g.dwc = FastDiv::make(g.wp * bz);
-    g.dunit = FastDiv::make(g.wp * bz * (Lt >> bseg));
+    g.dwc = FastDiv::make(g.wp * g.wz);
+    g.dunit = FastDiv::make(g.wp * g.wz * (g.L[3] >> g.wseg));
     g.dnyt = FastDiv::make(nyt);
     g.dtiles = FastDiv::make(nyt * nzt);
     return true;
