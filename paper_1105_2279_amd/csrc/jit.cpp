@@ -619,12 +619,26 @@ struct Form {
     bool flat = false;          // no array read at several sites: blocks in plain order
     int groups() const { return split ? 4 / split : 4; }  // 64-site groups a block of 256 threads takes
 };
-Form form_of(const Node &root) {
+// Fields read outside the sum.
+int outer_fields(const Node &n) {
+    if (n.kind == Node::Sum) return 0;
+    int k = n.kind == Node::Field;
+    for (const auto &c : n.kids) k += outer_fields(*c);
+    return k;
+}
+// In FP32 a sum of two directions with three or more fields around it stays a
+// loop: each of the two waves would hold half of every field beside its
+// direction (seven fields around it, loop / split: 20.9 / 22.9 us at 16^3x32, 25.9
+// / 28.9 at 14x18x22x30; two, 12.1 / 11.6 and 15.3 / 15.8).
+Form form_of(const Node &root, int prec) {
     Form f;
     f.sum = split_sum(root);
-    if (f.sum) {
-        f.split = __builtin_popcount(f.sum->mask) == 2 ? 2 : 4;
-    } else {
+    if (f.sum) f.split = __builtin_popcount(f.sum->mask) == 2 ? 2 : 4;
+    if (f.split == 2 && prec == QDPX_F32 && outer_fields(root) > 2) {
+        f.sum = nullptr;
+        f.split = 0;
+    }
+    if (!f.sum) {
         std::map<int, std::array<int, 4>> seen;
         f.flat = !rereads(root, 0, {0, 0, 0, 0}, seen);
     }
@@ -914,7 +928,7 @@ int parse_and_generate(const char *expr, qdpx_prec prec, qdpx_linkfmt fmt, int n
         std::snprintf(msg, sizeof msg, "%s: %s", fn, p.err.c_str());
         return set_error(QDPX_EINVAL, msg);
     }
-    const Form form = form_of(*root);
+    const Form form = form_of(*root, prec);
     k.source = generate(*root, form, prec, fmt == QDPX_LINK12 ? 2 : 3, n_fields, n_scalars);
     k.groups = form.groups();
     k.flat = form.flat;

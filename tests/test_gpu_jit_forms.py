@@ -15,7 +15,9 @@ from oracle import expr
 pytestmark = pytest.mark.gpu
 
 TWO = ["(sum 0x9 (umul m (shift f0 + m)))",
-       "(sub (shift f1 - 2) (scale s0 (sum 0x6 (add (umul m (shift f0 + m)) (shift (uadj m f0) - m)))))"]
+       "(sub (shift f1 - 2) (scale s0 (sum 0x6 (add (umul m (shift f0 + m)) (shift (uadj m f0) - m)))))",
+       # three fields around it: a loop in FP32
+       "(add (sum 0x3 (umul m (shift f0 + m))) (sub (scale s0 f1) (add f0 (shift f1 + 3))))"]
 FLAT = ["(umul 3 (shift f0 + 3))", "(add f0 (scale s0 (shift (uadj 0 f1) - 0)))"]
 # 1 group; 3 and 7, the last ragged; 2 and 130 of columns; the tile order in
 # FP64 (from 88 K sites on) and in all formats (175 K), and FP64 fields of 270 MB
