@@ -152,9 +152,15 @@ def _ptr(t):
     return t.data_ptr()
 
 
+# The current stream's handle without an object for it, where torch has it.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream=None):
-    if stream is None:  # the current stream's handle, without an object for it
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if stream is None:
+        if _raw_stream is None:
+            return torch.cuda.current_stream().cuda_stream
+        return _raw_stream(torch.cuda.current_device())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
