@@ -283,8 +283,9 @@ int qdpx_jacobi_smear(qdpx_ctx *ctx, const qdpx_geom *geom, qdpx_prec prec, qdpx
  * projection: QDPX_PROJ_GRAM_SCHMIDT (the rows above; only rows 0 and 1 of
  * the staples are formed) or QDPX_PROJ_POLAR: V = W (W^dag W)^(-1/2)
  * exp(-i arg(det)/3), the unitary polar factor with the phase of its
- * determinant removed (principal branch), by nine scaled Newton iterations in
- * FP64 on the full staple sum.  The polar projection commutes with
+ * determinant removed (principal branch), by at most nine scaled Newton
+ * iterations in FP64 on the full staple sum, each link's ending when it has
+ * converged.  The polar projection commutes with
  * W -> g W h^dag for any g, h in SU(3), so the whole step commutes with a
  * gauge transformation U_mu(x) -> g(x) U_mu(x) g(x+mu)^dag; row Gram-Schmidt
  * does so only for diagonal g.

@@ -620,7 +620,9 @@ enum ApeMode { kApe = 0, kApePlaq = 1 };
 // SIMD that its registers allow, so the loads of a half phase are issued
 // while the half phase before is computed: U_mu(x-nu) before the upper
 // staple, U_nu(x-nu+mu) before the lower one's first product and the next
-// phase's U_mu(x+nu) before its second.  Against 84 loads, each half phase's
+// phase's U_mu(x+nu) before its second.  Lanes of a plane outside the smear mask
+// load their own link instead, and a phase without a plane is passed over
+// (f64_phases).  Against 84 loads, each half phase's
 // issued and waited for in it: 882 to 837 us at 32^3x64, 272 to 258 us at
 // 24^3x48 (327 to 301 us with the plaquette), 5360 to 4706 us at 48^3x96, 76 to
 // 68 us at 14x18x22x30.  Direction-dependent addresses differ between lanes

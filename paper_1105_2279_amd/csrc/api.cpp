@@ -838,7 +838,7 @@ extern "C" int qdpx_ape_smear_batched(qdpx_ctx *ctx, int n_lat, const qdpx_geom 
 
     // launch geometry: threads per block (256 or 512: one or two groups at a
     // time) and groups per ticket, tuned per (first lattice's extents,
-    // precision, format)
+    // precision, format) for batches on this one's side of kBatchSmallGroups
     const LaunchCfg bcfg = batched_cfg(ctx, n_lat, geoms, prec, fmt);
     const int block = bcfg.block == 512 ? 512 : 256;
     const int group_chunk = std::max(1, bcfg.nsite);

@@ -111,7 +111,10 @@ __device__ __forceinline__ int take_ticket(unsigned *counters, int stride, const
 // Count `items` finished items of this block as done, device-wide.  Every
 // store of theirs is in the XCD's L2 (its wave has waited for it); what makes
 // it visible to the other XCDs is the write-back of that L2, which covers all
-// of the XCD's blocks (XCC_ID names the L2).  So the blocks of an XCD share
+// of the XCD's blocks.  That rests on the MI355X beyond what the language's
+// memory model says: every workgroup with one XCC_ID stores through one L2, a
+// store counted down by vmcnt has reached it, and the waves of a workgroup share
+// a CU (no threadgroup split).  So the blocks of an XCD share
 // write-backs: `pending` holds the XCD's items that are in L2 and not yet
 // counted; the block that finds it empty writes back and counts for all,
 // until nothing is left.  A write-back by every block: 60 us a phase with 512

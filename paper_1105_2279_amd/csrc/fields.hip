@@ -38,8 +38,10 @@ Geo make_geo(const int32_t L[4]) {
     return g;
 }
 
-// The block order a launch uses: the XCD slab walk (mode 2) only where its
-// preconditions hold, else the identity order.
+// The block order where no tiles were planned: order 2 only where make_geo's own
+// tiles, eight equal ranges of columns, hold every group (tile_plan finds a plan
+// wherever they do, so order_blocks has the identity order from here), else the
+// identity order.
 int launch_order(const Geo &g, const LaunchCfg &cfg, int groups_per_block) {
     if (cfg.xcd != 2) return cfg.xcd;
     const int groups = (g.V + 63) / 64;
