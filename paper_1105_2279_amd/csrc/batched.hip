@@ -125,6 +125,9 @@ __device__ __forceinline__ void publish(unsigned *pending, unsigned *done, unsig
     while (n) {
         asm volatile("" ::"v"(n) : "memory");  // n has arrived before the write-back begins
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        // The write-back has finished.  It counts in vmcnt, but the compiler tracks
+        // none for it: with no store of its own outstanding it leaves the fence's wait out.
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __hip_atomic_fetch_add(done, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         n = __hip_atomic_fetch_sub(pending, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - n;
     }
